@@ -63,7 +63,7 @@ ckpt_status check_image(ckpt_ctx* c, int b, hipStream_t stream, bool scatter, co
     // Per-span events are reused round-robin past the unit count; timing is
     // kept for whole-image operations only.
     const bool timed = c->timing && !ids;
-    unsigned long long* partials = c->d_partials + c->geo.n_tiles * kTileParts;
+    unsigned long long* partials = c->d_partials + c->geo.n_tiles;
     HIPCHK(c, hipMemcpyAsync(c->d_expected, c->h_sums[b], c->n_chunks * 8, hipMemcpyHostToDevice, L.s_copy));
     if (scatter) {
         HIPCHK(c, hipEventRecord(c->ev_trigger, stream));
@@ -106,7 +106,7 @@ ckpt_status check_image(ckpt_ctx* c, int b, hipStream_t stream, bool scatter, co
         hipEvent_t k0 = timed ? (*L.tk0)[u] : nullptr, k1 = timed ? (*L.tk1)[u] : nullptr;
         hipError_t e;
         if (scatter)
-            e = launch_scatter(c->d_frags, c->d_tile_first, c->d_tile_last, c->geo, t_lo, t_hi, stage, lo, partials,
+            e = launch_scatter(c->d_frags, c->d_tile_src, c->geo, t_lo, t_hi, stage, lo, partials,
                                c->grid_cap, L.s_ker, k0, k1);
         else
             e = launch_checksum(c->geo, t_lo, t_hi, stage, lo, partials, c->grid_cap, L.s_ker, k0, k1);

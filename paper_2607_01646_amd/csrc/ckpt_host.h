@@ -340,10 +340,9 @@ struct ckpt_ctx {
 
     // device memory
     FragDev* d_frags = nullptr;
-    uint32_t* d_tile_first = nullptr;
-    uint32_t* d_tile_last = nullptr;
+    uint64_t* d_tile_src = nullptr;           // per tile: tile_entry()
     uint8_t* d_staging = nullptr;
-    unsigned long long* d_partials = nullptr; // [2][n_tiles * kTileParts] tile partial sums: pack, check
+    unsigned long long* d_partials = nullptr; // [2][n_tiles] tile partial sums: pack, check
     unsigned long long* d_expected = nullptr;
     unsigned long long* d_recomputed = nullptr;
     uint8_t* d_bad = nullptr;

@@ -15,25 +15,36 @@
 // subnormals pass unchanged.
 //
 // Work split.  The image is cut into power-of-two tiles of at most 8 KiB
-// that never cross a chunk.  A workgroup of 256 lanes (4 wave64) takes one
+// that never cross a chunk.  A workgroup of 512 lanes (8 wave64) takes one
 // tile (a separate instantiation strides over tiles when the grid is
-// capped).  Wave w owns the tile's 2 KiB slice w, and each lane moves two
-// 16-byte vectors of it, both loads issued before the stores; a tile shorter
-// than 8 KiB leaves its last waves idle.  Consecutive tiles go to
-// consecutive workgroups, which the hardware deals out round-robin over the
-// 8 XCDs (measured faster than giving each XCD a contiguous range).  A tile
-// inside one 16-byte-aligned fragment takes an unrolled non-temporal stream;
-// otherwise each vector finds its fragment (binary search over the tile's
-// fragment offsets in LDS), loads aligned 16-byte blocks and funnel-shifts
-// them when the fragment is misaligned, masks the fragment tail and writes
-// zeros for padding.
-// Sum reduction: per lane in 64 bits, across the wave with lane shuffles;
-// each wave stores its slice's sum (four partial sums per tile), with no
-// workgroup barrier on the streaming path.  A small second kernel adds the
-// partial sums of each chunk (and, when checking, compares with the stored
-// sum).  The hot kernel thus has no atomics and no device-scope fence: on
-// gfx950 such a fence writes back and invalidates the XCD's L2, which per
-// tile would cost more than the tile's own traffic.
+// capped): wave w owns the tile's 1 KiB slice w and each lane moves one
+// 16-byte vector; a tile shorter than 8 KiB leaves its last waves idle.
+// Consecutive tiles go to consecutive workgroups, which the hardware deals
+// out round-robin over the 8 XCDs (measured faster than giving each XCD a
+// contiguous range).
+// What bounds it: HBM, and how soon a wave's load goes out.  A copy of 8 GiB
+// with no lookup ahead of it runs at 6.6-6.8 TB/s with one vector per lane
+// and 6.1 with two, 5.0 with eight (the fewer bytes a workgroup holds, the
+// closer together the reads and writes in flight are).  With two dependent
+// lookups ahead of the load (tile -> fragment index -> fragment record) one
+// vector per lane fell to 5.3-5.6 TB/s, so each tile's table entry is the
+// address of its bytes itself.  The whole pack of a 14.2 GB shard: 4478 us
+// with 256 lanes x 2 vectors and the two lookups, 4460 with the entry alone,
+// 4385 with 512 lanes x 1.
+// A tile inside one fragment takes an unrolled non-temporal stream, with
+// unaligned 16-byte accesses on the fragment's side when the fragment is not
+// 16-byte aligned; otherwise each vector finds its fragment (binary search
+// over the tile's fragment offsets in LDS), loads aligned 16-byte blocks and
+// funnel-shifts them when the fragment is misaligned, masks the fragment
+// tail and writes zeros for padding.
+// Sum reduction: per lane in 64 bits, across the wave with lane shuffles,
+// across the workgroup in LDS; one partial sum per tile (one per wave instead
+// costs 1.4% of the pack: 32 bytes written per 8 KiB, from four waves).  A
+// small second kernel adds the partial sums of each chunk (and, when
+// checking, compares with the stored sum).  The hot kernel thus has no
+// atomics and no device-scope fence: on gfx950 such a fence writes back and
+// invalidates the XCD's L2, which per tile would cost more than the tile's
+// own traffic.
 // Addition modulo 2^64 is associative and commutative, so any order of
 // tiles gives the same bits.
 #include <hip/hip_ext.h>
@@ -48,16 +59,15 @@ namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kBlock = 256;      // lanes per workgroup (4 wave64)
+constexpr int kBlock = 512;      // lanes per workgroup (8 wave64)
 constexpr int kLdsFrags = 256;  // fragment offsets cached per tile (an 8 KiB tile holds at most 33 non-empty ones)
-constexpr int kUnroll = 2;      // 16-byte vectors per lane per batch: one batch covers an 8 KiB tile
+constexpr int kUnroll = 1;      // 16-byte vectors per lane per batch: one batch covers an 8 KiB tile
 
 enum Mode { PACK = 0, SCATTER = 1, VERIFY = 2, SUMS = 3 };
 
 struct Args {
     const FragDev* frags;
-    const uint32_t* tile_first; // first fragment holding a byte of tile t
-    const uint32_t* tile_last;  // last fragment holding a byte of tile t
+    const uint64_t* tile_src; // per tile: where its bytes are (tile_entry)
     Geometry g;
     uint64_t t_lo, t_hi;
     uint8_t* img; // PACK: destination window; SCATTER/VERIFY: source window; SUMS: unused
@@ -210,24 +220,39 @@ __device__ __forceinline__ void st(u32x4 v, u32x4* p)
     else *p = v;
 }
 
-// One wave's slice of a tile inside one 16-byte-aligned span: the n <= 64 *
-// UNROLL vectors at s (copied to d unless d is null) and their sum.  Lane l
-// takes vectors l, l + 64, ...; every guarded load is issued before the
-// first store, each a contiguous 1 KiB run per wave.  Written out without
-// a loop: a runtime trip count here measured ~1.5% slower.
-template <int UNROLL, bool NTL, bool NTS, bool STORE>
-__device__ __forceinline__ unsigned long long slice_stream(const u32x4* __restrict__ s, u32x4* __restrict__ d,
-                                                           uint32_t n, uint32_t lane)
+// 16 bytes at any address.  Unaligned vector accesses are one instruction on
+// gfx950; the memory pipe splits those that cross a cache line.
+typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+
+template <bool NT>
+__device__ __forceinline__ u32x4 ld_any(const uint8_t* p)
+{
+    const u32x4_any* q = reinterpret_cast<const u32x4_any*>(p);
+    if (NT) return __builtin_nontemporal_load(q);
+    return *q;
+}
+
+// One wave's slice of a tile: the n <= 64 * UNROLL vectors at s (copied to d
+// unless STORE is false) and their sum.  Lane l takes vectors l, l + 64, ...;
+// every guarded load is issued before the first store, each a contiguous
+// 1 KiB run per wave.  SRC_ANY / DST_ANY: that side is at any address, not
+// only a multiple of 16.  Written out without a loop: a runtime trip count
+// here measured ~1.5% slower.
+template <int UNROLL, bool NTL, bool NTS, bool STORE, bool SRC_ANY = false, bool DST_ANY = false>
+__device__ __forceinline__ unsigned long long slice_stream(const uint8_t* s, uint8_t* d, uint32_t n, uint32_t lane)
 {
     u32x4 r[UNROLL];
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u)
-        if (lane + u * 64 < n) r[u] = ld<NTL>(s + lane + u * 64);
+        if (lane + u * 64 < n)
+            r[u] = SRC_ANY ? ld_any<NTL>(s + 16 * (lane + u * 64))
+                           : ld<NTL>(reinterpret_cast<const u32x4*>(s) + lane + u * 64);
     unsigned long long acc = 0;
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u)
         if (lane + u * 64 < n) {
-            if (STORE) st<NTS>(r[u], d + lane + u * 64);
+            if (STORE && DST_ANY) *reinterpret_cast<u32x4_any*>(d + 16 * (lane + u * 64)) = r[u];
+            else if (STORE) st<NTS>(r[u], reinterpret_cast<u32x4*>(d) + lane + u * 64);
             acc += vsum(r[u]);
         }
     return acc;
@@ -290,93 +315,82 @@ __device__ __forceinline__ uint32_t find_frag_global(const FragDev* frags, uint3
     return lo;
 }
 
-// One tile: wave w owns vectors [w * slice, (w + 1) * slice) of it and
-// stores that slice's sum to partials[t * WAVES + w].
+// One tile: wave w owns vectors [w * slice, (w + 1) * slice) of it; lane 0
+// of the workgroup stores the tile's sum to partials[t].
 template <int MODE, int BLOCK, int UNROLL, bool NTL, bool NTS>
-__device__ __forceinline__ void do_tile(const Args& a, uint64_t t, uint64_t* s_off)
+__device__ __forceinline__ void do_tile(const Args& a, uint64_t t, uint64_t* s_off, unsigned long long* s_red)
 {
-    static_assert(BLOCK / 64 == kTileParts, "one partial sum per wave");
     static_assert(BLOCK * UNROLL * 16 == (1u << kMaxTileShift), "one batch per lane covers the largest tile");
     constexpr uint32_t WAVES = BLOCK / 64;
     constexpr uint32_t kSlice = 64 * UNROLL; // vectors per wave slice
     const uint32_t tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    {
-        const uint64_t base = t << a.g.tile_shift;
-        uint64_t end = base + (1ull << a.g.tile_shift);
-        if (end > a.g.image_bytes) end = a.g.image_bytes;
-        const uint32_t nvec = (uint32_t)((end - base) >> 4);
-        // Wave w owns vectors [v0, v1) of the tile (empty past a short tile's end).
-        const uint32_t v0 = w * kSlice;
-        const uint32_t v1 = v0 + kSlice < nvec ? v0 + kSlice : (nvec > v0 ? nvec : v0);
-        uint8_t* win = MODE == SUMS ? nullptr : a.img + (base - a.origin);
-        unsigned long long acc = 0;
-        if (MODE == VERIFY) {
-            acc = slice_stream<UNROLL, NTL, NTS, false>(reinterpret_cast<const u32x4*>(win) + v0, nullptr, v1 - v0, lane);
+    const uint64_t base = t << a.g.tile_shift;
+    uint64_t end = base + (1ull << a.g.tile_shift);
+    if (end > a.g.image_bytes) end = a.g.image_bytes;
+    const uint32_t nvec = (uint32_t)((end - base) >> 4);
+    // Wave w owns vectors [v0, v1) of the tile (empty past a short tile's end).
+    const uint32_t v0 = w * kSlice;
+    const uint32_t v1 = v0 + kSlice < nvec ? v0 + kSlice : (nvec > v0 ? nvec : v0);
+    uint8_t* win = MODE == SUMS ? nullptr : a.img + (base - a.origin);
+    unsigned long long acc = 0;
+    if (MODE == VERIFY) {
+        acc = slice_stream<UNROLL, NTL, NTS, false>(win + 16 * v0, nullptr, v1 - v0, lane);
+    } else {
+        const uint64_t e = a.tile_src[t];
+        if (!(e & kTileSlow)) {
+            uint8_t* fr = reinterpret_cast<uint8_t*>(e) + 16 * v0;
+            uint8_t* im = win + 16 * v0;
+            const uint32_t n = v1 - v0;
+            const bool aligned = (e & 15) == 0;
+            if (MODE == SUMS)
+                acc = aligned ? slice_stream<UNROLL, NTL, NTS, false>(fr, nullptr, n, lane)
+                              : slice_stream<UNROLL, NTL, NTS, false, true>(fr, nullptr, n, lane);
+            else if (MODE == PACK)
+                acc = aligned ? slice_stream<UNROLL, NTL, NTS, true>(fr, im, n, lane)
+                              : slice_stream<UNROLL, NTL, NTS, true, true>(fr, im, n, lane);
+            else
+                acc = aligned ? slice_stream<UNROLL, NTL, NTS, true>(im, fr, n, lane)
+                              : slice_stream<UNROLL, NTL, NTS, true, false, true>(im, fr, n, lane);
         } else {
-            const uint32_t f0 = a.tile_first[t], f1 = a.tile_last[t];
-            if (f0 == f1) {
-                const FragDev F = a.frags[f0];
-                const uint64_t p0 = base - F.off;
-                if ((F.ptr & 15) == 0 && p0 + (end - base) <= F.nbytes) {
-                    u32x4* fr = reinterpret_cast<u32x4*>(F.ptr + p0) + v0;
-                    if (MODE == SUMS)
-                        acc = slice_stream<UNROLL, NTL, NTS, false>(fr, nullptr, v1 - v0, lane);
-                    else if (MODE == PACK)
-                        acc = slice_stream<UNROLL, NTL, NTS, true>(fr, reinterpret_cast<u32x4*>(win) + v0, v1 - v0,
-                                                                   lane);
-                    else
-                        acc = slice_stream<UNROLL, NTL, NTS, true>(reinterpret_cast<u32x4*>(win) + v0, fr, v1 - v0,
-                                                                   lane);
-                } else {
-                    for (uint32_t v = v0 + lane; v < v1; v += 64) {
-                        const uint64_t p = p0 + 16ull * v;
-                        if (MODE == SUMS) {
-                            acc += vsum(fetch_general(F.ptr, F.nbytes, p));
-                        } else if (MODE == PACK) {
-                            const u32x4 r = fetch_general(F.ptr, F.nbytes, p);
-                            st_stream(r, reinterpret_cast<u32x4*>(win) + v);
-                            acc += vsum(r);
-                        } else {
-                            u32x4* wv = reinterpret_cast<u32x4*>(win) + v;
-                            const u32x4 r = __builtin_nontemporal_load(wv);
-                            store_general(F.ptr, F.nbytes, p, r);
-                            acc += vsum(r);
-                        }
-                    }
-                }
-            } else {
+            const uint32_t f0 = tile_first(e), f1 = tile_last(e), nf = f1 - f0 + 1;
+            const bool in_lds = f0 != f1 && nf <= (uint32_t)kLdsFrags;
+            if (in_lds) {
                 // Several fragments: their offsets go to LDS for the search.
-                // Both barriers are workgroup-uniform (f0, f1 depend on t only);
+                // Both barriers are workgroup-uniform (e depends on t only);
                 // the first keeps the previous tile's readers ahead of the refill.
-                const uint32_t nf = f1 - f0 + 1;
-                const bool in_lds = nf <= (uint32_t)kLdsFrags;
                 __syncthreads();
-                if (in_lds) {
-                    for (uint32_t k = tid; k < nf; k += BLOCK) s_off[k] = a.frags[f0 + k].off;
-                }
+                for (uint32_t k = tid; k < nf; k += BLOCK) s_off[k] = a.frags[f0 + k].off;
                 __syncthreads();
-                for (uint32_t v = v0 + lane; v < v1; v += 64) {
-                    const uint64_t x = base + 16ull * v;
-                    const uint32_t i = in_lds ? f0 + find_frag_lds(s_off, nf, x) : find_frag_global(a.frags, f0, f1, x);
-                    const FragDev F = a.frags[i];
-                    const uint64_t p = x - F.off;
-                    if (MODE == SUMS) {
-                        acc += vsum(fetch_general(F.ptr, F.nbytes, p));
-                    } else if (MODE == PACK) {
-                        const u32x4 r = fetch_general(F.ptr, F.nbytes, p);
-                        st_stream(r, reinterpret_cast<u32x4*>(win) + v);
-                        acc += vsum(r);
-                    } else {
-                        u32x4* wv = reinterpret_cast<u32x4*>(win) + v;
-                        const u32x4 r = __builtin_nontemporal_load(wv);
-                        store_general(F.ptr, F.nbytes, p, r);
-                        acc += vsum(r);
-                    }
+            }
+            FragDev F = a.frags[f0];
+            for (uint32_t v = v0 + lane; v < v1; v += 64) {
+                const uint64_t x = base + 16ull * v;
+                if (f0 != f1)
+                    F = a.frags[in_lds ? f0 + find_frag_lds(s_off, nf, x) : find_frag_global(a.frags, f0, f1, x)];
+                const uint64_t p = x - F.off;
+                if (MODE == SUMS) {
+                    acc += vsum(fetch_general(F.ptr, F.nbytes, p));
+                } else if (MODE == PACK) {
+                    const u32x4 r = fetch_general(F.ptr, F.nbytes, p);
+                    st_stream(r, reinterpret_cast<u32x4*>(win) + v);
+                    acc += vsum(r);
+                } else {
+                    u32x4* wv = reinterpret_cast<u32x4*>(win) + v;
+                    const u32x4 r = __builtin_nontemporal_load(wv);
+                    store_general(F.ptr, F.nbytes, p, r);
+                    acc += vsum(r);
                 }
             }
         }
-        acc = wave_sum(acc);
-        if (lane == 0) a.partials[t * WAVES + w] = acc;
+    }
+    acc = wave_sum(acc);
+    if (lane == 0) s_red[w] = acc;
+    __syncthreads();
+    if (tid == 0) {
+        unsigned long long sum = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < WAVES; ++k) sum += s_red[k];
+        a.partials[t] = sum;
     }
 }
 
@@ -387,12 +401,15 @@ template <int MODE, bool LOOP, int BLOCK = kBlock, int UNROLL = kUnroll, bool NT
 __global__ __launch_bounds__(BLOCK) void tile_kernel(Args a)
 {
     __shared__ uint64_t s_off[kLdsFrags];
+    __shared__ unsigned long long s_red[BLOCK / 64];
     const uint64_t first = blockIdx.x;
     if (LOOP) {
-        for (uint64_t t = a.t_lo + first; t < a.t_hi; t += gridDim.x) do_tile<MODE, BLOCK, UNROLL, NTL, NTS>(a, t, s_off);
+        for (uint64_t t = a.t_lo + first; t < a.t_hi; t += gridDim.x) {
+            do_tile<MODE, BLOCK, UNROLL, NTL, NTS>(a, t, s_off, s_red);
+            __syncthreads(); // s_red is read before the next tile writes it
+        }
     } else {
-        const uint64_t t = a.t_lo + first;
-        if (t < a.t_hi) do_tile<MODE, BLOCK, UNROLL, NTL, NTS>(a, t, s_off);
+        do_tile<MODE, BLOCK, UNROLL, NTL, NTS>(a, a.t_lo + first, s_off, s_red);
     }
     if (MODE == PACK || MODE == SUMS) release_signal(a.release);
 }
@@ -400,54 +417,55 @@ __global__ __launch_bounds__(BLOCK) void tile_kernel(Args a)
 // SUMS over runs of kSumsTiles tiles: workgroup b takes tiles
 // [t_lo + kSumsTiles * b, t_lo + kSumsTiles * (b + 1)).  When they are all
 // full 8 KiB tiles inside one 16-byte-aligned fragment, the workgroup streams
-// them in one batch: wave w owns a quarter of the run, kSumsTiles 2 KiB
-// slices (two vectors per lane per slice, all loads issued first), and
-// stores each slice's sum in that slice's partial slot.  Otherwise each tile
-// takes the per-tile path.  A read-only stream has no stores to keep the
+// them in one batch: wave w owns a quarter of the run (four vectors per lane,
+// all loads issued first), and two waves make up a tile's sum.  Otherwise
+// each tile takes the per-tile path.  A read-only stream has no stores to keep the
 // memory busy while a workgroup waits for its table lookups, so it needs
 // more bytes per workgroup than the pack.  Measured on the 1.3B shard's
 // layout: one 8 KiB tile per workgroup ~6.15 TB/s, two ~6.6 TB/s, four
 // ~6.4 TB/s, eight ~6.0 TB/s.
 constexpr uint32_t kSumsTiles = 2;
+constexpr int kSumsBlock = 256;
 
-__global__ __launch_bounds__(kBlock) void sums_run_kernel(Args a)
+__global__ __launch_bounds__(kSumsBlock) void sums_run_kernel(Args a)
 {
     __shared__ uint64_t s_off[kLdsFrags];
-    constexpr uint32_t kRun = kSumsTiles << kMaxTileShift; // bytes per workgroup
+    __shared__ unsigned long long s_red[kSumsBlock / 64];
+    constexpr uint32_t kTileVecs = 1u << (kMaxTileShift - 4);
     const uint64_t t = a.t_lo + (uint64_t)kSumsTiles * blockIdx.x; // < t_hi (grid: ceil(tiles / kSumsTiles))
-    bool fast = false;
-    FragDev F{};
-    if (t + kSumsTiles <= a.t_hi && a.g.tile_shift == kMaxTileShift) {
-        const uint32_t f0 = a.tile_first[t], f1 = a.tile_last[t + kSumsTiles - 1];
-        if (f0 == f1) { // the run holds bytes of this fragment only (or its padding)
-            F = a.frags[f0];
-            fast = (F.ptr & 15) == 0 && (t << kMaxTileShift) - F.off + kRun <= F.nbytes;
-        }
+    uint64_t e = kTileSlow;
+    if (t + kSumsTiles <= a.t_hi && a.g.tile_shift == kMaxTileShift &&
+        ((t + kSumsTiles) << kMaxTileShift) <= a.g.image_bytes) {
+        e = a.tile_src[t];
+        if ((e & 15) || a.tile_src[t + 1] != e + (1u << kMaxTileShift)) e = kTileSlow;
     }
-    if (fast) {
+    if (!(e & kTileSlow)) { // both tiles full, in one aligned span
         const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-        const u32x4* src = reinterpret_cast<const u32x4*>(F.ptr + ((t << kMaxTileShift) - F.off)) +
-                           w * (kSumsTiles * 128);
-        u32x4 r[2 * kSumsTiles];
+        const u32x4* src = reinterpret_cast<const u32x4*>(e) + w * (kTileVecs / 2); // waves 0, 1: tile t; 2, 3: t + 1
+        u32x4 r[4];
 #pragma unroll
-        for (uint32_t u = 0; u < 2 * kSumsTiles; ++u) r[u] = __builtin_nontemporal_load(src + lane + u * 64);
-        unsigned long long* p = a.partials + t * kTileParts + w * kSumsTiles; // slice w * kSumsTiles of the run
+        for (uint32_t u = 0; u < 4; ++u) r[u] = __builtin_nontemporal_load(src + lane + u * 64);
+        unsigned long long acc = 0;
 #pragma unroll
-        for (uint32_t k = 0; k < kSumsTiles; ++k) {
-            const unsigned long long sk = wave_sum(vsum(r[2 * k]) + vsum(r[2 * k + 1]));
-            if (lane == 0) p[k] = sk;
-        }
+        for (uint32_t u = 0; u < 4; ++u) acc += vsum(r[u]);
+        acc = wave_sum(acc);
+        if (lane == 0) s_red[w] = acc;
+        __syncthreads();
+        if (threadIdx.x < kSumsTiles) a.partials[t + threadIdx.x] = s_red[2 * threadIdx.x] + s_red[2 * threadIdx.x + 1];
     } else {
-        for (uint32_t k = 0; k < kSumsTiles && t + k < a.t_hi; ++k)
-            do_tile<SUMS, kBlock, kUnroll, true, true>(a, t + k, s_off);
+        for (uint32_t k = 0; k < kSumsTiles && t + k < a.t_hi; ++k) {
+            do_tile<SUMS, kSumsBlock, 2, true, true>(a, t + k, s_off, s_red);
+            __syncthreads(); // s_red is read before the next tile writes it
+        }
     }
     release_signal(a.release);
 }
 
 // One workgroup per chunk: add the chunk's tile sums; when expected is given,
-// also flag a mismatch.  A 64 MiB chunk has 32768 partial sums; each lane
-// keeps eight independent loads in flight (a plain strided loop with one
-// load at a time took ~70 us per 1 GiB of chunks).
+// also flag a mismatch.  A 64 MiB chunk has 8192 partial sums; each lane
+// keeps eight independent loads in flight (with four partial sums per tile,
+// a plain strided loop with one load at a time took ~70 us per 1 GiB of
+// chunks; now 5 us).
 constexpr int kReduceBlock = 1024;
 constexpr int kReduceUnroll = 8;
 
@@ -459,8 +477,8 @@ __global__ __launch_bounds__(kReduceBlock) void chunk_reduce_kernel(ReduceArgs r
     const uint64_t t0 = c * r.tiles_per_chunk;
     uint64_t t1 = t0 + r.tiles_per_chunk;
     if (t1 > r.n_tiles) t1 = r.n_tiles;
-    const uint64_t end = t1 * kTileParts;
-    uint64_t k = t0 * kTileParts + threadIdx.x;
+    const uint64_t end = t1;
+    uint64_t k = t0 + threadIdx.x;
     unsigned long long acc = 0;
     for (; k + (kReduceUnroll - 1) * kReduceBlock < end; k += kReduceUnroll * kReduceBlock) {
         unsigned long long v[kReduceUnroll];
@@ -526,16 +544,15 @@ __global__ __launch_bounds__(128) void frag_upload_kernel(FragDev* dst, FragBatc
 // [off, end) ends past the tile's first byte, and for the first one ending
 // past its last byte (end[] never decreases; empty fragments have empty spans).
 __global__ __launch_bounds__(256) void tile_table_kernel(const FragDev* frags, uint32_t n, Geometry g, uint64_t t_lo,
-                                                         uint64_t t_hi, uint32_t* first, uint32_t* last)
+                                                         uint64_t t_hi, uint64_t* tile_src)
 {
     const uint64_t t = t_lo + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= t_hi) return;
     const uint64_t x0 = t << g.tile_shift;
     uint64_t x1 = x0 + (1ull << g.tile_shift);
     if (x1 > g.image_bytes) x1 = g.image_bytes;
-    --x1;
     uint32_t r[2];
-    const uint64_t xs[2] = {x0, x1};
+    const uint64_t xs[2] = {x0, x1 - 1};
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         uint32_t lo = 0, hi = n - 1; // the answer lies in [lo, hi]; n - 1 when no span ends past x
@@ -546,8 +563,7 @@ __global__ __launch_bounds__(256) void tile_table_kernel(const FragDev* frags, u
         }
         r[k] = lo;
     }
-    first[t - t_lo] = r[0];
-    last[t - t_lo] = r[1];
+    tile_src[t - t_lo] = tile_entry(frags[r[0]], r[0], r[1], x0, x1);
 }
 
 // The scratch of ckpt_pack_noalloc (layout in ckpt_internal.h).  Host code
@@ -603,12 +619,12 @@ hipError_t launch_frag_upload(FragDev* dst, const FragDev* src, uint32_t count, 
 }
 
 hipError_t launch_tile_table(const FragDev* frags, uint32_t n, const Geometry& g, uint64_t t_lo, uint64_t t_hi,
-                             uint32_t* first, uint32_t* last, hipStream_t s)
+                             uint64_t* tile_src, hipStream_t s)
 {
     if (t_hi <= t_lo || n == 0) return hipSuccess;
     const uint64_t nt = t_hi - t_lo;
     hipLaunchKernelGGL(tile_table_kernel, dim3((uint32_t)((nt + 255) / 256)), dim3(256), 0, s, frags, n, g, t_lo, t_hi,
-                       first, last);
+                       tile_src);
     return hipGetLastError();
 }
 
@@ -618,36 +634,36 @@ hipError_t launch_release(int64_t* signal_value, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_pack(const FragDev* frags, const uint32_t* tile_first, const uint32_t* tile_last,
+hipError_t launch_pack(const FragDev* frags, const uint64_t* tile_src,
                        const Geometry& g, uint64_t t_lo, uint64_t t_hi, uint8_t* dst, uint64_t dst_origin,
                        unsigned long long* partials, uint32_t grid_cap, hipStream_t s, hipEvent_t t0, hipEvent_t t1,
                        int64_t* release)
 {
-    Args a{frags, tile_first, tile_last, g, t_lo, t_hi, dst, dst_origin, partials, release};
+    Args a{frags, tile_src, g, t_lo, t_hi, dst, dst_origin, partials, release};
     return launch_tiles<PACK>(a, grid_cap, s, t0, t1);
 }
 
-hipError_t launch_sums(const FragDev* frags, const uint32_t* tile_first, const uint32_t* tile_last,
+hipError_t launch_sums(const FragDev* frags, const uint64_t* tile_src,
                        const Geometry& g, uint64_t t_lo, uint64_t t_hi, unsigned long long* partials,
                        uint32_t grid_cap, hipStream_t s, hipEvent_t t0, hipEvent_t t1, int64_t* release)
 {
-    Args a{frags, tile_first, tile_last, g, t_lo, t_hi, nullptr, 0, partials, release};
+    Args a{frags, tile_src, g, t_lo, t_hi, nullptr, 0, partials, release};
     if (t_hi <= t_lo) return hipSuccess;
     const uint64_t runs = (t_hi - t_lo + kSumsTiles - 1) / kSumsTiles;
     if (runs > grid_cap) return launch_tiles<SUMS>(a, grid_cap, s, t0, t1); // a capped grid strides over tiles
     if (t0 && t1)
-        hipExtLaunchKernelGGL(sums_run_kernel, dim3((uint32_t)runs), dim3(kBlock), 0, s, t0, t1, 0, a);
+        hipExtLaunchKernelGGL(sums_run_kernel, dim3((uint32_t)runs), dim3(kSumsBlock), 0, s, t0, t1, 0, a);
     else
-        hipLaunchKernelGGL(sums_run_kernel, dim3((uint32_t)runs), dim3(kBlock), 0, s, a);
+        hipLaunchKernelGGL(sums_run_kernel, dim3((uint32_t)runs), dim3(kSumsBlock), 0, s, a);
     return hipGetLastError();
 }
 
-hipError_t launch_scatter(const FragDev* frags, const uint32_t* tile_first, const uint32_t* tile_last,
+hipError_t launch_scatter(const FragDev* frags, const uint64_t* tile_src,
                           const Geometry& g, uint64_t t_lo, uint64_t t_hi, const uint8_t* src, uint64_t src_origin,
                           unsigned long long* partials, uint32_t grid_cap, hipStream_t s, hipEvent_t t0,
                           hipEvent_t t1)
 {
-    Args a{frags, tile_first, tile_last, g, t_lo, t_hi, const_cast<uint8_t*>(src), src_origin, partials, nullptr};
+    Args a{frags, tile_src, g, t_lo, t_hi, const_cast<uint8_t*>(src), src_origin, partials, nullptr};
     return launch_tiles<SCATTER>(a, grid_cap, s, t0, t1);
 }
 
@@ -655,7 +671,7 @@ hipError_t launch_checksum(const Geometry& g, uint64_t t_lo, uint64_t t_hi, cons
                            unsigned long long* partials, uint32_t grid_cap, hipStream_t s, hipEvent_t t0,
                            hipEvent_t t1)
 {
-    Args a{nullptr, nullptr, nullptr, g, t_lo, t_hi, const_cast<uint8_t*>(src), src_origin, partials, nullptr};
+    Args a{nullptr, nullptr, g, t_lo, t_hi, const_cast<uint8_t*>(src), src_origin, partials, nullptr};
     return launch_tiles<VERIFY>(a, grid_cap, s, t0, t1);
 }
 

@@ -133,8 +133,7 @@ extern "C" ckpt_status ckpt_pack_noalloc(const ckpt_tensor* t, uint32_t n, uint6
     hipError_t e = noalloc_scratch(&base);
     if (e != hipSuccess) return fail_free(CKPT_EHIP, "scratch address: %s", hipGetErrorString(e));
     FragDev* d_frags = reinterpret_cast<FragDev*>(base + kNoallocFragsOff);
-    uint32_t* d_first = reinterpret_cast<uint32_t*>(base + kNoallocFirstOff);
-    uint32_t* d_last = reinterpret_cast<uint32_t*>(base + kNoallocLastOff);
+    uint64_t* d_tiles = reinterpret_cast<uint64_t*>(base + kNoallocTilesOff);
     unsigned long long* d_part = reinterpret_cast<unsigned long long*>(base + kNoallocPartialsOff);
     hipStream_t s = (hipStream_t)stream;
 
@@ -169,17 +168,15 @@ extern "C" ckpt_status ckpt_pack_noalloc(const ckpt_tensor* t, uint32_t n, uint6
     for (uint64_t lo = 0; lo < I; lo += G * C) {
         const uint64_t hi = std::min(lo + G * C, I);
         const uint64_t t_lo = lo >> ts, t_hi = (hi + (1ull << ts) - 1) >> ts;
-        e = launch_tile_table(d_frags, n, g, t_lo, t_hi, d_first, d_last, s);
+        e = launch_tile_table(d_frags, n, g, t_lo, t_hi, d_tiles, s);
         if (e != hipSuccess) return fail_free(CKPT_EHIP, "tile table: %s", hipGetErrorString(e));
         // The kernels index the tables and partial sums by absolute tile;
         // the group's entries sit at the start of the scratch, so the bases
         // passed are moved back by t_lo entries (only [t_lo, t_hi) is read
         // or written through them).
-        const uint32_t* first = reinterpret_cast<const uint32_t*>((uintptr_t)d_first - t_lo * 4);
-        const uint32_t* last = reinterpret_cast<const uint32_t*>((uintptr_t)d_last - t_lo * 4);
-        unsigned long long* part =
-            reinterpret_cast<unsigned long long*>((uintptr_t)d_part - t_lo * kTileParts * 8);
-        e = launch_pack(d_frags, first, last, g, t_lo, t_hi, (uint8_t*)image, 0, part, kDefaultGrid, s);
+        const uint64_t* tiles = reinterpret_cast<const uint64_t*>((uintptr_t)d_tiles - t_lo * 8);
+        unsigned long long* part = reinterpret_cast<unsigned long long*>((uintptr_t)d_part - t_lo * 8);
+        e = launch_pack(d_frags, tiles, g, t_lo, t_hi, (uint8_t*)image, 0, part, kDefaultGrid, s);
         if (e != hipSuccess) return fail_free(CKPT_EHIP, "pack launch: %s", hipGetErrorString(e));
         e = launch_chunk_reduce(g, t_lo, t_hi, part, (unsigned long long*)sums, nullptr, nullptr, s);
         if (e != hipSuccess) return fail_free(CKPT_EHIP, "reduce launch: %s", hipGetErrorString(e));

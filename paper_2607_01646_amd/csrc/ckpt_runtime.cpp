@@ -584,8 +584,7 @@ void free_ctx(ckpt_ctx* c)
         if (e) (void)hipEventDestroy(e);
     (void)hipFree(c->d_vring);
     (void)hipFree(c->d_frags);
-    (void)hipFree(c->d_tile_first);
-    (void)hipFree(c->d_tile_last);
+    (void)hipFree(c->d_tile_src);
     (void)hipFree(c->d_staging);
     (void)hipFree(c->d_partials);
     (void)hipFree(c->d_expected);
@@ -746,6 +745,7 @@ ckpt_status ckpt_register_tensors(ckpt_ctx* c, const ckpt_tensor* t, uint32_t n)
     if (!c) return CKPT_EINVAL;
     if (c->registered) return fail(c, CKPT_ESTATE, "tensors already registered");
     if (!t || n == 0) return fail(c, CKPT_EINVAL, "need at least one fragment");
+    if (n > kMaxFrags) return fail(c, CKPT_EINVAL, "%u fragments: at most %u", n, kMaxFrags);
     HIPCHK(c, hipSetDevice(c->device));
     std::vector<uint64_t> nb(n);
     for (uint32_t i = 0; i < n; ++i) {
@@ -849,6 +849,10 @@ ckpt_status ckpt_register_tensors(ckpt_ctx* c, const ckpt_tensor* t, uint32_t n)
         for (size_t k = 0; k < c->pieces.size(); ++k) c->pieces[k].src += c->frags[pf[k]].ptr;
     }
     const uint64_t nt = pl.n_tiles;
+    std::vector<uint64_t> tile_src(nt);
+    for (uint64_t k = 0; k < nt; ++k)
+        tile_src[k] = tile_entry(fd[pl.tile_first[k]], pl.tile_first[k], pl.tile_last[k], k << pl.tile_shift,
+                                 std::min<uint64_t>((k + 1) << pl.tile_shift, c->I));
     const uint64_t n_areas = c->ring ? c->n_slots : c->n_groups;
 
 #define ALLOC(ptr, bytes)                                                                                   \
@@ -859,9 +863,8 @@ ckpt_status ckpt_register_tensors(ckpt_ctx* c, const ckpt_tensor* t, uint32_t n)
         }                                                                                                   \
     } while (0)
     ALLOC(c->d_frags, n * sizeof(FragDev));
-    ALLOC(c->d_tile_first, nt * 4);
-    ALLOC(c->d_tile_last, nt * 4);
-    ALLOC(c->d_partials, 2 * nt * kTileParts * 8);
+    ALLOC(c->d_tile_src, nt * 8);
+    ALLOC(c->d_partials, 2 * nt * 8);
     ALLOC(c->d_expected, c->n_chunks * 8);
     ALLOC(c->d_recomputed, c->n_chunks * 8);
     ALLOC(c->d_bad, c->n_chunks);
@@ -871,8 +874,7 @@ ckpt_status ckpt_register_tensors(ckpt_ctx* c, const ckpt_tensor* t, uint32_t n)
     ALLOC(c->d_vring, c->n_vslots * c->G * c->C);
 #undef ALLOC
     HIPCHK(c, hipMemcpy(c->d_frags, fd.data(), n * sizeof(FragDev), hipMemcpyHostToDevice));
-    HIPCHK(c, hipMemcpy(c->d_tile_first, pl.tile_first.data(), nt * 4, hipMemcpyHostToDevice));
-    HIPCHK(c, hipMemcpy(c->d_tile_last, pl.tile_last.data(), nt * 4, hipMemcpyHostToDevice));
+    HIPCHK(c, hipMemcpy(c->d_tile_src, tile_src.data(), nt * 8, hipMemcpyHostToDevice));
     HIPCHK(c, hipMemset(c->d_area_done, 0, n_areas * 8));
     c->area_seq.assign(n_areas, 0);
     c->area_flag.assign(n_areas, hsa_signal_t{0});

@@ -88,7 +88,7 @@ ckpt_status issue_groups_direct(ckpt_ctx* c, SnapRec& r, hipStream_t after, uint
     int64_t* pending = nullptr; // the previous group's release, carried by the next launch
     for (uint64_t g = 0; g < c->n_groups; ++g) {
         const uint64_t lo = group_lo(c, g);
-        hipError_t e = launch_sums(c->d_frags, c->d_tile_first, c->d_tile_last, c->geo, tiles_lo(c, g),
+        hipError_t e = launch_sums(c->d_frags, c->d_tile_src, c->geo, tiles_lo(c, g),
                                    tiles_hi(c, g), c->d_partials, c->grid_cap, c->s_pack,
                                    r.timed && (r.per_launch || g == 0) ? res->k0[g] : nullptr,
                                    r.timed && (r.per_launch || g == 0) ? res->k1[g] : nullptr, pending);
@@ -220,7 +220,7 @@ ckpt_status issue_groups(ckpt_ctx* c, SnapRec& r, hipStream_t after, uint64_t n_
                 hipError_t e = launch_fill16(staging_of(c, g0), group_hi(c, g1 - 1) - lo, w, c->s_pack);
                 if (e != hipSuccess) return fail(c, CKPT_EHIP, "canary fill failed: %s", hipGetErrorString(e));
             }
-            hipError_t e = launch_pack(c->d_frags, c->d_tile_first, c->d_tile_last, c->geo, tiles_lo(c, g0),
+            hipError_t e = launch_pack(c->d_frags, c->d_tile_src, c->geo, tiles_lo(c, g0),
                                        tiles_hi(c, g1 - 1), staging_of(c, g0), lo, c->d_partials, c->grid_cap,
                                        c->s_pack, r.timed && (r.per_launch || j == 0) ? res->k0[j] : nullptr,
                                        r.timed && (r.per_launch || j == 0) ? res->k1[j] : nullptr,
