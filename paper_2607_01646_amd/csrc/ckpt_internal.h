@@ -99,22 +99,54 @@ hipError_t launch_fill16(uint8_t* p, uint64_t n, const uint32_t w[4], hipStream_
 // of at most kNoallocGroupTiles tiles, then that group's partial sums.  Groups are whole chunks and are packed one
 // after another on the caller's stream, reusing the tables.
 constexpr uint32_t kNoallocMaxFrags = 65536;
-constexpr uint64_t kNoallocGroupTiles = 131072; // 1 GiB of 8 KiB tiles
+constexpr uint64_t kNoallocGroupTiles = 262144; // 2 GiB of 8 KiB tiles
+constexpr uint64_t kNoallocMaxChunkTiles = 131072; // a chunk of at most 1 GiB
 constexpr uint64_t kNoallocFragsOff = 0;
 constexpr uint64_t kNoallocTilesOff = kNoallocFragsOff + (uint64_t)kNoallocMaxFrags * sizeof(FragDev);
 constexpr uint64_t kNoallocPartialsOff = kNoallocTilesOff + kNoallocGroupTiles * 8;
-constexpr uint64_t kNoallocScratchBytes = kNoallocPartialsOff + kNoallocGroupTiles * 8; // 4 MiB
-// Fragment descriptors per upload launch (they travel as kernel arguments).
-constexpr uint32_t kUploadBatch = 96;
+constexpr uint64_t kNoallocScratchBytes = kNoallocPartialsOff + kNoallocGroupTiles * 8; // 6 MiB
+// Fragment descriptors travel as kernel arguments, so the caller's array has
+// been read when the call returns and nothing is allocated for it.  A batch
+// is the most that fits 4 KiB of arguments beside a kernel's others: pointer
+// and size only, the image offsets being a scan of the padded sizes.
+constexpr uint32_t kArgFrags = 248;
+struct FragArgs {
+    uint32_t count, align;
+    uint64_t off; // image offset of the batch's first fragment
+    struct {
+        uint64_t ptr, nbytes;
+    } f[kArgFrags];
+};
+// Without a tile table, for at most kArgFrags fragments (launch_pack_small):
+// images of up to kSmallChunksImage whose chunks are at most kSmallSpan, one
+// workgroup and one launch for each chunk's bytes and sum; and images of up
+// to kSmallImage in 8 KiB tiles, the chunk reduce following.  The lines lie
+// where the table's launches stop costing more.  Time a call in a row of calls,
+// in us, with tables -> without (8 fragments): 64 KiB chunks, image of 1 MiB
+// 13.0 -> 7.4, 16 MiB 12.0 -> 9.3, 64 MiB 30.5 -> 22.3 (128 KiB chunks by one
+// workgroup each: 13.0 -> 12.1 at 1 MiB, 11.5 -> 15.4 at 16 MiB); 1 MiB chunks
+// in tiles, image of 1 MiB 12.4 -> 9.6, 16 MiB 11.6 -> 10.7, 64 MiB 28.7 -> 28.3.
+constexpr uint64_t kSmallSpan = 64ull << 10;
+constexpr uint64_t kSmallChunksImage = 64ull << 20;
+constexpr uint64_t kSmallImage = 16ull << 20;
 
 // Device address of the current device's scratch array, looked up once per
 // device with that device current (the array's host-side name is only a
 // handle, never a device address).
 hipError_t noalloc_scratch(uint8_t** ptr);
 
-// Write descriptors src[0, count) (host memory, count <= kUploadBatch) to
-// dst[0, count) on the device, in stream order, through kernel arguments.
-hipError_t launch_frag_upload(FragDev* dst, const FragDev* src, uint32_t count, hipStream_t s);
+// Write the batch's fragment records to dst[0, b.count) on the device.
+hipError_t launch_frag_upload(FragDev* dst, const FragArgs& b, hipStream_t s);
+
+// The tile table (see launch_tile_table) and the records of a fragment list
+// that is one batch, in one launch.
+hipError_t launch_tile_table_args(const FragArgs& b, FragDev* frags, const Geometry& g, uint64_t t_lo, uint64_t t_hi,
+                                  uint64_t* tile_src, hipStream_t s);
+
+// Pack an image of one batch of fragments into img with no tables: out[k] is
+// the word-sum of image bytes [k * span, (k + 1) * span), span a multiple of 16.
+hipError_t launch_pack_small(const FragArgs& b, uint8_t* img, uint64_t image_bytes, uint64_t span,
+                             unsigned long long* out, hipStream_t s);
 
 // Tile table of tiles [t_lo, t_hi) over the n fragments in frags (device):
 // tile_src[t - t_lo] = tile_entry() of the first and last fragment holding a

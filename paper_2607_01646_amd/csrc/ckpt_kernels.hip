@@ -527,17 +527,110 @@ __global__ __launch_bounds__(256) void fill16_kernel(u32x4* p, uint64_t n16, u32
         p[k] = w;
 }
 
-// ---- allocation-free pack: scratch, table upload, tile table ----
+// ---- allocation-free pack: scratch, fragment and tile tables, small images ----
 
-struct FragBatch {
-    uint32_t count;
-    FragDev f[kUploadBatch];
-};
-
-__global__ __launch_bounds__(128) void frag_upload_kernel(FragDev* dst, FragBatch b)
+// Image offsets of the batch's fragments, by a scan of their padded sizes:
+// s_off[k] for k < b.count.  Called by all lanes of a workgroup of at least
+// kArgFrags lanes; ends with a barrier.  s_wave holds one value per wave.
+static_assert(kArgFrags <= 256, "the scan covers four waves");
+__device__ __forceinline__ void scan_offsets(const FragArgs& b, uint64_t* s_off, uint64_t* s_wave)
 {
-    const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < b.count) dst[k] = b.f[k];
+    const uint32_t tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const uint64_t mask = b.align - 1;
+    const uint64_t size = tid < b.count ? (b.f[tid].nbytes + mask) & ~mask : 0;
+    uint64_t v = size; // inclusive scan over the wave
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const unsigned lo = __shfl_up((unsigned)v, d), hi = __shfl_up((unsigned)(v >> 32), d);
+        if (lane >= (uint32_t)d) v += ((uint64_t)hi << 32) | lo;
+    }
+    if (lane == 63 && w < 4) s_wave[w] = v;
+    __syncthreads();
+    if (tid < b.count) {
+        uint64_t off = b.off + v - size;
+        for (uint32_t k = 0; k < w; ++k) off += s_wave[k];
+        s_off[tid] = off;
+    }
+    __syncthreads();
+}
+
+__device__ __forceinline__ FragDev arg_frag(const FragArgs& b, const uint64_t* s_off, uint32_t k)
+{
+    FragDev f;
+    f.ptr = b.f[k].ptr;
+    f.nbytes = b.f[k].nbytes;
+    f.off = s_off[k];
+    f.end = f.off + ((f.nbytes + b.align - 1) & ~(uint64_t)(b.align - 1));
+    return f;
+}
+
+// The batch's fragment records, at dst.
+__global__ __launch_bounds__(256) void frag_upload_kernel(FragDev* dst, FragArgs b)
+{
+    __shared__ uint64_t s_off[kArgFrags], s_wave[4];
+    scan_offsets(b, s_off, s_wave);
+    if (threadIdx.x < b.count) dst[threadIdx.x] = arg_frag(b, s_off, threadIdx.x);
+}
+
+// Tile table of tiles [t_lo, t_hi) when every fragment fits one batch: the
+// offsets are scanned into LDS and searched there, and workgroup 0 stores the
+// records (the pack reads them for tiles that no single fragment covers).
+// One launch instead of an upload and a table kernel that searches memory.
+__global__ __launch_bounds__(256) void tile_table_args_kernel(FragArgs b, FragDev* frags, Geometry g, uint64_t t_lo,
+                                                              uint64_t t_hi, uint64_t* tile_src)
+{
+    __shared__ uint64_t s_off[kArgFrags], s_wave[4];
+    scan_offsets(b, s_off, s_wave);
+    if (blockIdx.x == 0 && threadIdx.x < b.count) frags[threadIdx.x] = arg_frag(b, s_off, threadIdx.x);
+    const uint64_t t = t_lo + 256ull * blockIdx.x + threadIdx.x;
+    if (t >= t_hi) return;
+    const uint64_t x0 = t << g.tile_shift;
+    uint64_t x1 = x0 + (1ull << g.tile_shift);
+    if (x1 > g.image_bytes) x1 = g.image_bytes;
+    const uint32_t f0 = find_frag_lds(s_off, b.count, x0), f1 = find_frag_lds(s_off, b.count, x1 - 1);
+    tile_src[t - t_lo] = tile_entry(arg_frag(b, s_off, f0), f0, f1, x0, x1);
+}
+
+// A small image in one pass over the fragments, with no table: workgroup k
+// packs image bytes [k * span, (k + 1) * span) and stores their word-sum in
+// out[k].  With span the chunk size these are the chunk sums and the pack is
+// one launch; else span is the tile size and the chunk reduce follows.  Every
+// workgroup scans the fragment sizes for itself (about 2 us), which costs
+// less than the launches that the tables need (3-6 us each, the gap between
+// them included).  Four vectors per lane are under way at a time: a 64 KiB
+// chunk is two rounds.
+constexpr int kSmallBlock = 512;
+constexpr int kSmallUnroll = 4;
+__global__ __launch_bounds__(kSmallBlock) void pack_small_kernel(FragArgs b, uint8_t* img, uint64_t image_bytes,
+                                                                 uint64_t span, unsigned long long* out)
+{
+    __shared__ uint64_t s_off[kArgFrags], s_wave[4];
+    __shared__ unsigned long long s_red[kSmallBlock / 64];
+    scan_offsets(b, s_off, s_wave);
+    const uint64_t lo = (uint64_t)blockIdx.x * span;
+    const uint64_t hi = lo + span < image_bytes ? lo + span : image_bytes;
+    unsigned long long acc = 0;
+    for (uint64_t x0 = lo + 16 * threadIdx.x; x0 < hi; x0 += 16 * kSmallBlock * kSmallUnroll) {
+        u32x4 r[kSmallUnroll];
+#pragma unroll
+        for (int u = 0; u < kSmallUnroll; ++u) {
+            const uint64_t x = x0 + 16 * kSmallBlock * u;
+            if (x < hi) {
+                const uint32_t k = find_frag_lds(s_off, b.count, x);
+                r[u] = fetch_general(b.f[k].ptr, b.f[k].nbytes, x - s_off[k]);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kSmallUnroll; ++u) {
+            const uint64_t x = x0 + 16 * kSmallBlock * u;
+            if (x < hi) {
+                st_stream(r[u], reinterpret_cast<u32x4*>(img + x));
+                acc += vsum(r[u]);
+            }
+        }
+    }
+    acc = block_sum<kSmallBlock>(acc, s_red);
+    if (threadIdx.x == 0) out[blockIdx.x] = acc;
 }
 
 // One lane per tile: binary search for the first fragment whose padded span
@@ -546,7 +639,7 @@ __global__ __launch_bounds__(128) void frag_upload_kernel(FragDev* dst, FragBatc
 __global__ __launch_bounds__(256) void tile_table_kernel(const FragDev* frags, uint32_t n, Geometry g, uint64_t t_lo,
                                                          uint64_t t_hi, uint64_t* tile_src)
 {
-    const uint64_t t = t_lo + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t t = t_lo + 256ull * blockIdx.x + threadIdx.x;
     if (t >= t_hi) return;
     const uint64_t x0 = t << g.tile_shift;
     uint64_t x1 = x0 + (1ull << g.tile_shift);
@@ -607,14 +700,30 @@ hipError_t launch_fill16(uint8_t* p, uint64_t n, const uint32_t w[4], hipStream_
     return hipGetLastError();
 }
 
-hipError_t launch_frag_upload(FragDev* dst, const FragDev* src, uint32_t count, hipStream_t s)
+hipError_t launch_frag_upload(FragDev* dst, const FragArgs& b, hipStream_t s)
 {
-    if (count == 0) return hipSuccess;
-    if (count > kUploadBatch) return hipErrorInvalidValue;
-    FragBatch b;
-    b.count = count;
-    for (uint32_t k = 0; k < count; ++k) b.f[k] = src[k];
-    hipLaunchKernelGGL(frag_upload_kernel, dim3(1), dim3(128), 0, s, dst, b);
+    if (b.count == 0 || b.count > kArgFrags) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(frag_upload_kernel, dim3(1), dim3(256), 0, s, dst, b);
+    return hipGetLastError();
+}
+
+hipError_t launch_tile_table_args(const FragArgs& b, FragDev* frags, const Geometry& g, uint64_t t_lo, uint64_t t_hi,
+                                  uint64_t* tile_src, hipStream_t s)
+{
+    if (t_hi <= t_lo) return hipSuccess;
+    if (b.count == 0 || b.count > kArgFrags || b.off != 0) return hipErrorInvalidValue;
+    const uint64_t nt = t_hi - t_lo;
+    hipLaunchKernelGGL(tile_table_args_kernel, dim3((uint32_t)((nt + 255) / 256)), dim3(256), 0, s, b, frags, g, t_lo,
+                       t_hi, tile_src);
+    return hipGetLastError();
+}
+
+hipError_t launch_pack_small(const FragArgs& b, uint8_t* img, uint64_t image_bytes, uint64_t span,
+                             unsigned long long* out, hipStream_t s)
+{
+    if (b.count == 0 || b.count > kArgFrags || b.off != 0 || image_bytes == 0 || span % 16) return hipErrorInvalidValue;
+    const uint64_t n = (image_bytes + span - 1) / span;
+    hipLaunchKernelGGL(pack_small_kernel, dim3((uint32_t)n), dim3(kSmallBlock), 0, s, b, img, image_bytes, span, out);
     return hipGetLastError();
 }
 

@@ -85,9 +85,9 @@ extern "C" ckpt_status ckpt_pack_noalloc(const ckpt_tensor* t, uint32_t n, uint6
     if (!geometry_ok(C, A)) return fail_free(CKPT_EINVAL, "bad geometry: chunk %llu, alignment %u", (unsigned long long)C, A);
     const uint32_t ts = tile_shift_for(C);
     const uint64_t tpc = C >> ts; // tiles per chunk
-    if (tpc > kNoallocGroupTiles)
+    if (tpc > kNoallocMaxChunkTiles)
         return fail_free(CKPT_EINVAL, "a chunk of %llu tiles exceeds the scratch's %llu tiles (chunks up to 1 GiB)",
-                         (unsigned long long)tpc, (unsigned long long)kNoallocGroupTiles);
+                         (unsigned long long)tpc, (unsigned long long)kNoallocMaxChunkTiles);
     if (((uintptr_t)image & 15) || ((uintptr_t)sums & 7))
         return fail_free(CKPT_EINVAL, "image must be 16-byte aligned and sums 8-byte aligned");
 
@@ -137,38 +137,49 @@ extern "C" ckpt_status ckpt_pack_noalloc(const ckpt_tensor* t, uint32_t n, uint6
     unsigned long long* d_part = reinterpret_cast<unsigned long long*>(base + kNoallocPartialsOff);
     hipStream_t s = (hipStream_t)stream;
 
-    // Second pass: the fragment table, in batches carried by kernel arguments.
-    FragDev batch[kUploadBatch];
-    uint32_t k = 0;
-    uint64_t off = 0;
-    for (uint32_t i = 0; i < n; ++i) {
-        const uint64_t next = align_up(off + t[i].nbytes, A); // the next fragment's offset
-        FragDev& f = batch[k++];
-        f.ptr = (uint64_t)(uintptr_t)t[i].dev_ptr;
-        f.nbytes = t[i].nbytes;
-        f.off = off;
-        f.end = (i + 1 < n) ? next : I;
-        off = next;
-        if (k == kUploadBatch || i + 1 == n) {
-            e = launch_frag_upload(d_frags + (i + 1 - k), batch, k, s);
-            if (e != hipSuccess) return fail_free(CKPT_EHIP, "table upload: %s", hipGetErrorString(e));
-            k = 0;
-        }
-    }
-
     Geometry g;
     g.image_bytes = I;
     g.tile_shift = ts;
     g.n_tiles = (I + (1ull << ts) - 1) >> ts;
     g.n_chunks = nc;
     g.tiles_per_chunk = (uint32_t)tpc;
+
+    // Second pass: the descriptors, in batches carried by kernel arguments.
+    FragArgs batch;
+    batch.align = A;
+    batch.count = 0;
+    batch.off = 0;
+    const bool one_batch = n <= kArgFrags;
+    uint64_t off = 0;
+    for (uint32_t i = 0; i < n; ++i) {
+        batch.f[batch.count].ptr = (uint64_t)(uintptr_t)t[i].dev_ptr;
+        batch.f[batch.count++].nbytes = t[i].nbytes;
+        off = align_up(off + t[i].nbytes, A);
+        if (!one_batch && (batch.count == kArgFrags || i + 1 == n)) {
+            e = launch_frag_upload(d_frags + (i + 1 - batch.count), batch, s);
+            if (e != hipSuccess) return fail_free(CKPT_EHIP, "table upload: %s", hipGetErrorString(e));
+            batch.count = 0;
+            batch.off = off;
+        }
+    }
+    const bool by_chunk = one_batch && C <= kSmallSpan && I <= kSmallChunksImage;
+    const bool by_tile = one_batch && ts == kMaxTileShift && I <= kSmallImage;
+    if (by_chunk || by_tile) {
+        e = launch_pack_small(batch, (uint8_t*)image, I, by_chunk ? C : 1ull << ts,
+                              by_chunk ? (unsigned long long*)sums : d_part, s);
+        if (e == hipSuccess && !by_chunk)
+            e = launch_chunk_reduce(g, 0, g.n_tiles, d_part, (unsigned long long*)sums, nullptr, nullptr, s);
+        if (e != hipSuccess) return fail_free(CKPT_EHIP, "pack launch: %s", hipGetErrorString(e));
+        return CKPT_OK;
+    }
     // Groups of whole chunks, at most kNoallocGroupTiles tiles each, one after
     // another on the stream: each reuses the tile table and partial sums.
     const uint64_t G = std::max<uint64_t>(1, kNoallocGroupTiles / tpc);
     for (uint64_t lo = 0; lo < I; lo += G * C) {
         const uint64_t hi = std::min(lo + G * C, I);
         const uint64_t t_lo = lo >> ts, t_hi = (hi + (1ull << ts) - 1) >> ts;
-        e = launch_tile_table(d_frags, n, g, t_lo, t_hi, d_tiles, s);
+        e = one_batch ? launch_tile_table_args(batch, d_frags, g, t_lo, t_hi, d_tiles, s)
+                      : launch_tile_table(d_frags, n, g, t_lo, t_hi, d_tiles, s);
         if (e != hipSuccess) return fail_free(CKPT_EHIP, "tile table: %s", hipGetErrorString(e));
         // The kernels index the tables and partial sums by absolute tile;
         // the group's entries sit at the start of the scratch, so the bases

@@ -52,3 +52,36 @@ def test_unaligned_fragments_without_allocation(shift):
     got = image.cpu().numpy()
     assert np.array_equal(got[:want.size], want) and np.all(got[want.size:] == 0xC3)
     assert np.array_equal(sums.cpu().numpy().view(np.uint64), O.chunk_sums(want, 0, want.size, 4 * TILE))
+
+
+@pytest.mark.parametrize("n,total,chunk,align", [
+    (1, 1, 65536, 16),                     # one byte
+    (64, 1 << 20, 65536, 256),             # one workgroup a chunk
+    (248, 64 << 20, 65536, 256),           # ... the most fragments, about the largest image
+    (249, 1 << 20, 65536, 256),            # one fragment more than a batch of descriptors
+    (248, 3 << 20, 4112, 16),              # chunks of an odd number of vectors
+    (200, 16 << 20, 65536 + 8192, 16),     # tiles, about the largest such image
+    (200, (16 << 20) + 99999, 1 << 20, 16),  # just past it: the tile table from the arguments
+    (250, 10 << 20, 16 * 4099, 16),        # 16-byte tiles: several scratch groups, two batches
+    (20, 10 << 20, 16 * 4099, 16),         # ... from the arguments
+    (700, 5 << 20, 1 << 20, 4096),         # three batches
+])
+def test_allocation_free_paths(n, total, chunk, align):
+    """Each way the allocation-free pack takes by size and fragment count."""
+    rng = np.random.default_rng(n + total + chunk)
+    cuts = np.sort(rng.integers(0, total + 1, n - 1))
+    sizes = np.diff(np.concatenate([[0], cuts, [total]])).astype(np.int64)
+    if n > 4:
+        sizes[[0, n // 2, n - 1]] = 0  # empty at both ends and inside
+    flat = torch.from_numpy(rng.integers(0, 256, int(sizes.sum()), dtype=np.uint8)).cuda()
+    at = np.concatenate([[0], np.cumsum(sizes)])
+    views = [flat[int(a):int(a + s)] for a, s in zip(at, sizes)]
+    want, _, nc = O.pack([host_bytes(v) for v in views], align, chunk)
+    image = torch.full((want.size + 64,), 0xC3, dtype=torch.uint8, device="cuda")
+    sums = torch.full((nc + 1,), -1, dtype=torch.int64, device="cuda")
+    for _ in range(2):  # again over the first call's tables
+        assert P.ckpt_pack_noalloc(views, image, sums, chunk_bytes=chunk, align_bytes=align) == (want.size, nc)
+    got = image.cpu().numpy()
+    assert np.array_equal(got[:want.size], want) and np.all(got[want.size:] == 0xC3)
+    assert np.array_equal(sums.cpu().numpy().view(np.uint64)[:nc], O.chunk_sums(want, 0, want.size, chunk))
+    assert int(sums[nc]) == -1
