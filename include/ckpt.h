@@ -138,8 +138,7 @@ typedef struct {
                                       the HBM traffic of pack + copy, and no device image).  The
                                       gate (ckpt_wait CAPTURED) then also waits for the copies of
                                       the chunk groups it covers, so an update issued before the
-                                      copies finish waits for the host link.  Restore stages through
-                                      a device ring of up to four chunk groups.  Not combinable with
+                                      copies finish waits for the host link.  Not combinable with
                                       device_staging_bytes or poison; pack_launch_bytes is ignored.
                                       At most 65536 fragment pieces (fragments cut at group
                                       boundaries). */
@@ -216,10 +215,10 @@ ckpt_status ckpt_wait(ckpt_ctx* ctx, uint64_t snap_id, uint32_t mode, void* stre
 ckpt_status ckpt_snapshot_state(ckpt_ctx* ctx, uint64_t snap_id, uint32_t* state);
 
 /* Recovery (Sec. V-C third stage; Sec. VI-E, local case): first waits for the
- * context's outstanding snapshot work, then copies the committed image
- * snap_id (0 = the newest committed) to the device chunk group by chunk
- * group and scatters every byte back into the registered fragments, while
- * recomputing every chunk sum on the GPU.  The work is ordered after what is
+ * context's outstanding snapshot work, then reads the committed image
+ * snap_id (0 = the newest committed) from host memory in a kernel that
+ * scatters every byte back into the registered fragments and recomputes
+ * every chunk sum.  The work is ordered after what is
  * already enqueued on `stream`, and `stream` waits for it; the call returns
  * when it is done.  Chunks whose recomputed sum differs from the stored one
  * are listed in increasing order in bad_chunks (up to cap entries, NULL
@@ -233,8 +232,8 @@ ckpt_status ckpt_restore(ckpt_ctx* ctx, uint64_t snap_id, void* stream, uint32_t
                          uint32_t* n_bad);
 
 /* Integrity check of a committed host image without touching the live
- * tensors: copies it to the device and recomputes every chunk sum on the
- * GPU.  Same snap_id, list and error conventions as ckpt_restore. */
+ * tensors: a kernel reads it from host memory and recomputes every chunk
+ * sum.  Same snap_id, list and error conventions as ckpt_restore. */
 ckpt_status ckpt_verify(ckpt_ctx* ctx, uint64_t snap_id, uint32_t* bad_chunks, uint32_t cap, uint32_t* n_bad);
 
 /* Layout accessors.  frag_off may be NULL; otherwise it receives n offsets. */
@@ -284,8 +283,10 @@ typedef struct {
                             small per-chunk reduce kernel is not included */
     uint32_t kernels;    /* number of tile-kernel launches (a snapshot's pack launches cover
                             pack_launch_bytes each) */
-    uint32_t copies;     /* number of DMA copy requests (image bytes only) */
-    float copy_ms;       /* first image copy start to last image copy end */
+    uint32_t copies;     /* number of DMA copy requests (image bytes only; 0 for restore and
+                            verify, whose kernels read the host image themselves) */
+    float copy_ms;       /* first image copy start to last image copy end (restore and verify:
+                            first kernel start to last kernel end) */
     float total_ms;      /* operation start (after the trigger) to its last event; for a
                             snapshot: to its commit (image and sums in host memory; with
                             pageable images, the last group landed in the image) */

@@ -1,39 +1,12 @@
 // ckpt_check.cpp -- restore and verify of a committed host image (paper
-// Sec. V-C third stage, Sec. VI-E): each span of image bytes goes host ->
-// device staging on a copy stream, then the scatter or checksum kernel and
-// the chunk-sum compare run on the kernel stream, span by span, so that the
-// copies and the checks overlap.
+// Sec. V-C third stage, Sec. VI-E).  The scatter or checksum kernel reads the
+// image where it lies in pinned host memory, over the host link, and the
+// chunk-sum compare reads the stored sums and writes its results there too:
+// nothing is staged on the device, and the bytes' way over the link, the
+// writes into the fragments and the sums run at the same time.
 #include "ckpt_host.h"
 
 namespace ckpt {
-
-// Where restore and verify stage image bytes on the device, and the streams
-// and events that order them.  Unit u covers chunks [u*G, (u+1)*G).
-struct Lane {
-    hipStream_t s_copy, s_ker;
-    uint8_t* base;   // staging: full image, or ring slots of G chunks each
-    bool ring;
-    uint64_t n_slots;
-    uint64_t G;
-    uint64_t n_units;
-    std::vector<hipEvent_t>* area_free; // per slot (ring) or per unit
-    std::vector<hipEvent_t>* loaded;    // per unit
-    std::vector<hipEvent_t>* tk0;       // per unit, timing
-    std::vector<hipEvent_t>* tk1;
-    hipEvent_t done, t0, c0, c1;
-};
-
-Lane restore_lane(ckpt_ctx* c)
-{
-    return Lane{c->s_copy, c->s_pack, c->d_staging, c->ring || c->direct, c->n_slots, c->G, c->n_groups, &c->area_free,
-                &c->ev_loaded, &c->tk0, &c->tk1, c->ev_done, c->tt0, c->tc0, c->tc1};
-}
-
-Lane verify_lane(ckpt_ctx* c)
-{
-    return Lane{c->s_vcopy, c->s_vker, c->d_vring, true, c->n_vslots, c->G, c->n_groups, &c->vfree,
-                &c->vloaded, &c->vk0, &c->vk1, c->ev_vdone, c->vt0, c->vc0, c->vc1};
-}
 
 // Restore (scatter=true) or verify (scatter=false) the chunks of host image
 // b against the sums in h_sums[b]: every chunk, or only the chunks `ids`
@@ -43,90 +16,70 @@ ckpt_status check_image(ckpt_ctx* c, int b, hipStream_t stream, bool scatter, co
                         uint32_t* bad_chunks, uint32_t cap, uint32_t* n_bad,
                         const std::function<bool(uint64_t, uint64_t)>& fill)
 {
-    const Lane L = scatter ? restore_lane(c) : verify_lane(c);
     const int op = scatter ? CKPT_OP_RESTORE : CKPT_OP_VERIFY;
-    const uint64_t unit = L.G * c->C;
-    // Byte spans to move, each within one unit's size: whole units, or the
-    // runs of consecutive chunk ids cut at that size.
+    hipStream_t s = scatter ? c->s_pack : c->s_vker;
+    const hipEvent_t done = scatter ? c->ev_done : c->ev_vdone, t0 = scatter ? c->tt0 : c->vt0;
+    const std::vector<hipEvent_t>&k0 = scatter ? c->tk0 : c->vk0, &k1 = scatter ? c->tk1 : c->vk1;
+    // Byte spans, one launch each: runs of consecutive chunks, cut at the
+    // size of a chunk group when the host puts the bytes in place span by span
+    // (bounce slots, bytes arriving from a peer).
+    const uint64_t most = c->bounce || fill ? c->G : c->n_chunks;
     std::vector<std::pair<uint64_t, uint64_t>> spans;
     if (!ids) {
-        for (uint64_t u = 0; u < L.n_units; ++u) spans.emplace_back(u * unit, std::min((u + 1) * unit, c->I));
+        for (uint64_t k = 0; k < c->n_chunks; k += most)
+            spans.emplace_back(k * c->C, std::min((k + most) * c->C, c->I));
     } else {
         for (size_t j = 0; j < ids->size();) {
             size_t k = j + 1;
-            while (k < ids->size() && (*ids)[k] == (*ids)[k - 1] + 1 && k - j < L.G) ++k;
+            while (k < ids->size() && (*ids)[k] == (*ids)[k - 1] + 1 && k - j < most) ++k;
             spans.emplace_back((*ids)[j] * c->C, std::min(((*ids)[k - 1] + 1) * c->C, c->I));
             j = k;
         }
     }
-    const uint64_t n_spans = spans.size();
-    // Per-span events are reused round-robin past the unit count; timing is
-    // kept for whole-image operations only.
-    const bool timed = c->timing && !ids;
+    const uint64_t n_spans = spans.size(), slot_bytes = c->G * c->C;
+    const bool timed = c->timing && !ids; // timing is kept for whole-image operations only
     unsigned long long* partials = c->d_partials + c->geo.n_tiles;
-    HIPCHK(c, hipMemcpyAsync(c->d_expected, c->h_sums[b], c->n_chunks * 8, hipMemcpyHostToDevice, L.s_copy));
+    const uint32_t grid = std::min(c->grid_cap, scatter ? kRestoreGrid : kVerifyGrid);
     if (scatter) {
         HIPCHK(c, hipEventRecord(c->ev_trigger, stream));
-        HIPCHK(c, hipStreamWaitEvent(L.s_ker, c->ev_trigger, 0));
+        HIPCHK(c, hipStreamWaitEvent(s, c->ev_trigger, 0));
     }
-    if (timed) HIPCHK(c, hipEventRecord(L.t0, L.s_copy));
+    if (timed) HIPCHK(c, hipEventRecord(t0, s));
     for (uint64_t u = 0; u < n_spans; ++u) {
         const uint64_t lo = spans[u].first, hi = spans[u].second;
-        const uint64_t ev = u % L.n_units;
-        const uint64_t area = L.ring ? u % L.n_slots : ev;
-        uint8_t* stage = L.ring ? L.base + area * unit : L.base + lo;
-        // A device slot is reused once the kernel of the span that last used
-        // it has finished.  With pageable images the host paces every span
-        // (it fills the pinned slot first), so it waits for that kernel itself
-        // right before the copy: the same wait as a device-side one on the
-        // copy stream, which here cost ~6% of the link (verify 53.5 against
-        // 56.8 GB/s through the bounce rings).
-        const bool host_wait = c->bounce && L.ring;
-        if (!host_wait) HIPCHK(c, hipStreamWaitEvent(L.s_copy, (*L.area_free)[area], 0));
-        if (timed && u == 0) HIPCHK(c, hipEventRecord(L.c0, L.s_copy));
         if (fill && !fill(lo, hi)) { // the span's bytes did not arrive: let the issued work finish, then fail
-            (void)hipStreamSynchronize(L.s_copy);
-            (void)hipStreamSynchronize(L.s_ker);
+            (void)hipStreamSynchronize(s);
             return CKPT_EHIP;
         }
         const uint8_t* src = c->h_img[b] + lo;
-        if (c->bounce) { // pageable image: through a pinned ring slot
+        if (c->bounce) { // pageable image: through a pinned ring slot, free once the kernel that read it has finished
             const uint64_t slot = u % c->n_bslots;
             if (u >= c->n_bslots) HIPCHK(c, hipEventSynchronize(c->bin_done[slot]));
-            c->pool->copy(c->h_bin + slot * unit, src, hi - lo);
-            src = c->h_bin + slot * unit;
+            c->pool->copy(c->h_bin + slot * slot_bytes, src, hi - lo);
+            src = c->h_bin + slot * slot_bytes;
         }
-        if (host_wait) HIPCHK(c, hipEventSynchronize((*L.area_free)[area]));
-        HIPCHK(c, hipMemcpyAsync(stage, src, hi - lo, hipMemcpyHostToDevice, L.s_copy));
-        if (c->bounce) HIPCHK(c, hipEventRecord(c->bin_done[u % c->n_bslots], L.s_copy));
-        if (timed && u + 1 == n_spans) HIPCHK(c, hipEventRecord(L.c1, L.s_copy));
-        HIPCHK(c, hipEventRecord((*L.loaded)[ev], L.s_copy));
-        HIPCHK(c, hipStreamWaitEvent(L.s_ker, (*L.loaded)[ev], 0));
         const uint64_t t_lo = lo >> c->geo.tile_shift, t_hi = (hi + (1ull << c->geo.tile_shift) - 1) >> c->geo.tile_shift;
-        hipEvent_t k0 = timed ? (*L.tk0)[u] : nullptr, k1 = timed ? (*L.tk1)[u] : nullptr;
+        hipEvent_t e0 = timed ? k0[u] : nullptr, e1 = timed ? k1[u] : nullptr;
         hipError_t e;
         if (scatter)
-            e = launch_scatter(c->d_frags, c->d_tile_src, c->geo, t_lo, t_hi, stage, lo, partials,
-                               c->grid_cap, L.s_ker, k0, k1);
+            e = launch_scatter(c->d_frags, c->d_tile_src, c->geo, t_lo, t_hi, src, lo, partials, grid, s, e0, e1);
         else
-            e = launch_checksum(c->geo, t_lo, t_hi, stage, lo, partials, c->grid_cap, L.s_ker, k0, k1);
+            e = launch_checksum(c->geo, t_lo, t_hi, src, lo, partials, grid, s, e0, e1);
         if (e != hipSuccess) return fail(c, CKPT_EHIP, "kernel launch failed: %s", hipGetErrorString(e));
-        e = launch_chunk_reduce(c->geo, t_lo, t_hi, partials, c->d_recomputed, c->d_expected, c->d_bad, L.s_ker);
+        if (c->bounce) HIPCHK(c, hipEventRecord(c->bin_done[u % c->n_bslots], s));
+        e = launch_chunk_reduce(c->geo, t_lo, t_hi, partials, c->h_recomputed,
+                                (const unsigned long long*)c->h_sums[b], c->h_bad, s);
         if (e != hipSuccess) return fail(c, CKPT_EHIP, "kernel launch failed: %s", hipGetErrorString(e));
-        HIPCHK(c, hipEventRecord((*L.area_free)[area], L.s_ker));
     }
-    HIPCHK(c, hipMemcpyAsync(c->h_bad, c->d_bad, c->n_chunks, hipMemcpyDeviceToHost, L.s_ker));
-    HIPCHK(c, hipMemcpyAsync(c->h_recomputed, c->d_recomputed, c->n_chunks * 8, hipMemcpyDeviceToHost, L.s_ker));
-    HIPCHK(c, hipEventRecord(L.done, L.s_ker));
-    if (scatter) HIPCHK(c, hipStreamWaitEvent(stream, L.done, 0));
-    HIPCHK(c, hipEventSynchronize(L.done));
+    HIPCHK(c, hipEventRecord(done, s));
+    if (scatter) HIPCHK(c, hipStreamWaitEvent(stream, done, 0));
+    HIPCHK(c, hipEventSynchronize(done));
     if (timed) {
         ckpt_timing t{};
-        for (uint64_t u = 0; u < L.n_units; ++u) t.kernel_ms += elapsed((*L.tk0)[u], (*L.tk1)[u]);
-        t.kernels = (uint32_t)L.n_units;
-        t.copies = (uint32_t)L.n_units;
-        t.copy_ms = elapsed(L.c0, L.c1);
-        t.total_ms = elapsed(L.t0, (*L.tk1)[L.n_units - 1]);
+        for (uint64_t u = 0; u < n_spans; ++u) t.kernel_ms += elapsed(k0[u], k1[u]);
+        t.kernels = (uint32_t)n_spans;
+        t.copy_ms = elapsed(k0[0], k1[n_spans - 1]);
+        t.total_ms = elapsed(t0, k1[n_spans - 1]);
         t.kernel_bytes = scatter ? 2 * c->payload : c->I;
         t.copy_bytes = c->I;
         t.span_ms = -1.f;

@@ -43,7 +43,6 @@ constexpr uint64_t kDefaultLaunch = 0; // full-image staging: bytes per pack lau
 constexpr uint32_t kMaxMeta = 1u << 20;
 constexpr uint32_t kDefaultGrid = 0x7fffffff; // one workgroup per tile unless capped
 constexpr int kMaxEngines = 2;
-constexpr uint64_t kVerifySlots = 2; // verify's device ring: two slots of one chunk group each
 constexpr uint32_t kDefaultHostThreads = 12; // bounce mode: host copy threads (measured: 8 do not keep up with the link)
 
 struct Frag {
@@ -60,7 +59,6 @@ struct Piece {
     uint64_t n;
 };
 constexpr uint64_t kMaxDirectPieces = 65536;
-constexpr uint64_t kDirectRestoreSlots = 4; // restore's device ring in direct mode, in chunk groups
 
 // GPU-side resources of one snapshot record, recycled between snapshots.
 struct RecRes {
@@ -333,7 +331,7 @@ struct ckpt_ctx {
     uint64_t LG = 1;         // groups per pack launch (1 in ring mode)
     uint64_t n_launches = 0; // pack launches per snapshot
     bool ring = false;
-    uint64_t n_slots = 0;  // ring slots of G chunks each (ring mode; direct mode: restore's ring)
+    uint64_t n_slots = 0;  // ring slots of G chunks each (ring mode)
     bool direct = false;   // direct D2H: no snapshot staging, the engines copy the fragments
     std::vector<Piece> pieces, gaps;              // direct D2H, by group (CSR below)
     std::vector<uint64_t> piece_first, gap_first; // [n_groups + 1]
@@ -343,9 +341,6 @@ struct ckpt_ctx {
     uint64_t* d_tile_src = nullptr;           // per tile: tile_entry()
     uint8_t* d_staging = nullptr;
     unsigned long long* d_partials = nullptr; // [2][n_tiles] tile partial sums: pack, check
-    unsigned long long* d_expected = nullptr;
-    unsigned long long* d_recomputed = nullptr;
-    uint8_t* d_bad = nullptr;
     uint64_t* d_area_done = nullptr;          // per staging area (direct D2H: per group): number of
                                               // finished copies out of it
 
@@ -353,8 +348,8 @@ struct ckpt_ctx {
     uint8_t* h_img[2] = {nullptr, nullptr};
     uint64_t* h_sums[2] = {nullptr, nullptr};
     uint64_t holder[2] = {0, 0}; // snapshot id whose bytes each image holds (0 = none)
-    uint8_t* h_bad = nullptr;
-    unsigned long long* h_recomputed = nullptr;
+    uint8_t* h_bad = nullptr;                   // written by the chunk-sum compare
+    unsigned long long* h_recomputed = nullptr; // "
 
     // HSA agents and DMA engines
     hsa_agent_t gpu_agent{0}, img_agent[2] = {{0}, {0}};
@@ -366,14 +361,12 @@ struct ckpt_ctx {
     uint64_t ts_freq = 1;
 
     // streams and events
-    hipStream_t s_pack = nullptr, s_copy = nullptr;
+    hipStream_t s_pack = nullptr;
     bool own_pack = true; // false: s_pack is the caller's side stream (never destroyed here)
     hipEvent_t ev_trigger = nullptr, ev_done = nullptr;
     std::vector<uint64_t> area_seq;     // per staging area: copies issued out of it
     std::vector<hsa_signal_t> area_flag; // per staging area: completion signal of its latest counter copy
                                          // (0 once that copy, and the image copy before it, are done)
-    std::vector<hipEvent_t> area_free;  // restore/verify: per staging area
-    std::vector<hipEvent_t> ev_loaded;  // restore/verify: per group
     std::vector<RecRes*> free_res;
     std::map<uint64_t, SnapRec> recs;
     uint64_t next_id = 1;
@@ -384,7 +377,7 @@ struct ckpt_ctx {
     std::vector<uint64_t> last_sums;
     OpTiming op_timing[3];
     std::vector<hipEvent_t> tk0, tk1; // restore timing
-    hipEvent_t tt0 = nullptr, tc0 = nullptr, tc1 = nullptr;
+    hipEvent_t tt0 = nullptr;
 
     // bounce mode: pageable images behind two pinned rings of chunk groups
     bool bounce = false;
@@ -394,7 +387,7 @@ struct ckpt_ctx {
     uint64_t img_map_bytes = 0;       // mapped length of each pageable image
     uint8_t* h_bout = nullptr;        // device -> host ring
     uint8_t* h_bin = nullptr;         // host -> device ring
-    std::vector<hipEvent_t> bin_done; // per host -> device slot: its last copy to the device finished
+    std::vector<hipEvent_t> bin_done; // per host -> device slot: the kernel that last read it has finished
     CopyPool* pool = nullptr;
     Pump* pump = nullptr;
 
@@ -412,12 +405,10 @@ struct ckpt_ctx {
     FileHead fhead{};
     uint64_t file_seq = 0; // last commit number written (drainer thread after registration)
 
-    // verify: its own ring of chunk slots and streams
-    uint8_t* d_vring = nullptr;
-    uint64_t n_vslots = 0;
-    hipStream_t s_vcopy = nullptr, s_vker = nullptr;
-    hipEvent_t ev_vdone = nullptr, vt0 = nullptr, vc0 = nullptr, vc1 = nullptr;
-    std::vector<hipEvent_t> vfree, vloaded, vk0, vk1;
+    // verify: its own stream
+    hipStream_t s_vker = nullptr;
+    hipEvent_t ev_vdone = nullptr, vt0 = nullptr;
+    std::vector<hipEvent_t> vk0, vk1;
 
     std::string err;
 };

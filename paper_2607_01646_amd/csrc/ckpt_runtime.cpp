@@ -30,9 +30,9 @@
 // committed, and an interrupted snapshot is never the recovery point
 // (invariant I4 of Sec. V-C).
 //
-// Recovery (Sec. V-C third stage, Sec. VI-E) reverses the path group by
-// group: DMA host image -> staging on the copy stream, then the scatter
-// kernel on the pack stream writes the fragments and re-checks the sums.
+// Recovery (Sec. V-C third stage, Sec. VI-E) reverses the path: the scatter
+// kernel on the pack stream reads the host image over the link, writes the
+// fragments and re-checks the sums.
 //
 // Here: context set-up, registration and its layout, the snapshot records,
 // the gate, restore and verify entry points, and the accessors.  Issuing a
@@ -457,7 +457,7 @@ void prune(ckpt_ctx* c)
 // Wait for every enqueued kernel and copy of the context.
 ckpt_status drain(ckpt_ctx* c)
 {
-    for (hipStream_t st : {c->s_pack, c->s_copy, c->s_vcopy, c->s_vker})
+    for (hipStream_t st : {c->s_pack, c->s_vker})
         if (st) HIPCHK(c, hipStreamSynchronize(st));
     for (auto& kv : c->recs) {
         ckpt_status st = wait_copies(c, kv.second);
@@ -576,20 +576,14 @@ void free_ctx(ckpt_ctx* c)
     c->recs.clear();
     for (auto r : c->free_res) destroy_res(r);
     c->free_res.clear();
-    for (auto e : c->area_free) (void)hipEventDestroy(e);
-    for (auto e : c->ev_loaded) (void)hipEventDestroy(e);
-    for (auto* v : {&c->tk0, &c->tk1, &c->vfree, &c->vloaded, &c->vk0, &c->vk1, &c->bin_done})
+    for (auto* v : {&c->tk0, &c->tk1, &c->vk0, &c->vk1, &c->bin_done})
         for (auto e : *v) (void)hipEventDestroy(e);
-    for (hipEvent_t e : {c->ev_trigger, c->ev_done, c->tt0, c->tc0, c->tc1, c->ev_vdone, c->vt0, c->vc0, c->vc1})
+    for (hipEvent_t e : {c->ev_trigger, c->ev_done, c->tt0, c->ev_vdone, c->vt0})
         if (e) (void)hipEventDestroy(e);
-    (void)hipFree(c->d_vring);
     (void)hipFree(c->d_frags);
     (void)hipFree(c->d_tile_src);
     (void)hipFree(c->d_staging);
     (void)hipFree(c->d_partials);
-    (void)hipFree(c->d_expected);
-    (void)hipFree(c->d_recomputed);
-    (void)hipFree(c->d_bad);
     (void)hipFree(c->d_area_done);
     for (int b = 0; b < 2; ++b) {
         if (c->file_map) {
@@ -608,7 +602,7 @@ void free_ctx(ckpt_ctx* c)
     if (c->h_bad) (void)hipHostFree(c->h_bad);
     if (c->h_recomputed) (void)hipHostFree(c->h_recomputed);
     if (!c->own_pack) c->s_pack = nullptr; // the caller's stream
-    for (hipStream_t st : {c->s_pack, c->s_copy, c->s_vcopy, c->s_vker})
+    for (hipStream_t st : {c->s_pack, c->s_vker})
         if (st) (void)hipStreamDestroy(st);
 }
 
@@ -714,11 +708,11 @@ ckpt_status ckpt_create(const ckpt_config* cfg, ckpt_ctx** out)
         c->s_pack = (hipStream_t)d.side_stream;
         c->own_pack = false;
     }
-    for (hipStream_t* sp : {&c->s_pack, &c->s_copy, &c->s_vcopy, &c->s_vker})
+    for (hipStream_t* sp : {&c->s_pack, &c->s_vker})
         if (st == CKPT_OK && !*sp && hipStreamCreateWithFlags(sp, hipStreamNonBlocking) != hipSuccess) st = CKPT_EHIP;
     for (hipEvent_t* e : {&c->ev_trigger, &c->ev_done, &c->ev_vdone})
         if (st == CKPT_OK) st = make_event(c, e, false);
-    for (hipEvent_t* e : {&c->tt0, &c->tc0, &c->tc1, &c->vt0, &c->vc0, &c->vc1})
+    for (hipEvent_t* e : {&c->tt0, &c->vt0})
         if (st == CKPT_OK) st = make_event(c, e, true);
     if (st == CKPT_OK) st = setup_hsa(c);
     if (st != CKPT_OK) {
@@ -819,7 +813,6 @@ ckpt_status ckpt_register_tensors(ckpt_ctx* c, const ckpt_tensor* t, uint32_t n)
     c->LG = (c->ring || c->direct || !c->launch_cfg) ? 1 : std::max<uint64_t>(1, c->launch_cfg / (c->G * c->C));
     c->n_launches = (c->n_groups + c->LG - 1) / c->LG;
     if (c->ring) c->n_slots = std::max<uint64_t>(1, std::min<uint64_t>(c->staging_cap / (c->G * c->C), c->n_groups));
-    if (c->direct) c->n_slots = std::min<uint64_t>(kDirectRestoreSlots, c->n_groups);
     const uint64_t unit = c->G * c->C; // bytes of one chunk group
     if (c->bounce_cfg) {
         if (c->bounce_cfg / unit < 2)
@@ -865,13 +858,8 @@ ckpt_status ckpt_register_tensors(ckpt_ctx* c, const ckpt_tensor* t, uint32_t n)
     ALLOC(c->d_frags, n * sizeof(FragDev));
     ALLOC(c->d_tile_src, nt * 8);
     ALLOC(c->d_partials, 2 * nt * 8);
-    ALLOC(c->d_expected, c->n_chunks * 8);
-    ALLOC(c->d_recomputed, c->n_chunks * 8);
-    ALLOC(c->d_bad, c->n_chunks);
     ALLOC(c->d_area_done, n_areas * 8);
-    ALLOC(c->d_staging, (c->ring || c->direct) ? c->n_slots * c->G * c->C : c->I);
-    c->n_vslots = std::min<uint64_t>(kVerifySlots, c->n_groups);
-    ALLOC(c->d_vring, c->n_vslots * c->G * c->C);
+    if (!c->direct) ALLOC(c->d_staging, c->ring ? c->n_slots * c->G * c->C : c->I);
 #undef ALLOC
     HIPCHK(c, hipMemcpy(c->d_frags, fd.data(), n * sizeof(FragDev), hipMemcpyHostToDevice));
     HIPCHK(c, hipMemcpy(c->d_tile_src, tile_src.data(), nt * 8, hipMemcpyHostToDevice));
@@ -916,35 +904,12 @@ ckpt_status ckpt_register_tensors(ckpt_ctx* c, const ckpt_tensor* t, uint32_t n)
     if (hipHostMalloc((void**)&c->h_bad, c->n_chunks, hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void**)&c->h_recomputed, c->n_chunks * 8, hipHostMallocDefault) != hipSuccess)
         return fail(c, CKPT_ENOMEM, "pinned result buffers");
-    c->area_free.resize(n_areas, nullptr);
-    for (auto& e : c->area_free) {
-        ckpt_status st = make_event(c, &e, false);
-        if (st) return st;
-        HIPCHK(c, hipEventRecord(e, c->s_copy)); // every area starts free
-    }
-    c->ev_loaded.resize(c->n_groups, nullptr);
-    c->tk0.resize(c->n_groups, nullptr);
-    c->tk1.resize(c->n_groups, nullptr);
-    for (uint64_t g = 0; g < c->n_groups; ++g) {
-        ckpt_status st = make_event(c, &c->ev_loaded[g], false);
-        if (!st) st = make_event(c, &c->tk0[g], true);
-        if (!st) st = make_event(c, &c->tk1[g], true);
-        if (st) return st;
-    }
-    c->vfree.resize(c->n_vslots, nullptr);
-    for (auto& e : c->vfree) {
-        ckpt_status st = make_event(c, &e, false);
-        if (st) return st;
-        HIPCHK(c, hipEventRecord(e, c->s_vker)); // every slot starts free
-    }
-    c->vloaded.resize(c->n_groups, nullptr);
-    c->vk0.resize(c->n_groups, nullptr);
-    c->vk1.resize(c->n_groups, nullptr);
-    for (uint64_t k = 0; k < c->n_groups; ++k) {
-        ckpt_status st = make_event(c, &c->vloaded[k], false);
-        if (!st) st = make_event(c, &c->vk0[k], true);
-        if (!st) st = make_event(c, &c->vk1[k], true);
-        if (st) return st;
+    for (auto* v : {&c->tk0, &c->tk1, &c->vk0, &c->vk1}) {
+        v->resize(c->n_groups, nullptr);
+        for (auto& e : *v) {
+            ckpt_status st = make_event(c, &e, true);
+            if (st) return st;
+        }
     }
     if (c->bounce) {
         c->bin_done.resize(c->n_bslots, nullptr);
