@@ -185,7 +185,11 @@ ckpt_status ckpt_register_tensors(ckpt_ctx* ctx, const ckpt_tensor* t, uint32_t 
  * device staging on the library's side stream, then copies the image and the
  * sums chunk group by chunk group into the host image that does not hold
  * the newest committed snapshot (with direct_d2h: sums the fragments in place
- * and copies them straight into that image).  One image always holds the newest
+ * and copies them straight into that image).  Pinned images of one chunk
+ * group and at most 2 MiB (direct_d2h: 16 MiB) are written by the pack kernel
+ * itself, over the link, unless timing is on, poison is set or the snapshot
+ * is to be interrupted; their gate opens when they are written.  One image
+ * always holds the newest
  * committed snapshot and the other receives the one in flight, so a
  * snapshot starts only once the previous one has committed (the caller's
  * wait before the optimizer step, Sec. VI-A, normally ensures that; with

@@ -60,6 +60,18 @@ struct Piece {
 };
 constexpr uint64_t kMaxDirectPieces = 65536;
 
+// Images up to these sizes (one chunk group, pinned) are packed straight into
+// host memory: the kernels write over the link at its full rate (57 GB/s), and
+// a DMA request costs ~10 us before its first byte.  Trigger to commit in us,
+// DMA -> kernel, 64 KiB and 1 MiB chunks: staged, 64 KiB 53 -> 46, 1 MiB
+// 72 -> 50/57, 2 MiB 90 -> 71/76, 4 MiB 130 -> 113/123, 8 MiB 204 -> 236; the
+// gate waits for the kernel, so the line lies where that is still less than a
+// DMA snapshot of nothing.  Direct, where each fragment is a request of ~9 us
+// and the gate waits for the copies either way: 8 fragments, 1 MiB 132 -> 54,
+// 16 MiB 431 -> 369; 240 fragments, 1 MiB 2247 -> 55, 16 MiB 2635 -> 370.
+constexpr uint64_t kInKernelStaged = 2ull << 20;
+constexpr uint64_t kInKernelDirect = 16ull << 20;
+
 // GPU-side resources of one snapshot record, recycled between snapshots.
 struct RecRes {
     std::vector<hipEvent_t> captured;   // per group, on the pack stream
@@ -76,6 +88,8 @@ struct RecRes {
     std::vector<hipEvent_t> k0, k1;     // timing: around each pack launch
     hipEvent_t t0 = nullptr;
     hipEvent_t t_red = nullptr;         // timing: after the chunk-sum reduce and its release
+    bool in_kernel = false;             // this snapshot's kernels write the host image themselves (no copies):
+                                        // it is done when dep_sums is 0
     std::atomic<uint32_t> landed{0};    // bounce mode: groups moved from the ring into the image
     std::atomic<bool> failed{false};    // bounce mode: a copy of this record could not be completed
     std::atomic<bool> recorded{false};  // image file: the commit record has been written

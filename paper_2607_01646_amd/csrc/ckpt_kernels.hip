@@ -315,13 +315,12 @@ __device__ __forceinline__ uint32_t find_frag_global(const FragDev* frags, uint3
     return lo;
 }
 
-// One tile: wave w owns vectors [w * slice, (w + 1) * slice) of it; lane 0
-// of the workgroup stores the tile's sum to partials[t].
+// One tile: wave w owns vectors [w * slice, (w + 1) * slice) of it.  Returns
+// the sum of the vectors this lane moved.
 template <int MODE, int BLOCK, int UNROLL, bool NTL, bool NTS>
-__device__ __forceinline__ void do_tile(const Args& a, uint64_t t, uint64_t* s_off, unsigned long long* s_red)
+__device__ __forceinline__ unsigned long long move_tile(const Args& a, uint64_t t, uint64_t* s_off)
 {
     static_assert(BLOCK * UNROLL * 16 == (1u << kMaxTileShift), "one batch per lane covers the largest tile");
-    constexpr uint32_t WAVES = BLOCK / 64;
     constexpr uint32_t kSlice = 64 * UNROLL; // vectors per wave slice
     const uint32_t tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const uint64_t base = t << a.g.tile_shift;
@@ -383,13 +382,20 @@ __device__ __forceinline__ void do_tile(const Args& a, uint64_t t, uint64_t* s_o
             }
         }
     }
-    acc = wave_sum(acc);
-    if (lane == 0) s_red[w] = acc;
+    return acc;
+}
+
+// One tile and its sum, stored by lane 0 of the workgroup to partials[t].
+template <int MODE, int BLOCK, int UNROLL, bool NTL, bool NTS>
+__device__ __forceinline__ void do_tile(const Args& a, uint64_t t, uint64_t* s_off, unsigned long long* s_red)
+{
+    const unsigned long long acc = wave_sum(move_tile<MODE, BLOCK, UNROLL, NTL, NTS>(a, t, s_off));
+    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = acc;
     __syncthreads();
-    if (tid == 0) {
+    if (threadIdx.x == 0) {
         unsigned long long sum = 0;
 #pragma unroll
-        for (uint32_t k = 0; k < WAVES; ++k) sum += s_red[k];
+        for (uint32_t k = 0; k < BLOCK / 64; ++k) sum += s_red[k];
         a.partials[t] = sum;
     }
 }
@@ -493,6 +499,21 @@ __global__ __launch_bounds__(kReduceBlock) void chunk_reduce_kernel(ReduceArgs r
         r.sums_out[c] = s;
         if (r.expected) r.bad[c] = (s != r.expected[c]) ? 1 : 0;
     }
+}
+
+// The pack of one workgroup per chunk: its tiles one after another, and the
+// chunk's sum to sums_out, so that no reduce has to follow.  For images small
+// enough that their time is launches and not bytes.
+__global__ __launch_bounds__(kBlock) void pack_chunks_kernel(Args a, unsigned long long* sums_out)
+{
+    __shared__ uint64_t s_off[kLdsFrags];
+    __shared__ unsigned long long s_red[kBlock / 64];
+    const uint64_t t0 = (uint64_t)blockIdx.x * a.g.tiles_per_chunk;
+    const uint64_t t1 = t0 + a.g.tiles_per_chunk < a.g.n_tiles ? t0 + a.g.tiles_per_chunk : a.g.n_tiles;
+    unsigned long long acc = 0;
+    for (uint64_t t = t0; t < t1; ++t) acc += move_tile<PACK, kBlock, kUnroll, true, true>(a, t, s_off);
+    acc = block_sum<kBlock>(acc, s_red);
+    if (threadIdx.x == 0) sums_out[blockIdx.x] = acc;
 }
 
 // With timing events, the launch records them around the dispatch itself
@@ -750,6 +771,14 @@ hipError_t launch_pack(const FragDev* frags, const uint64_t* tile_src,
 {
     Args a{frags, tile_src, g, t_lo, t_hi, dst, dst_origin, partials, release};
     return launch_tiles<PACK>(a, grid_cap, s, t0, t1);
+}
+
+hipError_t launch_pack_chunks(const FragDev* frags, const uint64_t* tile_src, const Geometry& g, uint8_t* dst,
+                              unsigned long long* sums_out, hipStream_t s)
+{
+    Args a{frags, tile_src, g, 0, g.n_tiles, dst, 0, nullptr, nullptr};
+    hipLaunchKernelGGL(pack_chunks_kernel, dim3((uint32_t)g.n_chunks), dim3(kBlock), 0, s, a, sums_out);
+    return hipGetLastError();
 }
 
 hipError_t launch_sums(const FragDev* frags, const uint64_t* tile_src,

@@ -364,7 +364,7 @@ ckpt_status get_res(ckpt_ctx* c, RecRes** out)
 
 bool res_done(const RecRes* res, uint32_t groups_copied, bool bounce)
 {
-    if (hsa_signal_load_scacquire(res->done) != 0) return false;
+    if (hsa_signal_load_scacquire(res->in_kernel ? res->dep_sums : res->done) != 0) return false;
     for (uint32_t g = 0; g < groups_copied; ++g)
         if (hsa_signal_load_scacquire(res->flagged[g]) != 0) return false;
     if (bounce && res->landed.load(std::memory_order_acquire) < groups_copied) return false;
@@ -387,25 +387,40 @@ bool pump_failed(ckpt_ctx* c, std::string* why)
     return c->pump->failed;
 }
 
+// Poll a signal that only the GPU is told about until it is 0; false after
+// the deadline.  The first 100 us without sleeping: a sleep of 20 us takes
+// about 75, and the last of a snapshot's signals is usually a few away.
+bool poll_until(hsa_signal_t sig, std::chrono::steady_clock::time_point deadline)
+{
+    const auto spin = std::chrono::steady_clock::now() + std::chrono::microseconds(100);
+    while (hsa_signal_load_scacquire(sig) != 0) {
+        const auto now = std::chrono::steady_clock::now();
+        if (now > deadline) return false;
+        if (now > spin) std::this_thread::sleep_for(std::chrono::microseconds(20));
+    }
+    return true;
+}
+
 // Wait (bounded) until every copy of a snapshot has finished.
 ckpt_status wait_copies(ckpt_ctx* c, SnapRec& r)
 {
     // The wait's timeout is only a hint (in system-timestamp ticks): wait in
     // one-second slices against our own deadline.
     const auto deadline = std::chrono::steady_clock::now() + std::chrono::seconds(120);
+    if (r.res->in_kernel) { // a signal with no event behind it, stored by the GPU
+        if (!poll_until(r.res->dep_sums, deadline))
+            return fail(c, CKPT_EHIP, "snapshot %llu: not packed after 120 s", (unsigned long long)r.id);
+        return CKPT_OK;
+    }
     while (hsa_signal_wait_scacquire(r.res->done, HSA_SIGNAL_CONDITION_EQ, 0, c->ts_freq, HSA_WAIT_STATE_BLOCKED) != 0)
         if (std::chrono::steady_clock::now() > deadline)
             return fail(c, CKPT_EHIP, "snapshot %llu: chunk sums not copied after 120 s", (unsigned long long)r.id);
     // The per-group signals have the GPU as their only waiter; the host
     // polls their values (the engines run the groups in order, so this
     // rarely finds one still pending once the sums have landed).
-    for (uint32_t g = 0; g < r.groups_copied; ++g) {
-        while (hsa_signal_load_scacquire(r.res->flagged[g]) != 0) {
-            if (std::chrono::steady_clock::now() > deadline)
-                return fail(c, CKPT_EHIP, "snapshot %llu: group %u not copied after 120 s", (unsigned long long)r.id, g);
-            std::this_thread::sleep_for(std::chrono::microseconds(20));
-        }
-    }
+    for (uint32_t g = 0; g < r.groups_copied; ++g)
+        if (!poll_until(r.res->flagged[g], deadline))
+            return fail(c, CKPT_EHIP, "snapshot %llu: group %u not copied after 120 s", (unsigned long long)r.id, g);
     if (r.bounce) { // every group also has to reach the pageable image
         while (r.res->landed.load(std::memory_order_acquire) < r.groups_copied) {
             if (std::chrono::steady_clock::now() > deadline)

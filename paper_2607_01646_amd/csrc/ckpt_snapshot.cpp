@@ -306,8 +306,50 @@ ckpt_status issue_groups(ckpt_ctx* c, SnapRec& r, hipStream_t after, uint64_t n_
     return CKPT_OK;
 }
 
+// A small image: the pack writes it into host memory over the link and the
+// chunk sums follow, with no staging and no DMA request.
+ckpt_status issue_in_kernel(ckpt_ctx* c, SnapRec& r, hipStream_t after)
+{
+    RecRes* res = r.res;
+    hipStream_t s = c->s_pack;
+    HIPCHK(c, hipEventRecord(c->ev_trigger, after));
+    HIPCHK(c, hipStreamWaitEvent(s, c->ev_trigger, 0));
+    unsigned long long* sums = (unsigned long long*)c->h_sums[r.buf];
+    hipError_t e;
+    if (c->C <= kSmallSpan) {
+        e = launch_pack_chunks(c->d_frags, c->d_tile_src, c->geo, c->h_img[r.buf], sums, s);
+        if (e != hipSuccess) return fail(c, CKPT_EHIP, "pack launch failed: %s", hipGetErrorString(e));
+        HIPCHK(c, hipEventRecord(res->captured[0], s));
+    } else {
+        e = launch_pack(c->d_frags, c->d_tile_src, c->geo, 0, c->geo.n_tiles, c->h_img[r.buf], 0, c->d_partials,
+                        std::min(c->grid_cap, kHostPackGrid), s);
+        if (e != hipSuccess) return fail(c, CKPT_EHIP, "pack launch failed: %s", hipGetErrorString(e));
+        HIPCHK(c, hipEventRecord(res->captured[0], s));
+        e = launch_chunk_reduce(c->geo, 0, c->geo.n_tiles, c->d_partials, sums, nullptr, nullptr, s);
+        if (e != hipSuccess) return fail(c, CKPT_EHIP, "reduce launch failed: %s", hipGetErrorString(e));
+    }
+    e = launch_release(res->dep_sums_val, s);
+    if (e != hipSuccess) return fail(c, CKPT_EHIP, "release launch failed: %s", hipGetErrorString(e));
+    return CKPT_OK;
+}
+
+// Whether snapshot r takes issue_in_kernel: with timing on, an interruption
+// or the canary asked for, it takes the way that those look into.
+bool small_image(const ckpt_ctx* c, const SnapRec& r, int32_t stop)
+{
+    return c->n_groups == 1 && c->I <= (c->direct ? kInKernelDirect : kInKernelStaged) && !c->bounce &&
+           !c->poison && !r.timed && stop < 0;
+}
+
 ckpt_status issue_snapshot(ckpt_ctx* c, SnapRec& r, hipStream_t after, uint64_t n_copy, int32_t stop)
 {
+    r.res->in_kernel = small_image(c, r, stop);
+    if (r.res->in_kernel) {
+        hsa_signal_store_screlease(r.res->dep_sums, 1);
+        const ckpt_status st = issue_in_kernel(c, r, after);
+        if (st) hsa_signal_store_screlease(r.res->dep_sums, 0);
+        return st;
+    }
     hsa_signal_t carried{0};
     const ckpt_status st = c->direct ? issue_groups_direct(c, r, after, n_copy, stop, carried)
                                      : issue_groups(c, r, after, n_copy, stop, carried);

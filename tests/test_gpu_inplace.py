@@ -6,9 +6,13 @@ import pytest
 import torch
 
 import oracle as O
+
 from gpu_util import garbage_fill, host_bytes, random_byte_fragments, snapshot_and_check
 
 pytestmark = pytest.mark.gpu
+
+if torch.cuda.is_available():
+    import paper_2607_01646_amd as P
 
 TILE = 8192
 
@@ -37,4 +41,35 @@ def test_host_changes_between_calls_are_seen(tiles, mode):
         assert ck.restore() == []
         assert all(np.array_equal(host_bytes(t), h) for t, h in zip(tensors, host))
     assert np.array_equal(img, before)
+    ck.close()
+
+
+@pytest.mark.parametrize("direct", [False, True])
+@pytest.mark.parametrize("size,chunk", [
+    (1, 65536), (65536, 65536), (100_000, 16), (1_000_000, 48), (1 << 20, 4096), (1 << 20, 65536 + 16),
+    (2 << 20, 65536), ((2 << 20) + 1, 65536), (2 << 20, 1 << 20),  # about the largest staged image
+    (16 << 20, 65536), ((16 << 20) - 5, 1 << 20), ((16 << 20) + 1, 1 << 20),  # ... and direct one
+])
+def test_small_images_written_by_the_kernel(size, chunk, direct):
+    """Images on both sides of the sizes that the pack writes straight into
+    host memory: image and sums against the oracle, the gate before an
+    overwrite, and such snapshots before and after one that was interrupted."""
+    tensors, host = random_byte_fragments([size // 3, 0, size - size // 3], seed=size + chunk)
+    ck, _ = snapshot_and_check(tensors, host, chunk, 16, direct=direct)
+    for step in range(3):
+        before = [host_bytes(t) for t in tensors]
+        if step == 1:
+            P.ckpt_debug_interrupt_next(ck.ctx, 0)
+        s = ck.snapshot(step=step)
+        ck.wait_captured(s)
+        garbage_fill(tensors, 17 + step)  # behind the gate
+        if step == 1:
+            torch.cuda.synchronize()
+            assert ck.state(s) == P.CKPT_SNAP_ABORTED
+            continue
+        ck.wait_committed(s)
+        img, sums = ck.host_image(s)
+        want, _, _ = O.pack(before, 16, chunk)
+        assert np.array_equal(img, want)
+        assert np.array_equal(sums, O.chunk_sums(want, 0, want.size, chunk))
     ck.close()
