@@ -132,7 +132,9 @@ typedef struct {
                                       host image.  Costs one extra write of the staging per snapshot. */
     uint32_t direct_d2h;           /* nonzero = no device staging for snapshots: the DMA engines copy
                                       each fragment from the live tensors straight into its place in
-                                      the host image (or the bounce ring), the padding between
+                                      the host image (or the bounce ring; into a pinned image a
+                                      kernel copies the pieces of up to 512 KiB, which the engines
+                                      would take longer to take up than to copy), the padding between
                                       fragments is zeroed on the host, and the snapshot's kernels
                                       only compute the chunk sums (reading the fragments once: half
                                       the HBM traffic of pack + copy, and no device image).  The

@@ -50,14 +50,6 @@ struct Frag {
     uint32_t dtype, cls;
 };
 
-// Direct D2H: the bytes of one fragment inside one chunk group (the DMA
-// engines copy each piece straight from the tensor), or one run of image
-// padding inside a group (zeroed on the host before the group's copies).
-struct Piece {
-    uint64_t src; // device address (pieces); unused for padding
-    uint64_t off; // image offset
-    uint64_t n;
-};
 constexpr uint64_t kMaxDirectPieces = 65536;
 
 // Images up to these sizes (one chunk group, pinned) are packed straight into
@@ -349,9 +341,11 @@ struct ckpt_ctx {
     bool direct = false;   // direct D2H: no snapshot staging, the engines copy the fragments
     std::vector<Piece> pieces, gaps;              // direct D2H, by group (CSR below)
     std::vector<uint64_t> piece_first, gap_first; // [n_groups + 1]
+    std::vector<uint64_t> small_first;            // [n_groups + 1]: the pieces that a kernel copies instead
 
     // device memory
     FragDev* d_frags = nullptr;
+    Piece* d_small = nullptr;                 // direct D2H: the small pieces, by group
     uint64_t* d_tile_src = nullptr;           // per tile: tile_entry()
     uint8_t* d_staging = nullptr;
     unsigned long long* d_partials = nullptr; // [2][n_tiles] tile partial sums: pack, check

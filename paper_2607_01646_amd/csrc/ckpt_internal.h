@@ -104,6 +104,27 @@ hipError_t launch_chunk_reduce(const Geometry& g, uint64_t t_lo, uint64_t t_hi, 
                                unsigned long long* sums_out, const unsigned long long* expected, uint8_t* bad,
                                hipStream_t s, int64_t* release = nullptr);
 
+// Direct D2H: the bytes of one fragment inside one chunk group, or one run of
+// image padding inside a group (zeroed on the host before the group's copies).
+struct Piece {
+    uint64_t src; // device address (pieces); unused for padding
+    uint64_t off; // image offset
+    uint64_t n;
+};
+
+// Copy pieces[0, n_pieces) (device memory) into the pinned host image img:
+// the pieces of up to kKernelPiece bytes, which the DMA engines would spend
+// more time taking up than copying.  A DMA request costs its engine ~9 us, in
+// which the link moves 512 KiB; below that a kernel of few workgroups is
+// faster.  Direct snapshot in us by largest kernel piece, none / 32 / 128 /
+// 512 KiB / 2 MiB: 1.5 GB in 400 fragments 29032 / 27899 / 27902 / 27897 /
+// 28062, 512 MiB in 1024 ragged ones 19178 / 14145 / 13016 / 11758 / 10708,
+// 100 MiB in 300 4749 / 3198 / 2898 / 2537 / 2408 (pieces over 512 KiB stay
+// with the engines all the same: they leave the compute units alone).
+constexpr uint64_t kKernelPiece = 512ull << 10;
+constexpr uint32_t kPieceGrid = 64;
+hipError_t launch_copy_pieces(const Piece* pieces, uint64_t n_pieces, uint8_t* img, hipStream_t s);
+
 // Store 0 into *signal_value (an HSA signal's value) once the work enqueued
 // on s before this call has completed.
 hipError_t launch_release(int64_t* signal_value, hipStream_t s);

@@ -532,6 +532,18 @@ hipError_t launch_tiles(const Args& a, uint32_t grid_cap, hipStream_t s, hipEven
     return hipGetLastError();
 }
 
+// Bytes [src, src + n) to img + off for each of a list of small pieces (see
+// launch_copy_pieces): workgroups stride over the pieces, each lane moves 16
+// bytes at a time, and no byte outside a piece is written.
+__global__ __launch_bounds__(256) void copy_pieces_kernel(const Piece* pieces, uint64_t n_pieces, uint8_t* img)
+{
+    for (uint64_t k = blockIdx.x; k < n_pieces; k += gridDim.x) {
+        const Piece pc = pieces[k];
+        for (uint64_t x = 16 * threadIdx.x; x < pc.n; x += 16 * 256)
+            store_general((uint64_t)(uintptr_t)img + pc.off, pc.n, x, fetch_general(pc.src, pc.n, x));
+    }
+}
+
 // One lane: publish "this point of the stream has been reached" to a DMA
 // engine by storing 0 into an HSA signal value it polls.  The store is a
 // system-scope release; the kernels before it on the stream have finished
@@ -755,6 +767,14 @@ hipError_t launch_tile_table(const FragDev* frags, uint32_t n, const Geometry& g
     const uint64_t nt = t_hi - t_lo;
     hipLaunchKernelGGL(tile_table_kernel, dim3((uint32_t)((nt + 255) / 256)), dim3(256), 0, s, frags, n, g, t_lo, t_hi,
                        tile_src);
+    return hipGetLastError();
+}
+
+hipError_t launch_copy_pieces(const Piece* pieces, uint64_t n_pieces, uint8_t* img, hipStream_t s)
+{
+    if (n_pieces == 0) return hipSuccess;
+    hipLaunchKernelGGL(copy_pieces_kernel, dim3((uint32_t)std::min<uint64_t>(n_pieces, kPieceGrid)), dim3(256), 0, s,
+                       pieces, n_pieces, img);
     return hipGetLastError();
 }
 

@@ -153,6 +153,28 @@ bool direct_plan(const uint64_t* off, const uint64_t* nb, uint32_t n, uint64_t I
     return true;
 }
 
+// Direct D2H into pinned images: move the small pieces of c->pieces, except
+// each group's last (whose copy signals the group's), to `small`.  With
+// pageable images the ring slot a group goes through is not known when its
+// kernels are enqueued, so the engines copy everything.
+void split_small(ckpt_ctx* c, std::vector<Piece>& small)
+{
+    std::vector<Piece> large;
+    std::vector<uint64_t> first(c->n_groups + 1, 0);
+    c->small_first.assign(c->n_groups + 1, 0);
+    for (uint64_t g = 0; g < c->n_groups; ++g) {
+        first[g] = large.size();
+        c->small_first[g] = small.size();
+        for (uint64_t k = c->piece_first[g]; k < c->piece_first[g + 1]; ++k)
+            (!c->bounce && c->pieces[k].n <= kKernelPiece && k + 1 < c->piece_first[g + 1] ? small : large)
+                .push_back(c->pieces[k]);
+    }
+    first[c->n_groups] = large.size();
+    c->small_first[c->n_groups] = small.size();
+    c->pieces.swap(large);
+    c->piece_first.swap(first);
+}
+
 ckpt_status make_event(ckpt_ctx* c, hipEvent_t* e, bool timed)
 {
     HIPCHK(c, hipEventCreateWithFlags(e, timed ? hipEventDefault : hipEventDisableTiming));
@@ -596,6 +618,7 @@ void free_ctx(ckpt_ctx* c)
     for (hipEvent_t e : {c->ev_trigger, c->ev_done, c->tt0, c->ev_vdone, c->vt0})
         if (e) (void)hipEventDestroy(e);
     (void)hipFree(c->d_frags);
+    (void)hipFree(c->d_small);
     (void)hipFree(c->d_tile_src);
     (void)hipFree(c->d_staging);
     (void)hipFree(c->d_partials);
@@ -844,6 +867,7 @@ ckpt_status ckpt_register_tensors(ckpt_ctx* c, const ckpt_tensor* t, uint32_t n)
         fd[i].off = pl.off[i];
         fd[i].end = pl.end[i];
     }
+    std::vector<Piece> small;
     if (c->direct) { // each group's fragment pieces and padding runs, copied and zeroed per snapshot
         std::vector<uint64_t> fo(n);
         for (uint32_t i = 0; i < n; ++i) fo[i] = c->frags[i].off;
@@ -855,6 +879,7 @@ ckpt_status ckpt_register_tensors(ckpt_ctx* c, const ckpt_tensor* t, uint32_t n)
             return fail(c, CKPT_EINVAL, "direct D2H: %llu fragment pieces, at most %llu",
                         (unsigned long long)c->pieces.size(), (unsigned long long)kMaxDirectPieces);
         for (size_t k = 0; k < c->pieces.size(); ++k) c->pieces[k].src += c->frags[pf[k]].ptr;
+        split_small(c, small);
     }
     const uint64_t nt = pl.n_tiles;
     std::vector<uint64_t> tile_src(nt);
@@ -874,9 +899,12 @@ ckpt_status ckpt_register_tensors(ckpt_ctx* c, const ckpt_tensor* t, uint32_t n)
     ALLOC(c->d_tile_src, nt * 8);
     ALLOC(c->d_partials, 2 * nt * 8);
     ALLOC(c->d_area_done, n_areas * 8);
+    if (!small.empty()) ALLOC(c->d_small, small.size() * sizeof(Piece));
     if (!c->direct) ALLOC(c->d_staging, c->ring ? c->n_slots * c->G * c->C : c->I);
 #undef ALLOC
     HIPCHK(c, hipMemcpy(c->d_frags, fd.data(), n * sizeof(FragDev), hipMemcpyHostToDevice));
+    if (!small.empty())
+        HIPCHK(c, hipMemcpy(c->d_small, small.data(), small.size() * sizeof(Piece), hipMemcpyHostToDevice));
     HIPCHK(c, hipMemcpy(c->d_tile_src, tile_src.data(), nt * 8, hipMemcpyHostToDevice));
     HIPCHK(c, hipMemset(c->d_area_done, 0, n_areas * 8));
     c->area_seq.assign(n_areas, 0);

@@ -73,3 +73,22 @@ def test_small_images_written_by_the_kernel(size, chunk, direct):
         assert np.array_equal(img, want)
         assert np.array_equal(sums, O.chunk_sums(want, 0, want.size, chunk))
     ck.close()
+
+
+@pytest.mark.parametrize("align,shift", [(16, 1), (256, 0), (4096, 6)])
+def test_direct_pieces_around_the_kernel_size(align, shift):
+    """Direct D2H over several groups: pieces that the kernel copies and
+    pieces that the engines copy side by side, from unaligned fragments, and
+    groups whose only piece is a small one."""
+    k = 512 << 10
+    sizes = [k - 1, 3, k, 0, k + 1, 5 * k + 7, 16, 1, 1000, 2 * k, 4097, 40 * k + 11, 17, 255]
+    flat = torch.from_numpy(np.random.default_rng(align).integers(0, 256, sum(sizes) + 64 * len(sizes), dtype=np.uint8))
+    flat, at, views = flat.cuda(), shift, []
+    for n in sizes:
+        views.append(flat[at:at + n])
+        at += n + 3
+    before = host_bytes(flat)
+    for chunk, group in [(1 << 20, 4 << 20), (1 << 19, 1 << 19), (1 << 20, 0)]:
+        ck, _ = snapshot_and_check(views, [host_bytes(v) for v in views], chunk, align, group=group, direct=True)
+        ck.close()
+        assert np.array_equal(host_bytes(flat), before)
