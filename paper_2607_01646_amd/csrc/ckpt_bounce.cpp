@@ -17,6 +17,14 @@ bool poll_zero(hsa_signal_t sig, int seconds)
     return true;
 }
 
+// Wait (bounded) until a group's image copies have finished.
+bool copied_all(ckpt_ctx* c, const PumpItem& it)
+{
+    hsa_signal_t ends[2];
+    const int n = group_signals(c, it.res, it.g, ends);
+    return poll_zero(ends[0], 120) && (n < 2 || poll_zero(ends[1], 120));
+}
+
 // Bounce mode, issuer thread (see Pump).
 void pump_issue(ckpt_ctx* c)
 {
@@ -71,26 +79,28 @@ void pump_issue(ckpt_ctx* c)
         if (slot != UINT64_MAX) {
             if (c->direct) { // the group's fragment pieces, straight from the tensors into the slot
                 const uint64_t want = c->piece_first[it.g + 1] - c->piece_first[it.g];
+                const hsa_amd_sdma_engine_id_t engs[2] = {it.engine, it.engine};
                 const uint64_t got = issue_pieces(c, it.res, it.g, c->h_bout + slot * unit, c->img_agent[0],
-                                                  &it.res->dep[it.g], it.engine);
+                                                  &it.res->dep[it.g], engs);
                 issued = got == want;
                 if (!issued) {
                     // the pieces already issued must have finished before the slot is reused
-                    if (got) (void)poll_zero(it.res->piece_done[c->piece_first[it.g] + got - 1], 120);
+                    wait_pieces(c, it.res, it.g, got);
                     what = "DMA of a fragment piece to the bounce ring could not be issued";
                 }
             } else {
-                issued = hsa_amd_memory_async_copy_on_engine(c->h_bout + slot * unit, c->img_agent[0], it.staging,
-                                                             c->gpu_agent, it.n, 1,
-                                                             &it.res->dep[it.g / c->LG * c->LG],
-                                                             it.res->copied[it.g], it.engine,
-                                                             true) == HSA_STATUS_SUCCESS;
+                const int got = issue_halves(c, it.res, it.g, c->h_bout + slot * unit, c->img_agent[0], it.staging,
+                                             it.n, &it.res->dep[it.g / c->LG * c->LG]);
+                issued = got == (in_halves(c, it.g) ? 2 : 1);
+                if (!issued && got) (void)poll_zero(it.res->copied[it.g], 120); // before the slot is reused
                 if (!issued) what = "DMA of a chunk group to the bounce ring could not be issued";
             }
+            hsa_signal_t ends[2];
+            const int n_ends = group_signals(c, it.res, it.g, ends);
             if (issued)
-                counted = hsa_amd_memory_async_copy_on_engine(it.area_done, c->gpu_agent, it.seq, c->img_agent[0], 8, 1,
-                                                              &it.res->copied[it.g], it.res->flagged[it.g],
-                                                              c->h2d_engine, true) == HSA_STATUS_SUCCESS;
+                counted = hsa_amd_memory_async_copy_on_engine(it.area_done, c->gpu_agent, it.seq, c->img_agent[0], 8,
+                                                              n_ends, ends, it.res->flagged[it.g], c->h2d_engine,
+                                                              true) == HSA_STATUS_SUCCESS;
             if (issued && !counted) what = "staging counter copy could not be issued";
         }
         if (!issued) hsa_signal_store_screlease(it.res->copied[it.g], 0);
@@ -98,7 +108,7 @@ void pump_issue(ckpt_ctx* c)
             // Nothing bumps the staging area's use counter through the
             // engines: once no copy reads the area, write it directly, so
             // that no later pack waits for it forever.
-            if (!issued || poll_zero(it.res->copied[it.g], 120)) (void)hsa_memory_copy(it.area_done, it.seq, 8);
+            if (!issued || copied_all(c, it)) (void)hsa_memory_copy(it.area_done, it.seq, 8);
             hsa_signal_store_screlease(it.res->flagged[it.g], 0);
         }
         std::lock_guard<std::mutex> l(p->m);
@@ -150,7 +160,7 @@ void pump_drain(ckpt_ctx* c)
         }
         bool free_slot = slot != UINT64_MAX, ok = free_slot;
         if (ok) {
-            ok = poll_zero(it.res->copied[it.g], 120);
+            ok = copied_all(c, it);
             // The image's record (an older snapshot's) stops counting before
             // the first byte of a new one lands.
             if (ok && it.g == 0 && c->file_map) file_invalidate(c, it.buf);

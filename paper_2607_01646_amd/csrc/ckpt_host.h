@@ -43,6 +43,9 @@ constexpr uint64_t kDefaultLaunch = 0; // full-image staging: bytes per pack lau
 constexpr uint32_t kMaxMeta = 1u << 20;
 constexpr uint32_t kDefaultGrid = 0x7fffffff; // one workgroup per tile unless capped
 constexpr int kMaxEngines = 2;
+// Group copies of at least this many bytes are dealt to both engines in halves
+// (~57 GB/s together, ~55 alone); below, a second request costs more.
+constexpr uint64_t kSplitCopy = 8ull << 20;
 constexpr uint32_t kDefaultHostThreads = 12; // bounce mode: host copy threads (measured: 8 do not keep up with the link)
 
 struct Frag {
@@ -72,7 +75,8 @@ struct RecRes {
     std::vector<hsa_signal_t> copied;   // per group: the group's image copy finished
     std::vector<hsa_signal_t> flagged;  // per group: the area-done copy after it finished
     std::vector<hsa_signal_t> piece_done; // direct D2H, per piece but each group's last (whose copy
-                                          // signals `copied`): the piece's copy finished
+                                          // signals `copied`): the piece's copy finished;
+                                          // else per group: the copy of its second half (issue_halves)
     hsa_signal_t dep_sums{0}, done{0};  // sums packed; sums copied (the last copy issued)
     int64_t* dep_sums_val = nullptr;
     uint64_t* h_seq = nullptr;          // pinned, per group: area use number, source of the area-done copy
@@ -341,6 +345,9 @@ struct ckpt_ctx {
     bool direct = false;   // direct D2H: no snapshot staging, the engines copy the fragments
     std::vector<Piece> pieces, gaps;              // direct D2H, by group (CSR below)
     std::vector<uint64_t> piece_first, gap_first; // [n_groups + 1]
+    std::vector<uint8_t> piece_chain;             // per piece: which of its group's two chains of copies it is in
+    std::vector<uint64_t> other_last;             // per group: last piece of the chain that does not end with the
+                                                  // group's last piece (UINT64_MAX: a single chain)
     std::vector<uint64_t> small_first;            // [n_groups + 1]: the pieces that a kernel copies instead
 
     // device memory
@@ -449,6 +456,11 @@ bool geometry_ok(uint64_t C, uint32_t A);
 // device image) and where that area starts.
 inline uint64_t group_lo(const ckpt_ctx* c, uint64_t g) { return g * c->G * c->C; }
 inline uint64_t group_hi(const ckpt_ctx* c, uint64_t g) { return std::min((g + 1) * c->G * c->C, c->I); }
+// Whether group g's staged copy is dealt to two engines in halves.
+inline bool in_halves(const ckpt_ctx* c, uint64_t g)
+{
+    return c->n_d2h_engines > 1 && group_hi(c, g) - group_lo(c, g) >= kSplitCopy;
+}
 inline uint64_t tiles_lo(const ckpt_ctx* c, uint64_t g) { return group_lo(c, g) >> c->geo.tile_shift; }
 inline uint64_t tiles_hi(const ckpt_ctx* c, uint64_t g)
 {
@@ -463,10 +475,11 @@ inline uint8_t* staging_of(const ckpt_ctx* c, uint64_t g)
 ckpt_status make_event(ckpt_ctx* c, hipEvent_t* e, bool timed);
 // Milliseconds between two recorded timing events (-1 when unavailable).
 float elapsed(hipEvent_t a, hipEvent_t b);
-// Issue one SDMA copy of n bytes on `engine`, after *dep (when non-null),
-// completing into `completion`.
+// Issue one SDMA copy of n bytes on `engine`, after the n_dep signals at dep
+// (when non-null), completing into `completion`.
 ckpt_status dma(ckpt_ctx* c, void* dst, hsa_agent_t dst_agent, const void* src, hsa_agent_t src_agent, uint64_t n,
-                const hsa_signal_t* dep, hsa_signal_t completion, hsa_amd_sdma_engine_id_t engine);
+                const hsa_signal_t* dep, hsa_signal_t completion, hsa_amd_sdma_engine_id_t engine,
+                uint32_t n_dep = 1);
 // Text of this thread's last failed ckpt_pack_noalloc ("" if none).
 const char* noalloc_error();
 
@@ -498,12 +511,24 @@ std::vector<uint8_t> build_envelope(const ckpt_ctx* c, uint64_t step, const std:
 ckpt_status issue_snapshot(ckpt_ctx* c, SnapRec& r, hipStream_t after, uint64_t n_copy, int32_t stop);
 
 // Direct D2H: zero group g's padding runs in `dst` (host memory holding the
-// group's first image byte at dst), then copy its fragment pieces into place
-// on `engine`, each after the previous one (the first after first_dep); the
-// group's last piece signals res->copied[g].  Returns the pieces issued:
-// fewer than the group's means a copy could not be issued (ckpt_snapshot.cpp).
+// group's first image byte at dst), then copy its fragment pieces into place,
+// those of chain e on engine[e], each after the previous one of its chain
+// (the first after first_dep); the group's last piece signals
+// res->copied[g].  Returns the pieces issued: fewer than the group's means a
+// copy could not be issued (ckpt_snapshot.cpp).
 uint64_t issue_pieces(ckpt_ctx* c, RecRes* res, uint64_t g, uint8_t* dst, hsa_agent_t dst_agent,
-                      const hsa_signal_t* first_dep, hsa_amd_sdma_engine_id_t engine);
+                      const hsa_signal_t* first_dep, const hsa_amd_sdma_engine_id_t engine[2]);
+// Copy group g, n bytes at src (device staging) to dst (pinned), after *dep:
+// its halves on the two engines, or in one request when it is small or there is
+// one engine.  Returns the requests issued: fewer than group_signals() counts
+// means that one could not be (the signals of what was not issued are 0).
+int issue_halves(ckpt_ctx* c, RecRes* res, uint64_t g, uint8_t* dst, hsa_agent_t dst_agent, const uint8_t* src,
+                 uint64_t n, const hsa_signal_t* dep);
+// Wait (bounded) until the first `got` pieces of group g have been copied.
+void wait_pieces(ckpt_ctx* c, RecRes* res, uint64_t g, uint64_t got);
+// The signals that reach 0 once group g's image copies have finished: `copied`,
+// and the end of the group's other chain or its second half.  Returns how many.
+int group_signals(const ckpt_ctx* c, const RecRes* res, uint64_t g, hsa_signal_t out[2]);
 
 // Bounce mode (ckpt_bounce.cpp)
 bool poll_zero(hsa_signal_t sig, int seconds);

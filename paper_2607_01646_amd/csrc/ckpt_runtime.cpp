@@ -7,8 +7,8 @@
 //                  pack kernel (fragments -> staging, tile sums)
 //                  event captured[g]            <- the gate waits on this
 //                  release kernel: dep[g] = 0
-//   SDMA engine e: (polls dep[g]) copy staging(g) -> pinned image   -> copied[g]
-//   counter engine: (after copied[g]) 8-byte copy: area_done[area(g)] = use count
+//   SDMA engines : (poll dep[g]) copy the halves of staging(g) -> pinned image -> copied[g], piece_done[g]
+//   counter engine: (after both) 8-byte copy: area_done[area(g)] = use count
 //   after the last group: one reduce kernel (tile sums -> chunk sums), release
 //   dep_sums; SDMA copies the chunk sums.
 //
@@ -18,7 +18,7 @@
 // reached 0.
 //
 // The image copies go to the DMA engines through the HSA runtime that HIP
-// itself runs on, two engines taking alternate groups (one engine alone
+// itself runs on, each group's copy dealt to two engines (one engine alone
 // does not fill the host link).  A plain hipMemcpyAsync D2H may instead be
 // run as a copy kernel on the compute units, competing with the pack and
 // with the training step.
@@ -173,6 +173,29 @@ void split_small(ckpt_ctx* c, std::vector<Piece>& small)
     c->small_first[c->n_groups] = small.size();
     c->pieces.swap(large);
     c->piece_first.swap(first);
+}
+
+// Direct D2H into pinned images: deal each group's pieces to two chains of
+// about the same bytes, one for each DMA engine.  One engine moves ~50 GB/s of
+// a link of 57, and dealing whole groups instead leaves one engine alone at
+// the end (and throughout, with one group).  With pageable images a group
+// stays one chain: the ring's groups are to land one after another.
+void deal_chains(ckpt_ctx* c)
+{
+    c->piece_chain.assign(c->pieces.size(), 0);
+    c->other_last.assign(c->n_groups, UINT64_MAX);
+    if (c->bounce) return;
+    for (uint64_t g = 0; g < c->n_groups; ++g) {
+        const uint64_t p0 = c->piece_first[g], p1 = c->piece_first[g + 1];
+        uint64_t bytes[2] = {0, 0}, last[2] = {UINT64_MAX, UINT64_MAX};
+        for (uint64_t k = p0; k < p1; ++k) {
+            const int e = bytes[1] < bytes[0] ? 1 : 0;
+            c->piece_chain[k] = (uint8_t)e;
+            bytes[e] += c->pieces[k].n;
+            last[e] = k;
+        }
+        c->other_last[g] = last[1 - c->piece_chain[p1 - 1]];
+    }
 }
 
 ckpt_status make_event(ckpt_ctx* c, hipEvent_t* e, bool timed)
@@ -350,6 +373,11 @@ ckpt_status new_res(ckpt_ctx* c, RecRes** out)
         for (uint64_t g = 0; g < n && st == CKPT_OK; ++g)
             for (uint64_t k = c->piece_first[g]; k + 1 < c->piece_first[g + 1] && st == CKPT_OK; ++k)
                 st = gpu_consumed_signal(c, &r->piece_done[k]);
+    }
+    if (!c->direct) {
+        r->piece_done.assign(n, hsa_signal_t{0});
+        for (uint64_t g = 0; g < n && st == CKPT_OK; ++g)
+            if (in_halves(c, g)) st = gpu_consumed_signal(c, &r->piece_done[g]);
     }
     if (st == CKPT_OK) st = make_event(c, &r->t0, true);
     if (st == CKPT_OK) st = make_event(c, &r->t_red, true);
@@ -647,9 +675,9 @@ void free_ctx(ckpt_ctx* c)
 // Issue one SDMA copy; on failure the dependency chain of the snapshot is
 // released so no engine is left polling.
 ckpt_status dma(ckpt_ctx* c, void* dst, hsa_agent_t dst_agent, const void* src, hsa_agent_t src_agent, uint64_t n,
-                const hsa_signal_t* dep, hsa_signal_t completion, hsa_amd_sdma_engine_id_t engine)
+                const hsa_signal_t* dep, hsa_signal_t completion, hsa_amd_sdma_engine_id_t engine, uint32_t n_dep)
 {
-    HSACHK(c, hsa_amd_memory_async_copy_on_engine(dst, dst_agent, src, src_agent, n, dep ? 1 : 0, dep, completion,
+    HSACHK(c, hsa_amd_memory_async_copy_on_engine(dst, dst_agent, src, src_agent, n, dep ? n_dep : 0, dep, completion,
                                                   engine, true));
     return CKPT_OK;
 }
@@ -880,6 +908,7 @@ ckpt_status ckpt_register_tensors(ckpt_ctx* c, const ckpt_tensor* t, uint32_t n)
                         (unsigned long long)c->pieces.size(), (unsigned long long)kMaxDirectPieces);
         for (size_t k = 0; k < c->pieces.size(); ++k) c->pieces[k].src += c->frags[pf[k]].ptr;
         split_small(c, small);
+        deal_chains(c);
     }
     const uint64_t nt = pl.n_tiles;
     std::vector<uint64_t> tile_src(nt);
@@ -1337,6 +1366,15 @@ ckpt_status ckpt_last_timing(ckpt_ctx* c, uint32_t which, ckpt_timing* out)
                     break;
                 }
                 ct.start = c0.start;
+            }
+            hsa_signal_t ends[2];
+            if (group_signals(c, r, g, ends) == 2) { // the other chain may end later
+                hsa_amd_profiling_async_copy_time_t c1;
+                if (hsa_amd_profiling_get_async_copy_time(ends[1], &c1) != HSA_STATUS_SUCCESS) {
+                    ok = false;
+                    break;
+                }
+                ct.end = std::max(ct.end, c1.end);
             }
             t_start = std::min<uint64_t>(t_start, ct.start);
             t_end = std::max<uint64_t>(t_end, ct.end);

@@ -49,26 +49,58 @@ ckpt_status issue_sums_copy(ckpt_ctx* c, SnapRec& r)
 }
 
 uint64_t issue_pieces(ckpt_ctx* c, RecRes* res, uint64_t g, uint8_t* dst, hsa_agent_t dst_agent,
-                      const hsa_signal_t* first_dep, hsa_amd_sdma_engine_id_t engine)
+                      const hsa_signal_t* first_dep, const hsa_amd_sdma_engine_id_t engine[2])
 {
     const uint64_t lo = group_lo(c, g);
     for (uint64_t k = c->gap_first[g]; k < c->gap_first[g + 1]; ++k)
         std::memset(dst + (c->gaps[k].off - lo), 0, c->gaps[k].n);
     const uint64_t p0 = c->piece_first[g], p1 = c->piece_first[g + 1];
-    const hsa_signal_t* dep = first_dep;
+    const hsa_signal_t* dep[2] = {first_dep, first_dep};
     for (uint64_t k = p0; k < p1; ++k) {
         const Piece& pc = c->pieces[k];
+        const int e = c->piece_chain[k];
         const hsa_signal_t* done = k + 1 == p1 ? &res->copied[g] : &res->piece_done[k];
         hsa_signal_store_screlease(*done, 1);
         if (hsa_amd_memory_async_copy_on_engine(dst + (pc.off - lo), dst_agent, (const void*)(uintptr_t)pc.src,
-                                                c->gpu_agent, pc.n, dep ? 1 : 0, dep, *done, engine,
+                                                c->gpu_agent, pc.n, dep[e] ? 1 : 0, dep[e], *done, engine[e],
                                                 true) != HSA_STATUS_SUCCESS) {
             hsa_signal_store_screlease(*done, 0);
             return k - p0;
         }
-        dep = done;
+        dep[e] = done;
     }
     return p1 - p0;
+}
+
+void wait_pieces(ckpt_ctx* c, RecRes* res, uint64_t g, uint64_t got)
+{
+    const uint64_t p0 = c->piece_first[g], p1 = c->piece_first[g + 1];
+    for (uint64_t k = p0; k < p0 + got; ++k) (void)poll_zero(k + 1 == p1 ? res->copied[g] : res->piece_done[k], 120);
+}
+
+int group_signals(const ckpt_ctx* c, const RecRes* res, uint64_t g, hsa_signal_t out[2])
+{
+    out[0] = res->copied[g];
+    if (c->direct ? c->other_last[g] == UINT64_MAX : !in_halves(c, g)) return 1;
+    out[1] = res->piece_done[c->direct ? c->other_last[g] : g];
+    return 2;
+}
+
+int issue_halves(ckpt_ctx* c, RecRes* res, uint64_t g, uint8_t* dst, hsa_agent_t dst_agent, const uint8_t* src,
+                 uint64_t n, const hsa_signal_t* dep)
+{
+    const uint64_t half = in_halves(c, g) ? round_up(n / 2, 4096) : n;
+    if (hsa_amd_memory_async_copy_on_engine(dst, dst_agent, src, c->gpu_agent, half, 1, dep, res->copied[g],
+                                            c->d2h_engine[g % c->n_d2h_engines], true) != HSA_STATUS_SUCCESS)
+        return 0;
+    if (half == n) return 1;
+    hsa_signal_store_screlease(res->piece_done[g], 1);
+    if (hsa_amd_memory_async_copy_on_engine(dst + half, dst_agent, src + half, c->gpu_agent, n - half, 1, dep,
+                                            res->piece_done[g], c->d2h_engine[(g + 1) % c->n_d2h_engines],
+                                            true) == HSA_STATUS_SUCCESS)
+        return 2;
+    hsa_signal_store_screlease(res->piece_done[g], 0);
+    return 1;
 }
 
 // Direct D2H (no snapshot staging): per group, the sums kernel reads the
@@ -134,11 +166,14 @@ ckpt_status issue_groups_direct(ckpt_ctx* c, SnapRec& r, hipStream_t after, uint
             continue;
         }
         const uint64_t want = c->piece_first[g + 1] - c->piece_first[g];
-        const uint64_t got = issue_pieces(c, res, g, himg + lo, host, &res->dep[g], eng);
+        const hsa_amd_sdma_engine_id_t engs[2] = {eng, c->d2h_engine[(g + 1) % c->n_d2h_engines]};
+        const uint64_t got = issue_pieces(c, res, g, himg + lo, host, &res->dep[g], engs);
         ckpt_status st = CKPT_OK;
+        hsa_signal_t ends[2];
+        const int n_ends = group_signals(c, res, g, ends);
         if (got == want)
-            st = dma(c, c->d_area_done + g, c->gpu_agent, &res->h_seq[g], host, 8, &res->copied[g], res->flagged[g],
-                     c->h2d_engine);
+            st = dma(c, c->d_area_done + g, c->gpu_agent, &res->h_seq[g], host, 8, ends, res->flagged[g],
+                     c->h2d_engine, n_ends);
         if (got != want || st) {
             // Let the issued pieces run (nothing else will release them),
             // wait until they have read the tensors, then count the group
@@ -146,8 +181,7 @@ ckpt_status issue_groups_direct(ckpt_ctx* c, SnapRec& r, hipStream_t after, uint
             // marked interrupted and never restored.
             hsa_signal_store_screlease(res->dep[g], 0);
             carried.handle = 0;
-            if (got && got < want) (void)poll_zero(res->piece_done[c->piece_first[g] + got - 1], 120);
-            if (got == want) (void)poll_zero(res->copied[g], 120);
+            wait_pieces(c, res, g, got);
             (void)hsa_memory_copy(c->d_area_done + g, &res->h_seq[g], 8);
             hsa_signal_store_screlease(res->copied[g], 0);
             hsa_signal_store_screlease(res->flagged[g], 0);
@@ -250,7 +284,6 @@ ckpt_status issue_groups(ckpt_ctx* c, SnapRec& r, hipStream_t after, uint64_t n_
         hsa_signal_store_screlease(res->copied[g], 1);
         hsa_signal_store_screlease(res->flagged[g], 1);
         r.groups_copied = (uint32_t)(g + 1);
-        const hsa_amd_sdma_engine_id_t eng = c->d2h_engine[g % c->n_d2h_engines];
         res->h_seq[g] = c->area_seq[area] + 1;
         if (r.bounce) { // the pump issues the copies once a ring slot is free
             {
@@ -263,7 +296,6 @@ ckpt_status issue_groups(ckpt_ctx* c, SnapRec& r, hipStream_t after, uint64_t n_
                 it.n = hi - lo;
                 it.area_done = c->d_area_done + area;
                 it.seq = &res->h_seq[g];
-                it.engine = eng;
                 it.buf = r.buf;
                 c->pump->issue_q.push_back(it);
             }
@@ -272,10 +304,15 @@ ckpt_status issue_groups(ckpt_ctx* c, SnapRec& r, hipStream_t after, uint64_t n_
             c->area_flag[area] = res->flagged[g];
             continue;
         }
-        st = dma(c, himg + lo, host, staging_of(c, g), c->gpu_agent, hi - lo, &res->dep[g0], res->copied[g], eng);
-        if (!st)
-            st = dma(c, c->d_area_done + area, c->gpu_agent, &res->h_seq[g], host, 8, &res->copied[g],
-                     res->flagged[g], c->h2d_engine);
+        hsa_signal_t ends[2];
+        const int n_ends = group_signals(c, res, g, ends);
+        const int got = issue_halves(c, res, g, himg + lo, host, staging_of(c, g), hi - lo, &res->dep[g0]);
+        const char* what = got == n_ends ? nullptr : "DMA of group %llu could not be issued";
+        if (got) // after what was issued
+            st = dma(c, c->d_area_done + area, c->gpu_agent, &res->h_seq[g], host, 8, ends, res->flagged[g],
+                     c->h2d_engine, n_ends);
+        else
+            st = fail(c, CKPT_EHIP, what, (unsigned long long)g);
         if (st) {
             // nothing will lower the signals of this group
             hsa_signal_store_screlease(res->copied[g], 0);
@@ -284,6 +321,7 @@ ckpt_status issue_groups(ckpt_ctx* c, SnapRec& r, hipStream_t after, uint64_t n_
         }
         ++c->area_seq[area];
         c->area_flag[area] = res->flagged[g];
+        if (what) return fail(c, CKPT_EHIP, what, (unsigned long long)g);
     }
     if (stop >= 0) {
         r.aborted = true; // interrupted offload: never committed (its pack timing stays readable)
