@@ -46,6 +46,12 @@ constexpr int kMaxEngines = 2;
 // Group copies of at least this many bytes are dealt to both engines in halves
 // (~57 GB/s together, ~55 alone); below, a second request costs more.
 constexpr uint64_t kSplitCopy = 8ull << 20;
+// The lead: 16 MiB keep the link busy for 290 us, in which the rest of a group
+// of 1 GiB is packed (330 us); groups of less than four leads gain nothing.
+// Snapshot to commit without / with: 239 MB 4394 / 4288 us, 1.5 GB 27520 /
+// 27190, 2.8 GB 50340 / 49870 (a lead of 4 MiB 4288 / 27356 / 50334, of 32
+// 4307 / 27130 / 49819).
+constexpr uint64_t kLead = 16ull << 20;
 constexpr uint32_t kDefaultHostThreads = 12; // bounce mode: host copy threads (measured: 8 do not keep up with the link)
 
 struct Frag {
@@ -77,6 +83,8 @@ struct RecRes {
     std::vector<hsa_signal_t> piece_done; // direct D2H, per piece but each group's last (whose copy
                                           // signals `copied`): the piece's copy finished;
                                           // else per group: the copy of its second half (issue_halves)
+    hsa_signal_t dep_lead{0};           // the first group's lead (lead_bytes) packed
+    int64_t* dep_lead_val = nullptr;
     hsa_signal_t dep_sums{0}, done{0};  // sums packed; sums copied (the last copy issued)
     int64_t* dep_sums_val = nullptr;
     uint64_t* h_seq = nullptr;          // pinned, per group: area use number, source of the area-done copy
@@ -461,6 +469,12 @@ inline bool in_halves(const ckpt_ctx* c, uint64_t g)
 {
     return c->n_d2h_engines > 1 && group_hi(c, g) - group_lo(c, g) >= kSplitCopy;
 }
+// Bytes of the first group that a launch of their own packs ahead of the rest
+// (0: none), whole tiles; full-image staging only.
+inline uint64_t lead_bytes(const ckpt_ctx* c)
+{
+    return !c->ring && !c->direct && !c->poison && group_hi(c, 0) >= 4 * kLead ? kLead : 0;
+}
 inline uint64_t tiles_lo(const ckpt_ctx* c, uint64_t g) { return group_lo(c, g) >> c->geo.tile_shift; }
 inline uint64_t tiles_hi(const ckpt_ctx* c, uint64_t g)
 {
@@ -520,10 +534,11 @@ uint64_t issue_pieces(ckpt_ctx* c, RecRes* res, uint64_t g, uint8_t* dst, hsa_ag
                       const hsa_signal_t* first_dep, const hsa_amd_sdma_engine_id_t engine[2]);
 // Copy group g, n bytes at src (device staging) to dst (pinned), after *dep:
 // its halves on the two engines, or in one request when it is small or there is
-// one engine.  Returns the requests issued: fewer than group_signals() counts
+// one engine; with lead > 0 its first `lead` bytes (after res->dep_lead) and the
+// rest instead of halves.  Returns the requests issued: fewer than group_signals() counts
 // means that one could not be (the signals of what was not issued are 0).
 int issue_halves(ckpt_ctx* c, RecRes* res, uint64_t g, uint8_t* dst, hsa_agent_t dst_agent, const uint8_t* src,
-                 uint64_t n, const hsa_signal_t* dep);
+                 uint64_t n, const hsa_signal_t* dep, uint64_t lead = 0);
 // Wait (bounded) until the first `got` pieces of group g have been copied.
 void wait_pieces(ckpt_ctx* c, RecRes* res, uint64_t g, uint64_t got);
 // The signals that reach 0 once group g's image copies have finished: `copied`,

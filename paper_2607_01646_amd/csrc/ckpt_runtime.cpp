@@ -324,6 +324,7 @@ void destroy_res(RecRes* r)
         if (s.handle) hsa_signal_destroy(s);
     for (auto s : r->piece_done)
         if (s.handle) hsa_signal_destroy(s);
+    if (r->dep_lead.handle) hsa_signal_destroy(r->dep_lead);
     if (r->dep_sums.handle) hsa_signal_destroy(r->dep_sums);
     if (r->done.handle) hsa_signal_destroy(r->done);
     if (r->h_seq) (void)hipHostFree(r->h_seq);
@@ -381,6 +382,7 @@ ckpt_status new_res(ckpt_ctx* c, RecRes** out)
     }
     if (st == CKPT_OK) st = make_event(c, &r->t0, true);
     if (st == CKPT_OK) st = make_event(c, &r->t_red, true);
+    if (st == CKPT_OK) st = gpu_only_signal(c, &r->dep_lead, &r->dep_lead_val);
     if (st == CKPT_OK) st = gpu_only_signal(c, &r->dep_sums, &r->dep_sums_val);
     if (st == CKPT_OK && hsa_signal_create(0, 0, nullptr, &r->done) != HSA_STATUS_SUCCESS) {
         r->done.handle = 0;

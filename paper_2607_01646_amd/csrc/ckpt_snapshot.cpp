@@ -87,11 +87,12 @@ int group_signals(const ckpt_ctx* c, const RecRes* res, uint64_t g, hsa_signal_t
 }
 
 int issue_halves(ckpt_ctx* c, RecRes* res, uint64_t g, uint8_t* dst, hsa_agent_t dst_agent, const uint8_t* src,
-                 uint64_t n, const hsa_signal_t* dep)
+                 uint64_t n, const hsa_signal_t* dep, uint64_t lead)
 {
-    const uint64_t half = in_halves(c, g) ? round_up(n / 2, 4096) : n;
-    if (hsa_amd_memory_async_copy_on_engine(dst, dst_agent, src, c->gpu_agent, half, 1, dep, res->copied[g],
-                                            c->d2h_engine[g % c->n_d2h_engines], true) != HSA_STATUS_SUCCESS)
+    const uint64_t half = lead ? lead : in_halves(c, g) ? round_up(n / 2, 4096) : n;
+    if (hsa_amd_memory_async_copy_on_engine(dst, dst_agent, src, c->gpu_agent, half, 1, lead ? &res->dep_lead : dep,
+                                            res->copied[g], c->d2h_engine[g % c->n_d2h_engines],
+                                            true) != HSA_STATUS_SUCCESS)
         return 0;
     if (half == n) return 1;
     hsa_signal_store_screlease(res->piece_done[g], 1);
@@ -232,6 +233,12 @@ ckpt_status issue_groups(ckpt_ctx* c, SnapRec& r, hipStream_t after, uint64_t n_
     // pack instead.
     const bool carry = !c->ring;
     int64_t* pending = nullptr; // the previous launch's release, carried by the next launch
+    // The first group's first bytes are packed by a launch of their own, whose
+    // release the group's launch carries, so that their copy starts after a few
+    // us instead of the whole group's pack.  (Timed snapshots time one launch
+    // per group.)
+    const uint64_t lead = !r.timed && !r.bounce && n_copy && c->n_d2h_engines > 1 ? lead_bytes(c) : 0;
+    const uint64_t lead_tiles = lead >> c->geo.tile_shift;
     for (uint64_t g = 0; g < c->n_groups; ++g) {
         const uint64_t lo = group_lo(c, g), hi = group_hi(c, g);
         const uint64_t area = area_of(c, g);
@@ -258,7 +265,14 @@ ckpt_status issue_groups(ckpt_ctx* c, SnapRec& r, hipStream_t after, uint64_t n_
                 hipError_t e = launch_fill16(staging_of(c, g0), group_hi(c, g1 - 1) - lo, w, c->s_pack);
                 if (e != hipSuccess) return fail(c, CKPT_EHIP, "canary fill failed: %s", hipGetErrorString(e));
             }
-            hipError_t e = launch_pack(c->d_frags, c->d_tile_src, c->geo, tiles_lo(c, g0),
+            if (lead && g0 == 0) {
+                hipError_t e = launch_pack(c->d_frags, c->d_tile_src, c->geo, 0, lead_tiles, staging_of(c, 0), 0,
+                                           c->d_partials, c->grid_cap, c->s_pack);
+                if (e != hipSuccess) return fail(c, CKPT_EHIP, "pack launch failed: %s", hipGetErrorString(e));
+                hsa_signal_store_screlease(res->dep_lead, 1); // before the launch that clears it
+                pending = res->dep_lead_val;
+            }
+            hipError_t e = launch_pack(c->d_frags, c->d_tile_src, c->geo, tiles_lo(c, g0) + (g0 ? 0 : lead_tiles),
                                        tiles_hi(c, g1 - 1), staging_of(c, g0), lo, c->d_partials, c->grid_cap,
                                        c->s_pack, r.timed && (r.per_launch || j == 0) ? res->k0[j] : nullptr,
                                        r.timed && (r.per_launch || j == 0) ? res->k1[j] : nullptr,
@@ -306,7 +320,8 @@ ckpt_status issue_groups(ckpt_ctx* c, SnapRec& r, hipStream_t after, uint64_t n_
         }
         hsa_signal_t ends[2];
         const int n_ends = group_signals(c, res, g, ends);
-        const int got = issue_halves(c, res, g, himg + lo, host, staging_of(c, g), hi - lo, &res->dep[g0]);
+        const int got = issue_halves(c, res, g, himg + lo, host, staging_of(c, g), hi - lo, &res->dep[g0],
+                                     g ? 0 : lead);
         const char* what = got == n_ends ? nullptr : "DMA of group %llu could not be issued";
         if (got) // after what was issued
             st = dma(c, c->d_area_done + area, c->gpu_agent, &res->h_seq[g], host, 8, ends, res->flagged[g],

@@ -92,3 +92,35 @@ def test_direct_pieces_around_the_kernel_size(align, shift):
         ck, _ = snapshot_and_check(views, [host_bytes(v) for v in views], chunk, align, group=group, direct=True)
         ck.close()
         assert np.array_equal(host_bytes(flat), before)
+
+
+@pytest.mark.parametrize("size,chunk,group,launch", [
+    ((64 << 20) - 16, 1 << 20, 0, 0),                 # just under a led group
+    (64 << 20, 1 << 20, 0, 0),                        # the lead and the rest, in one group
+    ((64 << 20) + 777, 3 * 4096, 0, 0),               # 4 KiB tiles; the lead ends inside a chunk
+    (150 << 20, 5 << 20, 70 << 20, 0),                # the first of three groups is led
+    (200 << 20, 1 << 20, 64 << 20, 128 << 20),        # two groups per launch
+    (30 << 20, 1 << 20, 8 << 20, 0),                  # halves without a lead, the last group smaller
+])
+def test_led_and_halved_groups(size, chunk, group, launch):
+    """Full staging: the first group's lead, copies in two halves, and the
+    same after a snapshot that was interrupted behind its first group."""
+    tensors, host = random_byte_fragments([size // 7, size - size // 7 - 5, 5], seed=size)
+    ck, _ = snapshot_and_check(tensors, host, chunk, 16, group=group, launch=launch)
+    for step in range(3):
+        before = [host_bytes(t) for t in tensors]
+        if step == 1:
+            P.ckpt_debug_interrupt_next(ck.ctx, 1)
+        s = ck.snapshot(step=step)
+        ck.wait_captured(s)
+        garbage_fill(tensors, 17 + step)  # behind the gate
+        torch.cuda.synchronize()
+        if step == 1:
+            assert ck.state(s) == P.CKPT_SNAP_ABORTED
+            continue
+        ck.wait_committed(s)
+        img, sums = ck.host_image(s)
+        want, _, _ = O.pack(before, 16, chunk)
+        assert np.array_equal(img, want)
+        assert np.array_equal(sums, O.chunk_sums(want, 0, want.size, chunk))
+    ck.close()
