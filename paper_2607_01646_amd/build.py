@@ -1,15 +1,18 @@
-"""Build libckpt.so in-tree for gfx950 with hipcc.
+"""Build libckpt.so in-tree for gfx950 with hipcc, and the Python module that
+reads tensor lists for it.
 
     python -m paper_2607_01646_amd.build
 """
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libckpt.so")
+PY_EXT = os.path.join(PKG, "_ckpt_py.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
@@ -37,8 +40,28 @@ def _run(cmd, verbose):
         print(out)
 
 
+def build_py_ext(verbose=False):
+    """Compile _ckpt_py.so (csrc/ckpt_py.cpp) against this Python and torch."""
+    import torch
+    from torch.utils import cpp_extension
+
+    cmd = [HOST_CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-I", sysconfig.get_paths()["include"]]
+    for d in cpp_extension.include_paths():
+        cmd += ["-isystem", d]
+    tmp = PY_EXT + ".tmp"
+    cmd += [os.path.join(CSRC, "ckpt_py.cpp"), "-o", tmp]
+    for d in cpp_extension.library_paths():
+        cmd += ["-L", d]
+    _run(cmd + ["-lc10", "-ltorch_cpu", "-ltorch", "-ltorch_python"], verbose)
+    os.replace(tmp, PY_EXT)
+    return PY_EXT
+
+
 def build(verbose=False):
-    """Compile the kernels and the runtime and link libckpt.so (always rebuilds)."""
+    """Compile the kernels and the runtime, link libckpt.so, and compile the
+    Python module beside it (always rebuilds)."""
     obj_dir = os.path.join(PKG, "_build")
     os.makedirs(obj_dir, exist_ok=True)
     k_obj = os.path.join(obj_dir, "ckpt_kernels.o")
@@ -53,6 +76,7 @@ def build(verbose=False):
     _run([HIPCC, "--offload-arch=" + ARCH, "-shared", "-fPIC", k_obj] + host_objs + ["-o", tmp, "-L/opt/rocm/lib",
           "-lhsa-runtime64", "-lpthread"], verbose)
     os.replace(tmp, LIB)
+    build_py_ext(verbose)
     return LIB
 
 

@@ -136,6 +136,23 @@ def lib():
     return _lib
 
 
+_pack = None
+
+
+def _native_pack():
+    """(_ckpt_py.pack_noalloc, address of ckpt_pack_noalloc)."""
+    global _pack
+    if _pack is None:
+        fn = C.cast(lib().ckpt_pack_noalloc, C.c_void_p).value
+        try:
+            from . import _ckpt_py
+        except ImportError as e:
+            raise RuntimeError("_ckpt_py.so is not built for this Python; run "
+                               "`python -c 'import __graft_entry__ as g; g.build()'`") from e
+        _pack = (_ckpt_py.pack_noalloc, fn)
+    return _pack
+
+
 def _check(ctx, rc):
     if rc != CKPT_OK:
         raise CkptError(rc, (lib().ckpt_last_error(ctx) or b"").decode())
@@ -460,6 +477,14 @@ def ckpt_pack_noalloc(tensors, image, sums, chunk_bytes=0, align_bytes=0, stream
     (image_bytes, n_chunks).  Asynchronous like a kernel launch."""
     if device is None:
         device = torch.cuda.current_device()
+    s = _stream(stream)
+    pack, fn = _native_pack()
+    got = pack(fn, tensors, image, sums, chunk_bytes, align_bytes, device, s.value or 0)
+    if got is not None:
+        if got[0] != CKPT_OK:
+            raise CkptError(got[0], (lib().ckpt_last_error(None) or b"").decode())
+        return got[1], got[2]
+    # Arguments that are not plain tensors and numbers, and those refused here.
     n = len(tensors)
     arr = (ckpt_tensor * max(n, 1))()
     for i, t in enumerate(tensors):
@@ -471,7 +496,7 @@ def ckpt_pack_noalloc(tensors, image, sums, chunk_bytes=0, align_bytes=0, stream
     ib, nc = C.c_uint64(), C.c_uint64()
     rc = lib().ckpt_pack_noalloc(arr, n, chunk_bytes, align_bytes, device, C.c_void_p(image.data_ptr()),
                                  image.numel() * image.element_size(), C.c_void_p(sums.data_ptr()),
-                                 sums.numel() * sums.element_size() // 8, _stream(stream), C.byref(ib), C.byref(nc))
+                                 sums.numel() * sums.element_size() // 8, s, C.byref(ib), C.byref(nc))
     if rc != CKPT_OK:
         raise CkptError(rc, (lib().ckpt_last_error(None) or b"").decode())
     return ib.value, nc.value

@@ -85,3 +85,33 @@ def test_allocation_free_paths(n, total, chunk, align):
     assert np.array_equal(got[:want.size], want) and np.all(got[want.size:] == 0xC3)
     assert np.array_equal(sums.cpu().numpy().view(np.uint64)[:nc], O.chunk_sums(want, 0, want.size, chunk))
     assert int(sums[nc]) == -1
+
+
+def test_binding_reads_tensors_alike_on_both_paths():
+    """The native reading of plain tensors and the Python one of everything
+    else: the same results, and the same errors for what is refused."""
+    class Sub(torch.Tensor):
+        pass
+
+    base = [torch.arange(5000, device="cuda", dtype=torch.int32), torch.empty(0, device="cuda"),
+            torch.rand(3, 1001, device="cuda", dtype=torch.float64), torch.rand(777, device="cuda").to(torch.bfloat16)]
+    want, _, nc = O.pack([host_bytes(t) for t in base], 256, 65536)
+    image = torch.zeros(want.size, dtype=torch.uint8, device="cuda")
+    sums = torch.zeros(nc, dtype=torch.int64, device="cuda")
+    for tensors in (base, tuple(base), [base[0], base[1], torch.nn.Parameter(base[2]), base[3].detach()],
+                    [t.as_subclass(Sub) for t in base]):
+        for chunk in (65536, np.int64(65536)):
+            image.zero_()
+            sums.zero_()
+            assert P.ckpt_pack_noalloc(tensors, image, sums, chunk_bytes=chunk) == (want.size, nc)
+            assert np.array_equal(image.cpu().numpy(), want)
+            assert np.array_equal(sums.cpu().numpy().view(np.uint64), O.chunk_sums(want, 0, want.size, 65536))
+    with pytest.raises(ValueError, match="contiguous"):
+        P.ckpt_pack_noalloc([base[2].t()], image, sums)
+    with pytest.raises(ValueError, match="fragment 1 is not a device tensor"):
+        P.ckpt_pack_noalloc([base[0], base[0].cpu()], image, sums)
+    for bad in (dict(tensors=[]), dict(tensors=base, chunk_bytes=100), dict(tensors=base, image=image[:-16]),
+                dict(tensors=base, image=torch.zeros(want.size, dtype=torch.uint8))):
+        with pytest.raises(P.CkptError) as e:
+            P.ckpt_pack_noalloc(**dict(dict(image=image, sums=sums, chunk_bytes=65536), **bad))
+        assert e.value.code == P.CKPT_EINVAL and len(str(e.value)) > 20
