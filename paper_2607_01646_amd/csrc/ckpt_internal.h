@@ -45,7 +45,7 @@ __host__ __device__ inline uint32_t tile_first(uint64_t e) { return (uint32_t)e;
 __host__ __device__ inline uint32_t tile_last(uint64_t e) { return (uint32_t)e + (uint32_t)((e & ~kTileSlow) >> 32); }
 
 // Tiles are at most 1 << kMaxTileShift = 8 KiB: each wave's slice of a tile
-// is at most one batch of two 16-byte vectors per lane.
+// is at most one batch of one 16-byte vector per lane.
 constexpr uint32_t kMaxTileShift = 13;
 
 // The tile kernels.  Each covers tiles [t_lo, t_hi) and writes tile t's

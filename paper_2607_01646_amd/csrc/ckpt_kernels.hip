@@ -666,14 +666,53 @@ __global__ __launch_bounds__(kSmallBlock) void pack_small_kernel(FragArgs b, uin
     if (threadIdx.x == 0) out[blockIdx.x] = acc;
 }
 
-// One lane per tile: binary search for the first fragment whose padded span
-// [off, end) ends past the tile's first byte, and for the first one ending
-// past its last byte (end[] never decreases; empty fragments have empty spans).
+// First fragment whose padded span ends past x, by one wave: 64 ends a step, so
+// that 4096 fragments take two dependent loads and not twelve.  end[] never
+// decreases; n - 1 when no span ends past x.
+__device__ __forceinline__ uint32_t find_end_wave(const FragDev* frags, uint32_t n, uint64_t x)
+{
+    const uint32_t lane = threadIdx.x & 63;
+    uint32_t lo = 0, m = n; // the answer lies in [lo, lo + m)
+    while (m > 1) {
+        const uint32_t step = (m + 63) / 64, k = lane * step + step - 1; // the last of the lane's run
+        const uint32_t skip = step * (uint32_t)__popcll(__ballot(k < m && frags[lo + k].end <= x));
+        lo += skip;
+        m = step < m - skip ? step : m - skip;
+    }
+    return lo < n ? lo : n - 1;
+}
+
+// One lane per tile: the first fragment whose padded span [off, end) ends past
+// the tile's first byte, and the first one ending past its last byte (empty
+// fragments have empty spans).  Bound by the chain of dependent loads: two
+// waves find the fragments at the ends of the workgroup's tiles, the ends
+// between them go to LDS, and the lanes search there (memory is the fallback
+// when more than kTableFrags lie in the workgroup's 2 MiB).
+constexpr uint32_t kTableFrags = 1024;
 __global__ __launch_bounds__(256) void tile_table_kernel(const FragDev* frags, uint32_t n, Geometry g, uint64_t t_lo,
                                                          uint64_t t_hi, uint64_t* tile_src)
 {
-    const uint64_t t = t_lo + 256ull * blockIdx.x + threadIdx.x;
-    if (t >= t_hi) return;
+    __shared__ uint64_t s_end[kTableFrags];
+    __shared__ uint32_t s_f[2];
+    const uint32_t tid = threadIdx.x;
+    const uint64_t b_lo = t_lo + 256ull * blockIdx.x, b_hi = b_lo + 256 < t_hi ? b_lo + 256 : t_hi;
+    if (tid < 128) { // waves 0 and 1
+        uint64_t x = b_lo << g.tile_shift;
+        if (tid >= 64) {
+            x = b_hi << g.tile_shift;
+            x = (x < g.image_bytes ? x : g.image_bytes) - 1;
+        }
+        const uint32_t f = find_end_wave(frags, n, x);
+        if ((tid & 63) == 0) s_f[tid >> 6] = f;
+    }
+    __syncthreads();
+    const uint32_t f0 = s_f[0], f1 = s_f[1];
+    const bool in_lds = f1 - f0 < kTableFrags;
+    if (in_lds)
+        for (uint32_t k = tid; k <= f1 - f0; k += 256) s_end[k] = frags[f0 + k].end;
+    __syncthreads();
+    const uint64_t t = b_lo + tid;
+    if (t >= b_hi) return;
     const uint64_t x0 = t << g.tile_shift;
     uint64_t x1 = x0 + (1ull << g.tile_shift);
     if (x1 > g.image_bytes) x1 = g.image_bytes;
@@ -681,10 +720,10 @@ __global__ __launch_bounds__(256) void tile_table_kernel(const FragDev* frags, u
     const uint64_t xs[2] = {x0, x1 - 1};
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-        uint32_t lo = 0, hi = n - 1; // the answer lies in [lo, hi]; n - 1 when no span ends past x
+        uint32_t lo = k ? r[0] : f0, hi = f1; // the answer lies in [lo, hi]
         while (lo < hi) {
             const uint32_t mid = lo + ((hi - lo) >> 1);
-            if (frags[mid].end > xs[k]) hi = mid;
+            if ((in_lds ? s_end[mid - f0] : frags[mid].end) > xs[k]) hi = mid;
             else lo = mid + 1;
         }
         r[k] = lo;

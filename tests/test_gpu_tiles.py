@@ -65,6 +65,9 @@ def test_unaligned_fragments_without_allocation(shift):
     (250, 10 << 20, 16 * 4099, 16),        # 16-byte tiles: several scratch groups, two batches
     (20, 10 << 20, 16 * 4099, 16),         # ... from the arguments
     (700, 5 << 20, 1 << 20, 4096),         # three batches
+    (4097, 48 << 20, 1 << 20, 256),        # the tile table's wave search takes three steps
+    (3000, 1 << 20, 1 << 20, 16),          # more fragments than the table's LDS holds
+    (65536, 4 << 20, 1 << 20, 16),         # the most fragments
 ])
 def test_allocation_free_paths(n, total, chunk, align):
     """Each way the allocation-free pack takes by size and fragment count."""
