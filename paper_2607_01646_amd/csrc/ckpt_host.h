@@ -364,6 +364,7 @@ struct ckpt_ctx {
     uint64_t* d_tile_src = nullptr;           // per tile: tile_entry()
     uint8_t* d_staging = nullptr;
     unsigned long long* d_partials = nullptr; // [2][n_tiles] tile partial sums: pack, check
+    uint32_t* d_ticket = nullptr;             // launch_pack_chunks' (behind the counters)
     uint64_t* d_area_done = nullptr;          // per staging area (direct D2H: per group): number of
                                               // finished copies out of it
 

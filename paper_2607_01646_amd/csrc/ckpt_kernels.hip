@@ -503,8 +503,11 @@ __global__ __launch_bounds__(kReduceBlock) void chunk_reduce_kernel(ReduceArgs r
 
 // The pack of one workgroup per chunk: its tiles one after another, and the
 // chunk's sum to sums_out, so that no reduce has to follow.  For images small
-// enough that their time is launches and not bytes.
-__global__ __launch_bounds__(kBlock) void pack_chunks_kernel(Args a, unsigned long long* sums_out)
+// enough that their time is launches and not bytes.  With a ticket (0 between
+// launches) the workgroup that ends last stores the release itself; every
+// workgroup then needs a system-scope release of its own writes, a write-back
+// of its XCD's L2, so this is for few workgroups (kReleaseChunks).
+__global__ __launch_bounds__(kBlock) void pack_chunks_kernel(Args a, unsigned long long* sums_out, uint32_t* ticket)
 {
     __shared__ uint64_t s_off[kLdsFrags];
     __shared__ unsigned long long s_red[kBlock / 64];
@@ -514,6 +517,17 @@ __global__ __launch_bounds__(kBlock) void pack_chunks_kernel(Args a, unsigned lo
     for (uint64_t t = t0; t < t1; ++t) acc += move_tile<PACK, kBlock, kUnroll, true, true>(a, t, s_off);
     acc = block_sum<kBlock>(acc, s_red);
     if (threadIdx.x == 0) sums_out[blockIdx.x] = acc;
+    if (ticket) {
+        // The compiler does not count st_stream's stores as outstanding.
+        asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+        __threadfence_system();
+        __syncthreads();
+        if (threadIdx.x == 0 &&
+            __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1) {
+            __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(a.release, (int64_t)0, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
 }
 
 // With timing events, the launch records them around the dispatch itself
@@ -833,10 +847,11 @@ hipError_t launch_pack(const FragDev* frags, const uint64_t* tile_src,
 }
 
 hipError_t launch_pack_chunks(const FragDev* frags, const uint64_t* tile_src, const Geometry& g, uint8_t* dst,
-                              unsigned long long* sums_out, hipStream_t s)
+                              unsigned long long* sums_out, hipStream_t s, int64_t* release, uint32_t* ticket)
 {
-    Args a{frags, tile_src, g, 0, g.n_tiles, dst, 0, nullptr, nullptr};
-    hipLaunchKernelGGL(pack_chunks_kernel, dim3((uint32_t)g.n_chunks), dim3(kBlock), 0, s, a, sums_out);
+    if (!release != !ticket) return hipErrorInvalidValue;
+    Args a{frags, tile_src, g, 0, g.n_tiles, dst, 0, nullptr, release};
+    hipLaunchKernelGGL(pack_chunks_kernel, dim3((uint32_t)g.n_chunks), dim3(kBlock), 0, s, a, sums_out, ticket);
     return hipGetLastError();
 }
 

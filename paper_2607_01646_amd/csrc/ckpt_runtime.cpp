@@ -929,7 +929,7 @@ ckpt_status ckpt_register_tensors(ckpt_ctx* c, const ckpt_tensor* t, uint32_t n)
     ALLOC(c->d_frags, n * sizeof(FragDev));
     ALLOC(c->d_tile_src, nt * 8);
     ALLOC(c->d_partials, 2 * nt * 8);
-    ALLOC(c->d_area_done, n_areas * 8);
+    ALLOC(c->d_area_done, n_areas * 8 + 8); // and the ticket of launch_pack_chunks
     if (!small.empty()) ALLOC(c->d_small, small.size() * sizeof(Piece));
     if (!c->direct) ALLOC(c->d_staging, c->ring ? c->n_slots * c->G * c->C : c->I);
 #undef ALLOC
@@ -937,7 +937,8 @@ ckpt_status ckpt_register_tensors(ckpt_ctx* c, const ckpt_tensor* t, uint32_t n)
     if (!small.empty())
         HIPCHK(c, hipMemcpy(c->d_small, small.data(), small.size() * sizeof(Piece), hipMemcpyHostToDevice));
     HIPCHK(c, hipMemcpy(c->d_tile_src, tile_src.data(), nt * 8, hipMemcpyHostToDevice));
-    HIPCHK(c, hipMemset(c->d_area_done, 0, n_areas * 8));
+    HIPCHK(c, hipMemset(c->d_area_done, 0, n_areas * 8 + 8));
+    c->d_ticket = (uint32_t*)(c->d_area_done + n_areas);
     c->area_seq.assign(n_areas, 0);
     c->area_flag.assign(n_areas, hsa_signal_t{0});
     if (c->bounce) {

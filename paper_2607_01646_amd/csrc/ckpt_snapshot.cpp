@@ -374,9 +374,16 @@ ckpt_status issue_in_kernel(ckpt_ctx* c, SnapRec& r, hipStream_t after)
     unsigned long long* sums = (unsigned long long*)c->h_sums[r.buf];
     hipError_t e;
     if (c->C <= kSmallSpan) {
-        e = launch_pack_chunks(c->d_frags, c->d_tile_src, c->geo, c->h_img[r.buf], sums, s);
+        const bool fused = c->n_chunks <= kReleaseChunks;
+        e = launch_pack_chunks(c->d_frags, c->d_tile_src, c->geo, c->h_img[r.buf], sums, s,
+                               fused ? res->dep_sums_val : nullptr, fused ? c->d_ticket : nullptr);
         if (e != hipSuccess) return fail(c, CKPT_EHIP, "pack launch failed: %s", hipGetErrorString(e));
-        HIPCHK(c, hipEventRecord(res->captured[0], s));
+        e = hipEventRecord(res->captured[0], s);
+        if (e != hipSuccess) {
+            (void)hipStreamSynchronize(s); // the kernel's release comes before the signal is used again
+            return fail(c, CKPT_EHIP, "event record failed: %s", hipGetErrorString(e));
+        }
+        if (fused) return CKPT_OK;
     } else {
         e = launch_pack(c->d_frags, c->d_tile_src, c->geo, 0, c->geo.n_tiles, c->h_img[r.buf], 0, c->d_partials,
                         std::min(c->grid_cap, kHostPackGrid), s);

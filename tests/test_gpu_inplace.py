@@ -49,6 +49,9 @@ def test_host_changes_between_calls_are_seen(tiles, mode):
     (1, 65536), (65536, 65536), (100_000, 16), (1_000_000, 48), (1 << 20, 4096), (1 << 20, 65536 + 16),
     (2 << 20, 65536), ((2 << 20) + 1, 65536), (2 << 20, 1 << 20),  # about the largest staged image
     (16 << 20, 65536), ((16 << 20) - 5, 1 << 20), ((16 << 20) + 1, 1 << 20),  # ... and direct one
+    (64 * 4096, 4096),                       # the most chunks whose pack releases the commit itself
+    (64 * 4096 + 16, 4096),                  # one more
+    (64 * 65536, 65536),
 ])
 def test_small_images_written_by_the_kernel(size, chunk, direct):
     """Images on both sides of the sizes that the pack writes straight into
