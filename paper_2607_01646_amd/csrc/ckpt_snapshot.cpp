@@ -148,6 +148,7 @@ ckpt_status issue_groups_direct(ckpt_ctx* c, SnapRec& r, hipStream_t after, uint
         const hsa_amd_sdma_engine_id_t eng = c->d2h_engine[g % c->n_d2h_engines];
         res->h_seq[g] = c->area_seq[g] + 1;
         ++c->area_seq[g];
+        c->area_flag[g] = res->flagged[g];
         if (r.bounce) { // the pump issues the pieces once a ring slot is free
             {
                 std::lock_guard<std::mutex> l(c->pump->m);
@@ -329,7 +330,12 @@ ckpt_status issue_groups(ckpt_ctx* c, SnapRec& r, hipStream_t after, uint64_t n_
         else
             st = fail(c, CKPT_EHIP, what, (unsigned long long)g);
         if (st) {
-            // nothing will lower the signals of this group
+            // No counter will say when the requests issued have finished: let
+            // them run (nothing else will release them) and wait, so that no
+            // later snapshot writes this image beside them.
+            hsa_signal_store_screlease(res->dep[g0], 0);
+            carried.handle = 0;
+            for (int k = 0; k < got; ++k) (void)poll_zero(ends[k], 120);
             hsa_signal_store_screlease(res->copied[g], 0);
             hsa_signal_store_screlease(res->flagged[g], 0);
             return st;
@@ -371,6 +377,11 @@ ckpt_status issue_in_kernel(ckpt_ctx* c, SnapRec& r, hipStream_t after)
     hipStream_t s = c->s_pack;
     HIPCHK(c, hipEventRecord(c->ev_trigger, after));
     HIPCHK(c, hipStreamWaitEvent(s, c->ev_trigger, 0));
+    // The kernels write where the copies of an interrupted snapshot may still
+    // be landing: it never commits, so its image is picked again at once.  The
+    // image's one group has one counter, which those copies bump when done.
+    if (c->area_seq[0] && hsa_signal_load_scacquire(c->area_flag[0]) != 0)
+        HIPCHK(c, hipStreamWaitValue64(s, c->d_area_done, c->area_seq[0], hipStreamWaitValueGte, ~0ull));
     unsigned long long* sums = (unsigned long long*)c->h_sums[r.buf];
     hipError_t e;
     if (c->C <= kSmallSpan) {

@@ -78,6 +78,32 @@ def test_small_images_written_by_the_kernel(size, chunk, direct):
     ck.close()
 
 
+@pytest.mark.parametrize("size,chunk,direct", [(2 << 20, 65536, False), (2 << 20, 1 << 20, False),
+                                               (2 << 20, 65536, True), (16 << 20, 65536, True),
+                                               (16 << 20, 1 << 20, True)])
+def test_small_image_behind_an_interrupted_copy(size, chunk, direct):
+    """A small image written by the kernel right after a snapshot that was
+    interrupted once its copies were issued: the same host image, which must
+    hold the new bytes whenever those copies land."""
+    tensors, host = random_byte_fragments([size // 8] * 8, seed=size)
+    ck, _ = snapshot_and_check(tensors, host, chunk, 16, direct=direct)
+    for k in range(8):
+        P.ckpt_debug_interrupt_next(ck.ctx, 1)
+        s = ck.snapshot(step=2 * k)
+        if not direct:  # there the gate waits for the copies themselves
+            ck.wait_captured(s)
+        garbage_fill(tensors, 40 + k)
+        s2 = ck.snapshot(step=2 * k + 1)
+        ck.wait_committed(s2)
+        assert ck.state(s) == P.CKPT_SNAP_ABORTED
+        torch.cuda.synchronize()
+        img, sums = ck.host_image(s2)
+        assert np.all(img == 40 + k)
+        assert np.array_equal(sums, O.chunk_sums(img, 0, img.size, chunk))
+        assert ck.verify(s2) == []
+    ck.close()
+
+
 @pytest.mark.parametrize("align,shift", [(16, 1), (256, 0), (4096, 6)])
 def test_direct_pieces_around_the_kernel_size(align, shift):
     """Direct D2H over several groups: pieces that the kernel copies and
