@@ -101,6 +101,7 @@ def lib():
             "ckpt_last_timing": ([vp, u32, P(ckpt_timing)], i32),
             "ckpt_plan": ([P(u64), u32, u64, u32, P(u64), P(u64), P(u64)], i32),
             "ckpt_debug_tile_plan": ([P(u64), u32, u64, u32, P(u64), P(u64), P(u32), P(u32)], i32),
+            "ckpt_debug_copy_plan": ([u64, u32, u32, P(u64), P(u32)], i32),
             "ckpt_debug_direct_plan": ([P(u64), u32, u64, u32, u64, P(u64), P(u64), P(u64), P(u64), P(u64)], i32),
             "ckpt_last_error": ([vp], C.c_char_p),
             "ckpt_image_file": ([vp, C.c_char_p, u32], i32),
@@ -353,6 +354,14 @@ def ckpt_debug_tile_plan(nbytes, chunk_bytes=0, align_bytes=0):
     _check(None, lib().ckpt_debug_tile_plan(_u64p(nb), nb.size, chunk_bytes, align_bytes, C.byref(tb),
                                             C.byref(nt), _u32p(tf), _u32p(tl)))
     return tb.value, tf, tl
+
+
+def ckpt_debug_copy_plan(group_bytes, engines=2, led=False):
+    """[(first byte, bytes, engine)] of the requests that copy one staged
+    chunk group."""
+    spans, n = (C.c_uint64 * 9)(), C.c_uint32()
+    _check(None, lib().ckpt_debug_copy_plan(group_bytes, engines, int(led), spans, C.byref(n)))
+    return [tuple(spans[3 * k:3 * k + 3]) for k in range(n.value)]
 
 
 def ckpt_debug_direct_plan(nbytes, chunk_bytes=0, align_bytes=0, group_bytes=0):

@@ -43,15 +43,36 @@ constexpr uint64_t kDefaultLaunch = 0; // full-image staging: bytes per pack lau
 constexpr uint32_t kMaxMeta = 1u << 20;
 constexpr uint32_t kDefaultGrid = 0x7fffffff; // one workgroup per tile unless capped
 constexpr int kMaxEngines = 2;
-// Group copies of at least this many bytes are dealt to both engines in halves
-// (~57 GB/s together, ~55 alone); below, a second request costs more.
+// Group copies of at least this many bytes are dealt to both engines in halves.
+// What an engine alone moves depends on the machine (29 to 57 GB/s seen, and
+// not the same for the two), both together fill the link on each; below, a
+// second request costs more than it gives.
 constexpr uint64_t kSplitCopy = 8ull << 20;
 // The lead: 16 MiB keep the link busy for 290 us, in which the rest of a group
 // of 1 GiB is packed (330 us); groups of less than four leads gain nothing.
-// Snapshot to commit without / with: 239 MB 4394 / 4288 us, 1.5 GB 27520 /
-// 27190, 2.8 GB 50340 / 49870 (a lead of 4 MiB 4288 / 27356 / 50334, of 32
-// 4307 / 27130 / 49819).
+// It is part of its engine's half, so that each engine still moves half of
+// the group.  Snapshot to commit without / with it, where each engine alone
+// fills the link: 65 MiB 1336 / 1322 us, 120 MiB 2362 / 2329, 239 MB 4389 /
+// 4284, 1.5 GB 26744 / 26410, 2.8 GB 49514 / 49133.  (With all of the group
+// behind the lead on the other engine 239 MB took 4288 us there, and 7710
+// where that engine alone moves 29 GB/s.)
 constexpr uint64_t kLead = 16ull << 20;
+// The requests of a staged group's copy of n bytes, in the order in which
+// they are issued: the lead if any, the (rest of the) first half on the
+// group's first engine (0), the second half on its other one.  Returns how many.
+struct CopySpan {
+    uint64_t lo, n;
+    int engine;
+};
+inline int copy_spans(uint64_t n, int engines, uint64_t lead, CopySpan out[3])
+{
+    const uint64_t half = engines > 1 && n >= kSplitCopy ? ((n / 2 + 4095) & ~4095ull) : n;
+    int k = 0;
+    if (lead) out[k++] = CopySpan{0, lead, 0};
+    out[k++] = CopySpan{lead, half - lead, 0};
+    if (half < n) out[k++] = CopySpan{half, n - half, 1};
+    return k;
+}
 constexpr uint32_t kDefaultHostThreads = 12; // bounce mode: host copy threads (measured: 8 do not keep up with the link)
 
 struct Frag {
@@ -84,6 +105,7 @@ struct RecRes {
                                           // signals `copied`): the piece's copy finished;
                                           // else per group: the copy of its second half (issue_halves)
     hsa_signal_t dep_lead{0};           // the first group's lead (lead_bytes) packed
+    hsa_signal_t lead_done{0};          // ... and copied
     int64_t* dep_lead_val = nullptr;
     hsa_signal_t dep_sums{0}, done{0};  // sums packed; sums copied (the last copy issued)
     int64_t* dep_sums_val = nullptr;
@@ -535,9 +557,10 @@ uint64_t issue_pieces(ckpt_ctx* c, RecRes* res, uint64_t g, uint8_t* dst, hsa_ag
                       const hsa_signal_t* first_dep, const hsa_amd_sdma_engine_id_t engine[2]);
 // Copy group g, n bytes at src (device staging) to dst (pinned), after *dep:
 // its halves on the two engines, or in one request when it is small or there is
-// one engine; with lead > 0 its first `lead` bytes (after res->dep_lead) and the
-// rest instead of halves.  Returns the requests issued: fewer than group_signals() counts
-// means that one could not be (the signals of what was not issued are 0).
+// one engine; with lead > 0 (two engines, less than a half) the first `lead`
+// bytes of the first half go ahead, after res->dep_lead.  Returns the signals
+// of group_signals() that will be lowered: fewer means that a request could not
+// be issued (the signals of what was not issued are 0).
 int issue_halves(ckpt_ctx* c, RecRes* res, uint64_t g, uint8_t* dst, hsa_agent_t dst_agent, const uint8_t* src,
                  uint64_t n, const hsa_signal_t* dep, uint64_t lead = 0);
 // Wait (bounded) until the first `got` pieces of group g have been copied.

@@ -325,6 +325,7 @@ void destroy_res(RecRes* r)
     for (auto s : r->piece_done)
         if (s.handle) hsa_signal_destroy(s);
     if (r->dep_lead.handle) hsa_signal_destroy(r->dep_lead);
+    if (r->lead_done.handle) hsa_signal_destroy(r->lead_done);
     if (r->dep_sums.handle) hsa_signal_destroy(r->dep_sums);
     if (r->done.handle) hsa_signal_destroy(r->done);
     if (r->h_seq) (void)hipHostFree(r->h_seq);
@@ -383,6 +384,7 @@ ckpt_status new_res(ckpt_ctx* c, RecRes** out)
     if (st == CKPT_OK) st = make_event(c, &r->t0, true);
     if (st == CKPT_OK) st = make_event(c, &r->t_red, true);
     if (st == CKPT_OK) st = gpu_only_signal(c, &r->dep_lead, &r->dep_lead_val);
+    if (st == CKPT_OK) st = gpu_consumed_signal(c, &r->lead_done);
     if (st == CKPT_OK) st = gpu_only_signal(c, &r->dep_sums, &r->dep_sums_val);
     if (st == CKPT_OK && hsa_signal_create(0, 0, nullptr, &r->done) != HSA_STATUS_SUCCESS) {
         r->done.handle = 0;
@@ -1467,6 +1469,20 @@ ckpt_status ckpt_debug_direct_plan(const uint64_t* nbytes, uint32_t n, uint64_t 
     }
     std::memcpy(piece_first, p0.data(), 8 * p0.size());
     std::memcpy(gap_first, g0.data(), 8 * g0.size());
+    return CKPT_OK;
+}
+
+ckpt_status ckpt_debug_copy_plan(uint64_t group_bytes, uint32_t engines, uint32_t led, uint64_t* spans, uint32_t* n)
+{
+    if (!group_bytes || !engines || !spans || !n) return CKPT_EINVAL;
+    CopySpan sp[3];
+    *n = (uint32_t)copy_spans(group_bytes, (int)std::min<uint32_t>(engines, kMaxEngines),
+                              led && engines > 1 && group_bytes >= 4 * kLead ? kLead : 0, sp);
+    for (uint32_t k = 0; k < *n; ++k) {
+        spans[3 * k] = sp[k].lo;
+        spans[3 * k + 1] = sp[k].n;
+        spans[3 * k + 2] = (uint64_t)sp[k].engine;
+    }
     return CKPT_OK;
 }
 

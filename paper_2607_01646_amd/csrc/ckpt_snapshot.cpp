@@ -89,19 +89,24 @@ int group_signals(const ckpt_ctx* c, const RecRes* res, uint64_t g, hsa_signal_t
 int issue_halves(ckpt_ctx* c, RecRes* res, uint64_t g, uint8_t* dst, hsa_agent_t dst_agent, const uint8_t* src,
                  uint64_t n, const hsa_signal_t* dep, uint64_t lead)
 {
-    const uint64_t half = lead ? lead : in_halves(c, g) ? round_up(n / 2, 4096) : n;
-    if (hsa_amd_memory_async_copy_on_engine(dst, dst_agent, src, c->gpu_agent, half, 1, lead ? &res->dep_lead : dep,
-                                            res->copied[g], c->d2h_engine[g % c->n_d2h_engines],
-                                            true) != HSA_STATUS_SUCCESS)
-        return 0;
-    if (half == n) return 1;
-    hsa_signal_store_screlease(res->piece_done[g], 1);
-    if (hsa_amd_memory_async_copy_on_engine(dst + half, dst_agent, src + half, c->gpu_agent, n - half, 1, dep,
-                                            res->piece_done[g], c->d2h_engine[(g + 1) % c->n_d2h_engines],
-                                            true) == HSA_STATUS_SUCCESS)
-        return 2;
-    hsa_signal_store_screlease(res->piece_done[g], 0);
-    return 1;
+    CopySpan sp[3];
+    const int n_sp = copy_spans(n, c->n_d2h_engines, lead, sp);
+    int got = 0;
+    for (int k = 0; k < n_sp; ++k) {
+        const bool is_lead = lead && k == 0;
+        const hsa_signal_t deps[2] = {is_lead ? res->dep_lead : *dep, res->lead_done};
+        const hsa_signal_t done = is_lead ? res->lead_done : got ? res->piece_done[g] : res->copied[g];
+        hsa_signal_store_screlease(done, 1);
+        if (hsa_amd_memory_async_copy_on_engine(
+                dst + sp[k].lo, dst_agent, src + sp[k].lo, c->gpu_agent, sp[k].n, lead && k == 1 ? 2 : 1, deps, done,
+                c->d2h_engine[(g + (uint64_t)sp[k].engine) % c->n_d2h_engines], true) != HSA_STATUS_SUCCESS) {
+            hsa_signal_store_screlease(done, 0);
+            if (lead && k == 1) (void)poll_zero(res->lead_done, 120); // nobody else waits for it
+            return got;
+        }
+        got += !is_lead;
+    }
+    return got;
 }
 
 // Direct D2H (no snapshot staging): per group, the sums kernel reads the
