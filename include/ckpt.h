@@ -238,8 +238,10 @@ ckpt_status ckpt_restore(ckpt_ctx* ctx, uint64_t snap_id, void* stream, uint32_t
                          uint32_t* n_bad);
 
 /* Integrity check of a committed host image without touching the live
- * tensors: a kernel reads it from host memory and recomputes every chunk
- * sum.  Same snap_id, list and error conventions as ckpt_restore. */
+ * tensors: a DMA engine brings it to a small device ring, where a kernel
+ * recomputes every chunk sum (it may run beside training, whose compute units
+ * the transfer leaves alone).  Same snap_id, list and error conventions as
+ * ckpt_restore. */
 ckpt_status ckpt_verify(ckpt_ctx* ctx, uint64_t snap_id, uint32_t* bad_chunks, uint32_t cap, uint32_t* n_bad);
 
 /* Layout accessors.  frag_off may be NULL; otherwise it receives n offsets. */
@@ -289,10 +291,10 @@ typedef struct {
                             small per-chunk reduce kernel is not included */
     uint32_t kernels;    /* number of tile-kernel launches (a snapshot's pack launches cover
                             pack_launch_bytes each) */
-    uint32_t copies;     /* number of DMA copy requests (image bytes only; 0 for restore and
-                            verify, whose kernels read the host image themselves) */
-    float copy_ms;       /* first image copy start to last image copy end (restore and verify:
-                            first kernel start to last kernel end) */
+    uint32_t copies;     /* chunk groups copied by the DMA engines (verify: spans of its ring; 0 for
+                            restore, whose kernel reads the host image itself) */
+    float copy_ms;       /* first image copy start to last image copy end (restore: first kernel
+                            start to last kernel end) */
     float total_ms;      /* operation start (after the trigger) to its last event; for a
                             snapshot: to its commit (image and sums in host memory; with
                             pageable images, the last group landed in the image) */

@@ -1,9 +1,15 @@
 // ckpt_check.cpp -- restore and verify of a committed host image (paper
-// Sec. V-C third stage, Sec. VI-E).  The scatter or checksum kernel reads the
-// image where it lies in pinned host memory, over the host link, and the
-// chunk-sum compare reads the stored sums and writes its results there too:
-// nothing is staged on the device, and the bytes' way over the link, the
-// writes into the fragments and the sums run at the same time.
+// Sec. V-C third stage, Sec. VI-E).  Restore's scatter kernel reads the image
+// where it lies in pinned host memory, over the host link: nothing is staged
+// on the device, and the bytes' way over the link, the writes into the
+// fragments and the sums run at the same time.  Verify runs beside training,
+// so there a DMA engine brings the image to a small device ring and the
+// checksum kernel reads it from there: a kernel that reads over the link
+// holds its compute units for the whole transfer, and a GEMM with one
+// workgroup for every unit then takes two rounds (4096^3 in bf16 beside
+// verifies of 1.5 GB: +62% with 24 workgroups on the link, 27.5 ms a verify;
+// +3% with the ring, 28.0 ms).  The chunk-sum compare of both reads the
+// stored sums and writes its results in host memory.
 #include "ckpt_host.h"
 
 namespace ckpt {
@@ -22,8 +28,9 @@ ckpt_status check_image(ckpt_ctx* c, int b, hipStream_t stream, bool scatter, co
     const std::vector<hipEvent_t>&k0 = scatter ? c->tk0 : c->vk0, &k1 = scatter ? c->tk1 : c->vk1;
     // Byte spans, one launch each: runs of consecutive chunks, cut at the
     // size of a chunk group when the host puts the bytes in place span by span
-    // (bounce slots, bytes arriving from a peer).
-    const uint64_t most = c->bounce || fill ? c->G : c->n_chunks;
+    // (bounce slots, bytes arriving from a peer), and of a ring slot for verify.
+    uint64_t most = c->bounce || fill ? c->G : c->n_chunks;
+    if (!scatter) most = std::min(most, c->vslot_chunks);
     std::vector<std::pair<uint64_t, uint64_t>> spans;
     if (!ids) {
         for (uint64_t k = 0; k < c->n_chunks; k += most)
@@ -39,12 +46,13 @@ ckpt_status check_image(ckpt_ctx* c, int b, hipStream_t stream, bool scatter, co
     const uint64_t n_spans = spans.size(), slot_bytes = c->G * c->C;
     const bool timed = c->timing && !ids; // timing is kept for whole-image operations only
     unsigned long long* partials = c->d_partials + c->geo.n_tiles;
-    const uint32_t grid = std::min(c->grid_cap, scatter ? kRestoreGrid : kVerifyGrid);
+    const uint32_t grid = scatter ? std::min(c->grid_cap, kRestoreGrid) : c->grid_cap;
+    const uint64_t vslot_bytes = c->vslot_chunks * c->C;
     if (scatter) {
         HIPCHK(c, hipEventRecord(c->ev_trigger, stream));
         HIPCHK(c, hipStreamWaitEvent(s, c->ev_trigger, 0));
     }
-    if (timed) HIPCHK(c, hipEventRecord(t0, s));
+    if (timed) HIPCHK(c, hipEventRecord(t0, scatter ? s : c->s_vcopy[0]));
     for (uint64_t u = 0; u < n_spans; ++u) {
         const uint64_t lo = spans[u].first, hi = spans[u].second;
         if (fill && !fill(lo, hi)) { // the span's bytes did not arrive: let the issued work finish, then fail
@@ -52,11 +60,28 @@ ckpt_status check_image(ckpt_ctx* c, int b, hipStream_t stream, bool scatter, co
             return CKPT_EHIP;
         }
         const uint8_t* src = c->h_img[b] + lo;
-        if (c->bounce) { // pageable image: through a pinned ring slot, free once the kernel that read it has finished
+        if (c->bounce) { // pageable image: through a pinned ring slot, free once what read it has finished
             const uint64_t slot = u % c->n_bslots;
             if (u >= c->n_bslots) HIPCHK(c, hipEventSynchronize(c->bin_done[slot]));
             c->pool->copy(c->h_bin + slot * slot_bytes, src, hi - lo);
             src = c->h_bin + slot * slot_bytes;
+        }
+        if (!scatter) {
+            // The host paces the ring: it waits for the kernel that last read
+            // the slot, so that the copies follow each other with no wait of
+            // the device's between them (which cost ~6% of the link).  They
+            // alternate between two streams: one stream starts a copy ~15 us
+            // after its last one.
+            const uint64_t slot = u % c->n_vslots;
+            hipStream_t cs = c->s_vcopy[u % 2];
+            uint8_t* ring = c->d_vring + slot * vslot_bytes;
+            HIPCHK(c, hipEventSynchronize(c->vfree[slot]));
+            HIPCHK(c, hipMemcpyAsync(ring, src, hi - lo, hipMemcpyHostToDevice, cs));
+            if (c->bounce) HIPCHK(c, hipEventRecord(c->bin_done[u % c->n_bslots], cs));
+            if (timed && u + 1 == n_spans) HIPCHK(c, hipEventRecord(c->vc1, cs));
+            HIPCHK(c, hipEventRecord(c->vloaded[slot], cs));
+            HIPCHK(c, hipStreamWaitEvent(s, c->vloaded[slot], 0));
+            src = ring;
         }
         const uint64_t t_lo = lo >> c->geo.tile_shift, t_hi = (hi + (1ull << c->geo.tile_shift) - 1) >> c->geo.tile_shift;
         hipEvent_t e0 = timed ? k0[u] : nullptr, e1 = timed ? k1[u] : nullptr;
@@ -66,7 +91,8 @@ ckpt_status check_image(ckpt_ctx* c, int b, hipStream_t stream, bool scatter, co
         else
             e = launch_checksum(c->geo, t_lo, t_hi, src, lo, partials, grid, s, e0, e1);
         if (e != hipSuccess) return fail(c, CKPT_EHIP, "kernel launch failed: %s", hipGetErrorString(e));
-        if (c->bounce) HIPCHK(c, hipEventRecord(c->bin_done[u % c->n_bslots], s));
+        if (scatter && c->bounce) HIPCHK(c, hipEventRecord(c->bin_done[u % c->n_bslots], s));
+        if (!scatter) HIPCHK(c, hipEventRecord(c->vfree[u % c->n_vslots], s));
         e = launch_chunk_reduce(c->geo, t_lo, t_hi, partials, c->h_recomputed,
                                 (const unsigned long long*)c->h_sums[b], c->h_bad, s);
         if (e != hipSuccess) return fail(c, CKPT_EHIP, "kernel launch failed: %s", hipGetErrorString(e));
@@ -78,7 +104,8 @@ ckpt_status check_image(ckpt_ctx* c, int b, hipStream_t stream, bool scatter, co
         ckpt_timing t{};
         for (uint64_t u = 0; u < n_spans; ++u) t.kernel_ms += elapsed(k0[u], k1[u]);
         t.kernels = (uint32_t)n_spans;
-        t.copy_ms = elapsed(k0[0], k1[n_spans - 1]);
+        t.copies = scatter ? 0 : (uint32_t)n_spans;
+        t.copy_ms = scatter ? elapsed(k0[0], k1[n_spans - 1]) : elapsed(t0, c->vc1);
         t.total_ms = elapsed(t0, k1[n_spans - 1]);
         t.kernel_bytes = scatter ? 2 * c->payload : c->I;
         t.copy_bytes = c->I;

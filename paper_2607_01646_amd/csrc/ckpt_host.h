@@ -73,6 +73,15 @@ inline int copy_spans(uint64_t n, int engines, uint64_t lead, CopySpan out[3])
     if (half < n) out[k++] = CopySpan{half, n - half, 1};
     return k;
 }
+// Verify's device ring: slots of up to 64 MiB of whole chunks (at least one),
+// with pageable images 16 MiB; as many as fit 256 MiB, two to eight.  A slot's
+// checksum takes ~1% of the time of its copy, so only the last one's adds to a
+// verify.  By slot, 8 / 16 / 32 / 64 MiB: 239 MB 4300 / 4290 / 4308 / 4276 us,
+// 1.5 GB 26640 / 26625 / 26650 / 26440 (one copy of each chunk group, a ring of
+// two groups: 4295 and 26460); pageable 239 MB 4590 / 4574 / 4658 / 4720 (4900).
+constexpr uint64_t kVerifySlot = 64ull << 20;
+constexpr uint64_t kVerifySlotBounce = 16ull << 20;
+constexpr uint64_t kVerifyRing = 256ull << 20;
 constexpr uint32_t kDefaultHostThreads = 12; // bounce mode: host copy threads (measured: 8 do not keep up with the link)
 
 struct Frag {
@@ -433,7 +442,7 @@ struct ckpt_ctx {
     uint64_t img_map_bytes = 0;       // mapped length of each pageable image
     uint8_t* h_bout = nullptr;        // device -> host ring
     uint8_t* h_bin = nullptr;         // host -> device ring
-    std::vector<hipEvent_t> bin_done; // per host -> device slot: the kernel that last read it has finished
+    std::vector<hipEvent_t> bin_done; // per host -> device slot: the kernel or copy that last read it has finished
     CopyPool* pool = nullptr;
     Pump* pump = nullptr;
 
@@ -451,10 +460,13 @@ struct ckpt_ctx {
     FileHead fhead{};
     uint64_t file_seq = 0; // last commit number written (drainer thread after registration)
 
-    // verify: its own stream
-    hipStream_t s_vker = nullptr;
-    hipEvent_t ev_vdone = nullptr, vt0 = nullptr;
-    std::vector<hipEvent_t> vk0, vk1;
+    // verify: its own device ring and streams
+    uint8_t* d_vring = nullptr;
+    uint64_t vslot_chunks = 1, n_vslots = 0;
+    hipStream_t s_vcopy[2] = {nullptr, nullptr}, s_vker = nullptr;
+    hipEvent_t ev_vdone = nullptr, vt0 = nullptr, vc1 = nullptr;
+    std::vector<hipEvent_t> vfree, vloaded; // per slot: read by the kernel, filled
+    std::vector<hipEvent_t> vk0, vk1;       // per launch, timing
 
     std::string err;
 };

@@ -89,15 +89,12 @@ hipError_t launch_checksum(const Geometry& g, uint64_t t_lo, uint64_t t_hi, cons
                            unsigned long long* partials, uint32_t grid_cap, hipStream_t s, hipEvent_t t0 = nullptr,
                            hipEvent_t t1 = nullptr);
 
-// grid_cap of a checksum and of a scatter that read pinned host memory.  The
-// link needs ~200 KiB of loads in flight; a verify takes the fewest workgroups
-// that give them, so that the rest of the GPU stays free for other kernels,
-// and a restore, beside which nothing runs, enough to cover its stores too.
-// GB/s over a 1.5 GB image by grid, verify / restore: 12 51.3/44.5, 16
-// 57.1/55.8, 24 57.5/57.0, 32 57.6/56.4, 48 54.5/53.0, 64 56.2/55.0, 96
-// 57.5/56.9, 160 57.5/57.0, 256 57.5/57.0, 512 56.3/57.3 (windows of 320 to
-// 640 KiB are slow on the link itself: a plain copy kernel shows the same).
-constexpr uint32_t kVerifyGrid = 24;
+// grid_cap of a scatter that reads pinned host memory.  The link needs ~200
+// KiB of loads in flight, and a restore, beside which nothing runs, enough to
+// cover its stores too.  GB/s over a 1.5 GB image by grid: 12 44.5, 16 55.8,
+// 24 57.0, 32 56.4, 48 53.0, 64 55.0, 96 56.9, 160 57.0, 256 57.0, 512 57.3
+// (windows of 320 to 640 KiB are slow on the link itself: a plain copy kernel
+// shows the same).
 constexpr uint32_t kRestoreGrid = 160;
 
 // grid_cap of a pack that writes pinned host memory: 16 to 256 workgroups

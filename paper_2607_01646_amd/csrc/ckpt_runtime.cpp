@@ -526,7 +526,7 @@ void prune(ckpt_ctx* c)
 // Wait for every enqueued kernel and copy of the context.
 ckpt_status drain(ckpt_ctx* c)
 {
-    for (hipStream_t st : {c->s_pack, c->s_vker})
+    for (hipStream_t st : {c->s_pack, c->s_vcopy[0], c->s_vcopy[1], c->s_vker})
         if (st) HIPCHK(c, hipStreamSynchronize(st));
     for (auto& kv : c->recs) {
         ckpt_status st = wait_copies(c, kv.second);
@@ -614,10 +614,9 @@ float elapsed(hipEvent_t a, hipEvent_t b)
 
 // Restore (scatter=true) or verify (scatter=false) from a committed image.
 // Restore first waits for every outstanding snapshot (it rewrites the live
-// tensors and shares the snapshot staging).  Verify only reads a committed
-// image, which no in-flight snapshot targets, through its own staging ring
-// and streams, so it may run while a newer snapshot streams out: the host
-// link is full duplex.
+// tensors).  Verify only reads a committed image, which no in-flight snapshot
+// targets, through its own device ring and streams, so it may run while a
+// newer snapshot streams out: the host link is full duplex.
 ckpt_status run_check(ckpt_ctx* c, uint64_t snap_id, hipStream_t stream, bool scatter, uint32_t* bad_chunks,
                       uint32_t cap, uint32_t* n_bad)
 {
@@ -645,10 +644,11 @@ void free_ctx(ckpt_ctx* c)
     c->recs.clear();
     for (auto r : c->free_res) destroy_res(r);
     c->free_res.clear();
-    for (auto* v : {&c->tk0, &c->tk1, &c->vk0, &c->vk1, &c->bin_done})
+    for (auto* v : {&c->tk0, &c->tk1, &c->vfree, &c->vloaded, &c->vk0, &c->vk1, &c->bin_done})
         for (auto e : *v) (void)hipEventDestroy(e);
-    for (hipEvent_t e : {c->ev_trigger, c->ev_done, c->tt0, c->ev_vdone, c->vt0})
+    for (hipEvent_t e : {c->ev_trigger, c->ev_done, c->tt0, c->ev_vdone, c->vt0, c->vc1})
         if (e) (void)hipEventDestroy(e);
+    (void)hipFree(c->d_vring);
     (void)hipFree(c->d_frags);
     (void)hipFree(c->d_small);
     (void)hipFree(c->d_tile_src);
@@ -672,7 +672,7 @@ void free_ctx(ckpt_ctx* c)
     if (c->h_bad) (void)hipHostFree(c->h_bad);
     if (c->h_recomputed) (void)hipHostFree(c->h_recomputed);
     if (!c->own_pack) c->s_pack = nullptr; // the caller's stream
-    for (hipStream_t st : {c->s_pack, c->s_vker})
+    for (hipStream_t st : {c->s_pack, c->s_vcopy[0], c->s_vcopy[1], c->s_vker})
         if (st) (void)hipStreamDestroy(st);
 }
 
@@ -778,11 +778,11 @@ ckpt_status ckpt_create(const ckpt_config* cfg, ckpt_ctx** out)
         c->s_pack = (hipStream_t)d.side_stream;
         c->own_pack = false;
     }
-    for (hipStream_t* sp : {&c->s_pack, &c->s_vker})
+    for (hipStream_t* sp : {&c->s_pack, &c->s_vcopy[0], &c->s_vcopy[1], &c->s_vker})
         if (st == CKPT_OK && !*sp && hipStreamCreateWithFlags(sp, hipStreamNonBlocking) != hipSuccess) st = CKPT_EHIP;
     for (hipEvent_t* e : {&c->ev_trigger, &c->ev_done, &c->ev_vdone})
         if (st == CKPT_OK) st = make_event(c, e, false);
-    for (hipEvent_t* e : {&c->tt0, &c->vt0})
+    for (hipEvent_t* e : {&c->tt0, &c->vt0, &c->vc1})
         if (st == CKPT_OK) st = make_event(c, e, true);
     if (st == CKPT_OK) st = setup_hsa(c);
     if (st != CKPT_OK) {
@@ -933,6 +933,11 @@ ckpt_status ckpt_register_tensors(ckpt_ctx* c, const ckpt_tensor* t, uint32_t n)
     ALLOC(c->d_partials, 2 * nt * 8);
     ALLOC(c->d_area_done, n_areas * 8 + 8); // and the ticket of launch_pack_chunks
     if (!small.empty()) ALLOC(c->d_small, small.size() * sizeof(Piece));
+    c->vslot_chunks = std::min(std::max<uint64_t>(1, (c->bounce ? kVerifySlotBounce : kVerifySlot) / c->C), c->n_chunks);
+    if (c->bounce) c->vslot_chunks = std::min(c->vslot_chunks, c->G);
+    const uint64_t n_vspans = (c->n_chunks + c->vslot_chunks - 1) / c->vslot_chunks;
+    c->n_vslots = std::min(std::min<uint64_t>(std::max<uint64_t>(kVerifyRing / (c->vslot_chunks * c->C), 2), 8), n_vspans);
+    ALLOC(c->d_vring, n_vspans == 1 ? c->I : c->n_vslots * c->vslot_chunks * c->C);
     if (!c->direct) ALLOC(c->d_staging, c->ring ? c->n_slots * c->G * c->C : c->I);
 #undef ALLOC
     HIPCHK(c, hipMemcpy(c->d_frags, fd.data(), n * sizeof(FragDev), hipMemcpyHostToDevice));
@@ -981,11 +986,13 @@ ckpt_status ckpt_register_tensors(ckpt_ctx* c, const ckpt_tensor* t, uint32_t n)
     if (hipHostMalloc((void**)&c->h_bad, c->n_chunks, hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void**)&c->h_recomputed, c->n_chunks * 8, hipHostMallocDefault) != hipSuccess)
         return fail(c, CKPT_ENOMEM, "pinned result buffers");
-    for (auto* v : {&c->tk0, &c->tk1, &c->vk0, &c->vk1}) {
-        v->resize(c->n_groups, nullptr);
+    for (auto* v : {&c->tk0, &c->tk1, &c->vk0, &c->vk1, &c->vfree, &c->vloaded}) {
+        const bool slots = v == &c->vfree || v == &c->vloaded;
+        v->resize(slots ? c->n_vslots : v == &c->vk0 || v == &c->vk1 ? n_vspans : c->n_groups, nullptr);
         for (auto& e : *v) {
-            ckpt_status st = make_event(c, &e, true);
+            ckpt_status st = make_event(c, &e, !slots);
             if (st) return st;
+            if (slots) HIPCHK(c, hipEventRecord(e, c->s_vker)); // every slot starts free
         }
     }
     if (c->bounce) {

@@ -1,6 +1,7 @@
-"""Restore and verify read the host image where it lies (needs an MI355X):
-images of fewer tiles than the launch has workgroups, of as many and of more,
-in every mode, and bytes that the host changes between two calls."""
+"""Kernels that read or write the host image where it lies (needs an MI355X):
+restore with fewer tiles than the launch has workgroups, as many and more, in
+every mode, and bytes that the host changes between two calls; small images
+and small pieces written by the kernel; and verify, which does neither."""
 import numpy as np
 import pytest
 import torch
@@ -41,6 +42,33 @@ def test_host_changes_between_calls_are_seen(tiles, mode):
         assert ck.restore() == []
         assert all(np.array_equal(host_bytes(t), h) for t, h in zip(tensors, host))
     assert np.array_equal(img, before)
+    ck.close()
+
+
+@pytest.mark.parametrize("bounce", [0, 16 << 20])
+@pytest.mark.parametrize("size,chunk", [((700 << 20) - 77, 1 << 20), ((100 << 20) - 77, 3 * 4096 * 11),
+                                        ((70 << 20) + 1, 40 << 20), (5000, 4096), (1, 1 << 20)])
+def test_verify_goes_through_its_ring(size, chunk, bounce):
+    """Verify over fewer spans than its ring has slots and over more, with
+    several wrong chunks; its kernels run for a small part of the transfer, so
+    that training beside it keeps the compute units."""
+    if bounce and chunk > 8 << 20:
+        bounce = 2 * chunk
+    tensors, host = random_byte_fragments([size // 3, size - size // 3], seed=size)
+    ck, snap = snapshot_and_check(tensors, host, chunk, 16, group=chunk if bounce else 0, bounce=bounce)
+    P.ckpt_set_timing(ck.ctx, 1)
+    img, sums = ck.host_image(snap)
+    at = sorted({x // chunk: x for x in (0, img.size // 2, img.size - 1)}.values())  # one byte in a chunk
+    for x in at:
+        img[x] ^= 0x80
+    assert ck.verify() == [x // chunk for x in at]
+    for x in at:
+        img[x] ^= 0x80
+    assert ck.verify() == []
+    assert np.array_equal(P.ckpt_last_sums(ck.ctx), sums)
+    t = P.ckpt_last_timing(ck.ctx, P.CKPT_OP_VERIFY)
+    assert t["copies"] == t["kernels"] > 0 and t["copy_bytes"] == img.size
+    assert size < 1 << 20 or t["kernel_ms"] < 0.25 * t["copy_ms"]
     ck.close()
 
 
