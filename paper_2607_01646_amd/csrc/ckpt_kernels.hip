@@ -530,6 +530,12 @@ __global__ __launch_bounds__(kBlock) void pack_chunks_kernel(Args a, unsigned lo
     }
 }
 
+// Most workgroups of a launch: a dispatch counts its lanes in 32 bits.
+constexpr uint32_t max_grid(uint32_t block) { return 0xffffffffu / block; }
+
+// A grid of one workgroup per tile, or of as many as the cap and the dispatch
+// allow, each striding over tiles: 64 GiB of 8 KiB tiles are past that, and so
+// are 128 MiB of 16-byte ones.
 // With timing events, the launch records them around the dispatch itself
 // (the same interval a kernel trace reports).
 template <int MODE>
@@ -537,7 +543,7 @@ hipError_t launch_tiles(const Args& a, uint32_t grid_cap, hipStream_t s, hipEven
 {
     if (a.t_hi <= a.t_lo) return hipSuccess;
     const uint64_t n = a.t_hi - a.t_lo;
-    const uint32_t grid = (uint32_t)(n < grid_cap ? n : grid_cap);
+    const uint32_t grid = (uint32_t)std::min<uint64_t>(n, std::min(grid_cap, max_grid(kBlock)));
     void (*kern)(Args) = grid == n ? tile_kernel<MODE, false> : tile_kernel<MODE, true>;
     if (t0 && t1)
         hipExtLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), 0, s, t0, t1, 0, a);
@@ -862,7 +868,7 @@ hipError_t launch_sums(const FragDev* frags, const uint64_t* tile_src,
     Args a{frags, tile_src, g, t_lo, t_hi, nullptr, 0, partials, release};
     if (t_hi <= t_lo) return hipSuccess;
     const uint64_t runs = (t_hi - t_lo + kSumsTiles - 1) / kSumsTiles;
-    if (runs > grid_cap) return launch_tiles<SUMS>(a, grid_cap, s, t0, t1); // a capped grid strides over tiles
+    if (runs > std::min(grid_cap, max_grid(kSumsBlock))) return launch_tiles<SUMS>(a, grid_cap, s, t0, t1); // a capped grid strides over tiles
     if (t0 && t1)
         hipExtLaunchKernelGGL(sums_run_kernel, dim3((uint32_t)runs), dim3(kSumsBlock), 0, s, t0, t1, 0, a);
     else

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import oracle as O
-from gpu_util import host_bytes, snapshot_and_check
+from gpu_util import host_bytes, random_byte_fragments, snapshot_and_check
 
 pytestmark = pytest.mark.gpu
 
@@ -40,6 +40,17 @@ def test_unaligned_fragments(shift, chunk, align, direct):
     ck, _ = snapshot_and_check(views, [host_bytes(v) for v in views], chunk, align, direct=direct)
     ck.close()
     assert np.array_equal(host_bytes(flat), before)  # the guard bytes too
+
+
+@pytest.mark.parametrize("direct", [False, True])
+def test_more_tiles_than_a_dispatch_has_workgroups(direct):
+    """16-byte tiles of an image just past 128 MiB: one workgroup per tile
+    would be more lanes than a dispatch can count."""
+    n = (1 << 32) // 512 * 16 + 48
+    tensors, host = random_byte_fragments([n // 3, n - n // 3 - 21], seed=n)
+    ck, _ = snapshot_and_check(tensors, host, 16 * 65537, 16, direct=direct)
+    assert ck.image_bytes > (1 << 32) // 512 * 16
+    ck.close()
 
 
 @pytest.mark.parametrize("shift", [0, 3, 8, 14])
