@@ -18,7 +18,8 @@
 // that never cross a chunk.  A workgroup of 512 lanes (8 wave64) takes one
 // tile (a separate instantiation strides over tiles when the grid is
 // capped): wave w owns the tile's 1 KiB slice w and each lane moves one
-// 16-byte vector; a tile shorter than 8 KiB leaves its last waves idle.
+// 16-byte vector.  Where the chunk size leaves smaller tiles, a workgroup
+// takes the 8 KiB run of tiles that such a tile's workgroup would (run_kernel).
 // Consecutive tiles go to consecutive workgroups, which the hardware deals
 // out round-robin over the 8 XCDs (measured faster than giving each XCD a
 // contiguous range).
@@ -420,9 +421,81 @@ __global__ __launch_bounds__(BLOCK) void tile_kernel(Args a)
     if (MODE == PACK || MODE == SUMS) release_signal(a.release);
 }
 
+// One 16-byte vector at image byte x by one lane, which looks its tile up
+// itself.  Returns the vector's sum.
+template <int MODE>
+__device__ __forceinline__ unsigned long long move_vector(const Args& a, uint64_t x)
+{
+    u32x4* win = MODE == SUMS ? nullptr : reinterpret_cast<u32x4*>(a.img + (x - a.origin));
+    u32x4 r;
+    if (MODE == VERIFY) return vsum(__builtin_nontemporal_load(win));
+    const uint64_t e = a.tile_src[x >> a.g.tile_shift];
+    if (!(e & kTileSlow)) {
+        uint8_t* fr = reinterpret_cast<uint8_t*>(e + (x & ((1ull << a.g.tile_shift) - 1)));
+        if (MODE == SCATTER) {
+            r = __builtin_nontemporal_load(win);
+            if ((e & 15) == 0) st_stream(r, reinterpret_cast<u32x4*>(fr));
+            else *reinterpret_cast<u32x4_any*>(fr) = r;
+        } else {
+            r = ld_any<true>(fr);
+            if (MODE == PACK) st_stream(r, win);
+        }
+    } else {
+        const FragDev F = a.frags[find_frag_global(a.frags, tile_first(e), tile_last(e), x)];
+        if (MODE == SCATTER) {
+            r = __builtin_nontemporal_load(win);
+            store_general(F.ptr, F.nbytes, x - F.off, r);
+        } else {
+            r = fetch_general(F.ptr, F.nbytes, x - F.off);
+            if (MODE == PACK) st_stream(r, win);
+        }
+    }
+    return vsum(r);
+}
+
+// Tiles of less than 8 KiB: workgroup b takes 8 KiB of the image, a run of
+// whole tiles, one vector per lane, and strides over runs.  The tile size is
+// the largest power of two that divides the chunk size, so an odd chunk size
+// makes tiles of a few lanes; one workgroup for each of them (or a few that
+// stride over them, where the other side of the link wants 200 KiB in flight)
+// would be bound by dispatches and by one latency per tile.  256 MiB in 100
+// fragments, a workgroup per tile of 512 / of 256 lanes / this: tiles of 4 KiB
+// 159 / 174 / 146 us, of 1 KiB 446 / 357 / 144, of 256 bytes 1545 / 1100 / 185,
+// of 16 bytes 24600 / 24150 / 1650.
+template <int MODE>
+__global__ __launch_bounds__(kBlock) void run_kernel(Args a)
+{
+    __shared__ unsigned long long s_red[kBlock / 64];
+    const uint32_t tid = threadIdx.x, shift = a.g.tile_shift;
+    const uint32_t lpt = 1u << (shift - 4); // lanes per tile: 1 to 256
+    const uint64_t lo = a.t_lo << shift;
+    const uint64_t end = (a.t_hi << shift) < a.g.image_bytes ? a.t_hi << shift : a.g.image_bytes;
+    const uint64_t runs = (end - lo + (1u << kMaxTileShift) - 1) >> kMaxTileShift;
+    for (uint64_t b = blockIdx.x; b < runs; b += gridDim.x) {
+        const uint64_t x = lo + (b << kMaxTileShift) + 16 * tid;
+        unsigned long long acc = x < end ? move_vector<MODE>(a, x) : 0;
+        for (uint32_t m = 1; m < lpt && m < 64; m <<= 1) acc += shfl_xor64(acc, m);
+        if (lpt <= 64) {
+            if (x < end && (tid & (lpt - 1)) == 0) a.partials[x >> shift] = acc;
+        } else { // a tile is two or four waves; uniform over the workgroup
+            const uint32_t wpt = lpt >> 6;
+            if ((tid & 63) == 0) s_red[tid >> 6] = acc;
+            __syncthreads();
+            const uint64_t t = ((lo + (b << kMaxTileShift)) >> shift) + tid;
+            if (tid < kBlock / 64 / wpt && t < a.t_hi) {
+                unsigned long long sum = 0;
+                for (uint32_t k = 0; k < wpt; ++k) sum += s_red[tid * wpt + k];
+                a.partials[t] = sum;
+            }
+            __syncthreads(); // s_red is read before the next run writes it
+        }
+    }
+    if (MODE == PACK || MODE == SUMS) release_signal(a.release);
+}
+
 // SUMS over runs of kSumsTiles tiles: workgroup b takes tiles
-// [t_lo + kSumsTiles * b, t_lo + kSumsTiles * (b + 1)).  When they are all
-// full 8 KiB tiles inside one 16-byte-aligned fragment, the workgroup streams
+// [t_lo + kSumsTiles * b, t_lo + kSumsTiles * (b + 1)), of 8 KiB.  When they
+// are all full tiles inside one 16-byte-aligned fragment, the workgroup streams
 // them in one batch: wave w owns a quarter of the run (four vectors per lane,
 // all loads issued first), and two waves make up a tile's sum.  Otherwise
 // each tile takes the per-tile path.  A read-only stream has no stores to keep the
@@ -440,8 +513,7 @@ __global__ __launch_bounds__(kSumsBlock) void sums_run_kernel(Args a)
     constexpr uint32_t kTileVecs = 1u << (kMaxTileShift - 4);
     const uint64_t t = a.t_lo + (uint64_t)kSumsTiles * blockIdx.x; // < t_hi (grid: ceil(tiles / kSumsTiles))
     uint64_t e = kTileSlow;
-    if (t + kSumsTiles <= a.t_hi && a.g.tile_shift == kMaxTileShift &&
-        ((t + kSumsTiles) << kMaxTileShift) <= a.g.image_bytes) {
+    if (t + kSumsTiles <= a.t_hi && ((t + kSumsTiles) << kMaxTileShift) <= a.g.image_bytes) {
         e = a.tile_src[t];
         if ((e & 15) || a.tile_src[t + 1] != e + (1u << kMaxTileShift)) e = kTileSlow;
     }
@@ -514,7 +586,13 @@ __global__ __launch_bounds__(kBlock) void pack_chunks_kernel(Args a, unsigned lo
     const uint64_t t0 = (uint64_t)blockIdx.x * a.g.tiles_per_chunk;
     const uint64_t t1 = t0 + a.g.tiles_per_chunk < a.g.n_tiles ? t0 + a.g.tiles_per_chunk : a.g.n_tiles;
     unsigned long long acc = 0;
-    for (uint64_t t = t0; t < t1; ++t) acc += move_tile<PACK, kBlock, kUnroll, true, true>(a, t, s_off);
+    if (a.g.tile_shift < kMaxTileShift) {
+        const uint64_t lo = t0 << a.g.tile_shift;
+        const uint64_t end = (t1 << a.g.tile_shift) < a.g.image_bytes ? t1 << a.g.tile_shift : a.g.image_bytes;
+        for (uint64_t x = lo + 16 * threadIdx.x; x < end; x += 16 * kBlock) acc += move_vector<PACK>(a, x);
+    } else {
+        for (uint64_t t = t0; t < t1; ++t) acc += move_tile<PACK, kBlock, kUnroll, true, true>(a, t, s_off);
+    }
     acc = block_sum<kBlock>(acc, s_red);
     if (threadIdx.x == 0) sums_out[blockIdx.x] = acc;
     if (ticket) {
@@ -533,18 +611,19 @@ __global__ __launch_bounds__(kBlock) void pack_chunks_kernel(Args a, unsigned lo
 // Most workgroups of a launch: a dispatch counts its lanes in 32 bits.
 constexpr uint32_t max_grid(uint32_t block) { return 0xffffffffu / block; }
 
-// A grid of one workgroup per tile, or of as many as the cap and the dispatch
-// allow, each striding over tiles: 64 GiB of 8 KiB tiles are past that, and so
-// are 128 MiB of 16-byte ones.
+// A grid of one workgroup per tile (per 8 KiB run of smaller ones), or of as
+// many as the cap and the dispatch allow, each striding over the rest: 64 GiB
+// are past the dispatch.
 // With timing events, the launch records them around the dispatch itself
 // (the same interval a kernel trace reports).
 template <int MODE>
 hipError_t launch_tiles(const Args& a, uint32_t grid_cap, hipStream_t s, hipEvent_t t0, hipEvent_t t1)
 {
     if (a.t_hi <= a.t_lo) return hipSuccess;
-    const uint64_t n = a.t_hi - a.t_lo;
+    const uint32_t per_run = kMaxTileShift - a.g.tile_shift; // log2 of the tiles in 8 KiB
+    const uint64_t n = (a.t_hi - a.t_lo + (1ull << per_run) - 1) >> per_run;
     const uint32_t grid = (uint32_t)std::min<uint64_t>(n, std::min(grid_cap, max_grid(kBlock)));
-    void (*kern)(Args) = grid == n ? tile_kernel<MODE, false> : tile_kernel<MODE, true>;
+    void (*kern)(Args) = per_run ? run_kernel<MODE> : grid == n ? tile_kernel<MODE, false> : tile_kernel<MODE, true>;
     if (t0 && t1)
         hipExtLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), 0, s, t0, t1, 0, a);
     else
@@ -868,7 +947,9 @@ hipError_t launch_sums(const FragDev* frags, const uint64_t* tile_src,
     Args a{frags, tile_src, g, t_lo, t_hi, nullptr, 0, partials, release};
     if (t_hi <= t_lo) return hipSuccess;
     const uint64_t runs = (t_hi - t_lo + kSumsTiles - 1) / kSumsTiles;
-    if (runs > std::min(grid_cap, max_grid(kSumsBlock))) return launch_tiles<SUMS>(a, grid_cap, s, t0, t1); // a capped grid strides over tiles
+    // Smaller tiles, and a capped grid, which strides over tiles.
+    if (g.tile_shift < kMaxTileShift || runs > std::min(grid_cap, max_grid(kSumsBlock)))
+        return launch_tiles<SUMS>(a, grid_cap, s, t0, t1);
     if (t0 && t1)
         hipExtLaunchKernelGGL(sums_run_kernel, dim3((uint32_t)runs), dim3(kSumsBlock), 0, s, t0, t1, 0, a);
     else

@@ -1,6 +1,8 @@
 """Tiles against fragments that start and end anywhere (needs an MI355X):
 whole tiles inside an unaligned fragment, tiles cut by a fragment's end, and
 neighbouring bytes that no kernel may touch, against the CPU oracle."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -40,6 +42,51 @@ def test_unaligned_fragments(shift, chunk, align, direct):
     ck, _ = snapshot_and_check(views, [host_bytes(v) for v in views], chunk, align, direct=direct)
     ck.close()
     assert np.array_equal(host_bytes(flat), before)  # the guard bytes too
+
+
+@pytest.mark.parametrize("tile", [16, 32, 256, 512, 1024, 2048, 4096])
+@pytest.mark.parametrize("size,kw", [
+    (200_003, dict()), (1_900_001, dict(direct=True)),          # written by the pack kernel
+    (2_500_007, dict()), (2_500_007, dict(grid=3)),
+    (17_000_003, dict(direct=True)), (2_500_007, dict(bounce=1)),
+])
+def test_small_tiles(tile, size, kw):
+    """Chunk sizes that leave tiles of less than 8 KiB, in runs that end inside
+    a chunk and past the image, over fragments that start and end anywhere."""
+    chunk = tile * (2 * (70_000 // tile // 2) + 1)
+    assert P.ckpt_debug_tile_plan([size], chunk, 16)[0] == tile
+    if "bounce" in kw:
+        kw = dict(bounce=4 * chunk, group=2 * chunk)
+    rng = np.random.default_rng(tile + size)
+    cuts = np.sort(rng.integers(0, size + 1, 37))
+    sizes = [int(n) for n in np.diff(np.concatenate([[0], cuts, [size]]))] + [0, 5, 16, 33]
+    flat = torch.from_numpy(rng.integers(0, 256, sum(sizes) + 3 * len(sizes) + 1, dtype=np.uint8)).cuda()
+    before, views, at = host_bytes(flat), [], 1
+    for n in sizes:
+        views.append(flat[at:at + n])
+        at += n + 3
+    ck, _ = snapshot_and_check(views, [host_bytes(v) for v in views], chunk, 16, **kw)
+    assert np.array_equal(host_bytes(flat), before)  # and no byte beside a fragment
+    ck.close()
+
+
+@pytest.mark.parametrize("chunk", [(1 << 20) + 16, (1 << 20) + 256, 65536 - 16])
+def test_small_tiles_cost_no_latency_each(chunk):
+    """What one workgroup per tile, or a few that stride over small tiles,
+    would take ten times as long for."""
+    tensors, _ = random_byte_fragments([2 << 20] * (7 if chunk < 1 << 20 else 16), seed=chunk)
+
+    def seconds(C):
+        best = []
+        with P.Checkpointer(tensors, chunk_bytes=C, align_bytes=16, direct=C < 1 << 20) as ck:
+            for _ in range(5):
+                t = time.perf_counter()
+                ck.wait_committed(ck.snapshot(step=1))
+                ck.restore()
+                best.append(time.perf_counter() - t)
+        return min(best)
+
+    assert seconds(chunk) < 3 * seconds(-(-chunk // 8192) * 8192)
 
 
 @pytest.mark.parametrize("direct", [False, True])
