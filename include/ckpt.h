@@ -293,8 +293,8 @@ typedef struct {
                             pack_launch_bytes each) */
     uint32_t copies;     /* chunk groups copied by the DMA engines (verify: spans of its ring; 0 for
                             restore, whose kernel reads the host image itself) */
-    float copy_ms;       /* first image copy start to last image copy end (restore: first kernel
-                            start to last kernel end) */
+    float copy_ms;       /* first image copy start to last image copy end (direct_d2h: the kernel's
+                            copies included; restore: first kernel start to last kernel end) */
     float total_ms;      /* operation start (after the trigger) to its last event; for a
                             snapshot: to its commit (image and sums in host memory; with
                             pageable images, the last group landed in the image) */

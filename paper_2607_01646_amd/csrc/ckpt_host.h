@@ -122,6 +122,7 @@ struct RecRes {
     unsigned long long* d_sums = nullptr;
     std::vector<hipEvent_t> k0, k1;     // timing: around each pack launch
     hipEvent_t t0 = nullptr;
+    hipEvent_t t_pieces = nullptr;      // timing: after the kernel copy of the first group's small pieces
     hipEvent_t t_red = nullptr;         // timing: after the chunk-sum reduce and its release
     bool in_kernel = false;             // this snapshot's kernels write the host image themselves (no copies):
                                         // it is done when dep_sums is 0

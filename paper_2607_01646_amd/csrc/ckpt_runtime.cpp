@@ -315,6 +315,7 @@ void destroy_res(RecRes* r)
     for (auto e : r->k1)
         if (e) (void)hipEventDestroy(e);
     if (r->t0) (void)hipEventDestroy(r->t0);
+    if (r->t_pieces) (void)hipEventDestroy(r->t_pieces);
     if (r->t_red) (void)hipEventDestroy(r->t_red);
     for (auto s : r->dep)
         if (s.handle) hsa_signal_destroy(s);
@@ -382,6 +383,7 @@ ckpt_status new_res(ckpt_ctx* c, RecRes** out)
             if (in_halves(c, g)) st = gpu_consumed_signal(c, &r->piece_done[g]);
     }
     if (st == CKPT_OK) st = make_event(c, &r->t0, true);
+    if (st == CKPT_OK) st = make_event(c, &r->t_pieces, true);
     if (st == CKPT_OK) st = make_event(c, &r->t_red, true);
     if (st == CKPT_OK) st = gpu_only_signal(c, &r->dep_lead, &r->dep_lead_val);
     if (st == CKPT_OK) st = gpu_consumed_signal(c, &r->lead_done);
@@ -1391,12 +1393,18 @@ ckpt_status ckpt_last_timing(ckpt_ctx* c, uint32_t which, ckpt_timing* out)
             t_start = std::min<uint64_t>(t_start, ct.start);
             t_end = std::max<uint64_t>(t_end, ct.end);
         }
-        t.copy_ms = (ok && t_end > t_start) ? (float)((double)(t_end - t_start) * 1e3 / (double)c->ts_freq) : -1.f;
+        // In direct mode a kernel copies the first group's small pieces ahead
+        // of its DMA (the later groups' run beside the group before).
+        const float pieces = c->direct && c->small_first[1] ? elapsed(r->k1[0], r->t_pieces) : 0.f;
+        ok = ok && pieces >= 0.f;
+        t.copy_ms = (ok && t_end > t_start) ? pieces + (float)((double)(t_end - t_start) * 1e3 / (double)c->ts_freq)
+                                            : -1.f;
         // Trigger to commit: the first launch's pack, then from its copy's
         // start to the commit -- the last of: the last group copy's end, the
         // sums copy's end and, with pageable images, the last group landing in
         // the image (and the file record).  One clock throughout except the
-        // first pack (HIP events); the first copy starts right after it.
+        // first pack and piece copy (HIP events); the first DMA starts right
+        // after them.
         t.total_ms = -1.f;
         hsa_amd_profiling_async_copy_time_t cs;
         if (ok && t_end > t_start && hsa_amd_profiling_get_async_copy_time(r->done, &cs) == HSA_STATUS_SUCCESS) {
@@ -1404,7 +1412,7 @@ ckpt_status ckpt_last_timing(ckpt_ctx* c, uint32_t which, ckpt_timing* out)
             if (best->bounce) commit = std::max<uint64_t>(commit, r->landed_ts.load(std::memory_order_relaxed));
             if (best->file) commit = std::max<uint64_t>(commit, r->recorded_ts.load(std::memory_order_relaxed));
             const float k0 = elapsed(r->k0[0], r->k1[0]);
-            if (k0 >= 0.f) t.total_ms = k0 + (float)((double)(commit - t_start) * 1e3 / (double)c->ts_freq);
+            if (k0 >= 0.f) t.total_ms = k0 + pieces + (float)((double)(commit - t_start) * 1e3 / (double)c->ts_freq);
         }
         t.kernel_bytes = c->direct ? c->payload : 2 * c->payload;
         t.copy_bytes = c->I;

@@ -141,6 +141,7 @@ ckpt_status issue_groups_direct(ckpt_ctx* c, SnapRec& r, hipStream_t after, uint
         e = launch_copy_pieces(c->d_small + c->small_first[g], c->small_first[g + 1] - c->small_first[g], himg,
                                c->s_pack);
         if (e != hipSuccess) return fail(c, CKPT_EHIP, "piece copy launch failed: %s", hipGetErrorString(e));
+        if (r.timed && g == 0 && c->small_first[1]) HIPCHK(c, hipEventRecord(res->t_pieces, c->s_pack));
         // A copied group needs no event: its copies wait for the release that
         // the next launch stores once this one has finished, so the counter
         // the gate waits for implies the group's sums have been read too.
