@@ -133,8 +133,8 @@ typedef struct {
     uint32_t direct_d2h;           /* nonzero = no device staging for snapshots: the DMA engines copy
                                       each fragment from the live tensors straight into its place in
                                       the host image (or the bounce ring; into a pinned image a
-                                      kernel copies the pieces of up to 512 KiB, which the engines
-                                      would take longer to take up than to copy), the padding between
+                                      kernel copies the smallest pieces, which the engines would take
+                                      longer to take up than to copy), the padding between
                                       fragments is zeroed on the host, and the snapshot's kernels
                                       only compute the chunk sums (reading the fragments once: half
                                       the HBM traffic of pack + copy, and no device image).  The
@@ -341,6 +341,11 @@ ckpt_status ckpt_debug_tile_plan(const uint64_t* nbytes, uint32_t n, uint64_t ch
 ckpt_status ckpt_debug_direct_plan(const uint64_t* nbytes, uint32_t n, uint64_t chunk_bytes, uint32_t align_bytes,
                                    uint64_t group_bytes, uint64_t* counts, uint64_t* pieces, uint64_t* gaps,
                                    uint64_t* piece_first, uint64_t* gap_first);
+
+/* Test access to which of the pieces of one chunk group (nbytes[n], in image
+ * order) direct D2H into pinned images copies in a kernel (host-only):
+ * by_kernel[k] is 1 for those.  Errors: EINVAL. */
+ckpt_status ckpt_debug_kernel_pieces(const uint64_t* nbytes, uint32_t n, uint8_t* by_kernel);
 
 /* Test access to how the copy of one staged chunk group is dealt to the DMA
  * engines (host-only): spans (room for 9 words) receives n requests, in the

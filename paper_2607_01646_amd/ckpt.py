@@ -101,6 +101,7 @@ def lib():
             "ckpt_last_timing": ([vp, u32, P(ckpt_timing)], i32),
             "ckpt_plan": ([P(u64), u32, u64, u32, P(u64), P(u64), P(u64)], i32),
             "ckpt_debug_tile_plan": ([P(u64), u32, u64, u32, P(u64), P(u64), P(u32), P(u32)], i32),
+            "ckpt_debug_kernel_pieces": ([P(u64), u32, P(C.c_uint8)], i32),
             "ckpt_debug_copy_plan": ([u64, u32, u32, P(u64), P(u32)], i32),
             "ckpt_debug_direct_plan": ([P(u64), u32, u64, u32, u64, P(u64), P(u64), P(u64), P(u64), P(u64)], i32),
             "ckpt_last_error": ([vp], C.c_char_p),
@@ -354,6 +355,14 @@ def ckpt_debug_tile_plan(nbytes, chunk_bytes=0, align_bytes=0):
     _check(None, lib().ckpt_debug_tile_plan(_u64p(nb), nb.size, chunk_bytes, align_bytes, C.byref(tb),
                                             C.byref(nt), _u32p(tf), _u32p(tl)))
     return tb.value, tf, tl
+
+
+def ckpt_debug_kernel_pieces(nbytes):
+    """Which of one chunk group's pieces direct D2H copies in a kernel (bool)."""
+    nb = np.ascontiguousarray(np.asarray(nbytes, dtype=np.uint64))
+    out = np.zeros(nb.size, dtype=np.uint8)
+    _check(None, lib().ckpt_debug_kernel_pieces(_u64p(nb), nb.size, out.ctypes.data_as(C.POINTER(C.c_uint8))))
+    return out.astype(bool)
 
 
 def ckpt_debug_copy_plan(group_bytes, engines=2, led=False):

@@ -119,15 +119,24 @@ struct Piece {
 };
 
 // Copy pieces[0, n_pieces) (device memory) into the pinned host image img:
-// the pieces of up to kKernelPiece bytes, which the DMA engines would spend
-// more time taking up than copying.  A DMA request costs its engine ~9 us, in
-// which the link moves 512 KiB; below that a kernel of few workgroups is
-// faster.  Direct snapshot in us by largest kernel piece, none / 32 / 128 /
-// 512 KiB / 2 MiB: 1.5 GB in 400 fragments 29032 / 27899 / 27902 / 27897 /
-// 28062, 512 MiB in 1024 ragged ones 19178 / 14145 / 13016 / 11758 / 10708,
-// 100 MiB in 300 4749 / 3198 / 2898 / 2537 / 2408 (pieces over 512 KiB stay
-// with the engines all the same: they leave the compute units alone).
-constexpr uint64_t kKernelPiece = 512ull << 10;
+// the smallest pieces of a group, which the DMA engines would spend more time
+// taking up than copying (a request costs its engine ~9 us, in which the link
+// moves 512 KiB).  The kernel holds compute units while it writes over the
+// link, and a GEMM with one workgroup for every unit loses about as long as it
+// runs, so past kKernelPiece bytes a piece, where that loss is a tenth of what
+// the snapshot gains, it gets at most 1 / kKernelShare of a group's bytes.
+// Snapshot in ms / what 4096^3 bf16 products beside it lost by it: nothing by
+// the kernel; every piece of up to 512 KiB; those up to 32 KiB and a share of
+// 1/16, 1/32, 1/64 (this):
+//   1500 x 512 KiB            20.7/0.7  14.6/13.5  20.1/1.8  20.3/1.5  20.4/1.1
+//   2000 x 128 KiB            13.6/0.1   4.9/4.5   12.8/0.8  13.2/0.6  13.4/0.4
+//   2000 x 32 KiB             10.4/0.3   1.3/1.2        as every piece
+//   512 MiB in 1024 ragged    12.6/0.44 10.0/1.54  10.1/1.2  10.1/0.8  10.3/0.40
+//   100 MiB in 300 ragged      3.0/0.08  2.0/0.24   2.1/0.17  2.1/0.07  2.2/0.04
+//   1.5 GB of a GPT in 400    27.6/1.3  27.3/1.3        as every piece
+constexpr uint64_t kKernelPiece = 32ull << 10;
+constexpr uint64_t kKernelPieceMax = 512ull << 10;
+constexpr uint64_t kKernelShare = 64;
 constexpr uint32_t kPieceGrid = 64;
 hipError_t launch_copy_pieces(const Piece* pieces, uint64_t n_pieces, uint8_t* img, hipStream_t s);
 

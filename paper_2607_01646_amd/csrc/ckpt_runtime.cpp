@@ -153,10 +153,32 @@ bool direct_plan(const uint64_t* off, const uint64_t* nb, uint32_t n, uint64_t I
     return true;
 }
 
-// Direct D2H into pinned images: move the small pieces of c->pieces, except
-// each group's last (whose copy signals the group's), to `small`.  With
-// pageable images the ring slot a group goes through is not known when its
-// kernels are enqueued, so the engines copy everything.
+// Which of a group's pieces (their bytes, in image order) a kernel copies and
+// not the engines: every one of up to kKernelPiece bytes, and larger ones of up
+// to kKernelPieceMax, smallest first, while all of them are at most
+// 1 / kKernelShare of the group.  Never the last, whose copy signals the
+// group's.
+std::vector<uint8_t> kernel_pieces(const std::vector<uint64_t>& n)
+{
+    std::vector<uint8_t> by_kernel(n.size(), 0);
+    std::vector<size_t> order;
+    uint64_t total = 0, taken = 0;
+    for (size_t k = 0; k < n.size(); ++k) {
+        total += n[k];
+        if (k + 1 < n.size() && n[k] <= kKernelPieceMax) order.push_back(k);
+    }
+    std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return n[a] < n[b]; });
+    for (size_t k : order) {
+        if (n[k] > kKernelPiece && taken + n[k] > total / kKernelShare) break;
+        taken += n[k];
+        by_kernel[k] = 1;
+    }
+    return by_kernel;
+}
+
+// Direct D2H into pinned images: move the pieces of c->pieces that a kernel
+// copies to `small`.  With pageable images the ring slot a group goes through
+// is not known when its kernels are enqueued, so the engines copy everything.
 void split_small(ckpt_ctx* c, std::vector<Piece>& small)
 {
     std::vector<Piece> large;
@@ -165,9 +187,12 @@ void split_small(ckpt_ctx* c, std::vector<Piece>& small)
     for (uint64_t g = 0; g < c->n_groups; ++g) {
         first[g] = large.size();
         c->small_first[g] = small.size();
-        for (uint64_t k = c->piece_first[g]; k < c->piece_first[g + 1]; ++k)
-            (!c->bounce && c->pieces[k].n <= kKernelPiece && k + 1 < c->piece_first[g + 1] ? small : large)
-                .push_back(c->pieces[k]);
+        const uint64_t p0 = c->piece_first[g], p1 = c->piece_first[g + 1];
+        std::vector<uint64_t> n;
+        for (uint64_t k = p0; k < p1; ++k) n.push_back(c->pieces[k].n);
+        const std::vector<uint8_t> by_kernel = kernel_pieces(n);
+        for (uint64_t k = p0; k < p1; ++k)
+            (!c->bounce && by_kernel[k - p0] ? small : large).push_back(c->pieces[k]);
     }
     first[c->n_groups] = large.size();
     c->small_first[c->n_groups] = small.size();
@@ -1484,6 +1509,14 @@ ckpt_status ckpt_debug_direct_plan(const uint64_t* nbytes, uint32_t n, uint64_t 
     }
     std::memcpy(piece_first, p0.data(), 8 * p0.size());
     std::memcpy(gap_first, g0.data(), 8 * g0.size());
+    return CKPT_OK;
+}
+
+ckpt_status ckpt_debug_kernel_pieces(const uint64_t* nbytes, uint32_t n, uint8_t* by_kernel)
+{
+    if (!nbytes || n == 0 || !by_kernel) return CKPT_EINVAL;
+    const std::vector<uint8_t> k = kernel_pieces(std::vector<uint64_t>(nbytes, nbytes + n));
+    std::memcpy(by_kernel, k.data(), n);
     return CKPT_OK;
 }
 

@@ -168,6 +168,26 @@ def test_copy_plan_gives_each_engine_half(P, n, led):
     assert [b for _, b, _ in P.ckpt_debug_copy_plan(n, 1, led)] == [n]
 
 
+@pytest.mark.parametrize("seed", range(6))
+def test_kernel_copies_leave_training_the_compute_units(P, seed):
+    """Direct D2H: a GEMM beside the kernel that copies pieces loses about as
+    long as that kernel runs, so past pieces of 32 KiB its bytes are at most
+    1/64 of the group's, smallest pieces first."""
+    rng = np.random.default_rng(seed)
+    n = [np.full(1500, 512 << 10), np.full(2000, 128 << 10), np.full(2000, 32 << 10), np.array([5]),
+         np.exp(rng.uniform(np.log(1024), np.log(64 << 20), 300)).astype(np.int64),
+         rng.integers(1, 1 << 20, 700)][seed]
+    k = P.ckpt_debug_kernel_pieces(n)
+    assert not k[-1]
+    assert np.all(k[:-1][n[:-1] <= 32 << 10]) and not np.any(k[n > 512 << 10])
+    big = k & (n > 32 << 10)
+    assert not big.any() or n[k].sum() <= n.sum() // 64
+    left = n[:-1][~k[:-1]]  # what the engines copy is no smaller, and the next of it would be too much
+    if left.size and left.min() <= 512 << 10:
+        assert not k.any() or n[k].max() <= left.min()
+        assert n[k].sum() + left.min() > n.sum() // 64
+
+
 def test_plan_rejects_bad_geometry(P):
     with pytest.raises(P.CkptError):
         P.ckpt_plan([10, 20], 1000, 256)  # chunk not a multiple of the alignment
