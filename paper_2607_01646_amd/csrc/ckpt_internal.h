@@ -138,7 +138,7 @@ constexpr uint64_t kKernelPiece = 32ull << 10;
 constexpr uint64_t kKernelPieceMax = 512ull << 10;
 constexpr uint64_t kKernelShare = 64;
 constexpr uint32_t kPieceGrid = 64;
-hipError_t launch_copy_pieces(const Piece* pieces, uint64_t n_pieces, uint8_t* img, hipStream_t s);
+hipError_t launch_copy_pieces(const Piece* pieces, uint64_t n_pieces, uint8_t* img, uint32_t grid_cap, hipStream_t s);
 
 // Store 0 into *signal_value (an HSA signal's value) once the work enqueued
 // on s before this call has completed.

@@ -908,11 +908,11 @@ hipError_t launch_tile_table(const FragDev* frags, uint32_t n, const Geometry& g
     return hipGetLastError();
 }
 
-hipError_t launch_copy_pieces(const Piece* pieces, uint64_t n_pieces, uint8_t* img, hipStream_t s)
+hipError_t launch_copy_pieces(const Piece* pieces, uint64_t n_pieces, uint8_t* img, uint32_t grid_cap, hipStream_t s)
 {
     if (n_pieces == 0) return hipSuccess;
-    hipLaunchKernelGGL(copy_pieces_kernel, dim3((uint32_t)std::min<uint64_t>(n_pieces, kPieceGrid)), dim3(256), 0, s,
-                       pieces, n_pieces, img);
+    const uint32_t grid = (uint32_t)std::min<uint64_t>(n_pieces, std::min(grid_cap, kPieceGrid));
+    hipLaunchKernelGGL(copy_pieces_kernel, dim3(grid), dim3(256), 0, s, pieces, n_pieces, img);
     return hipGetLastError();
 }
 

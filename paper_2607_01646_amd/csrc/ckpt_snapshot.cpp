@@ -139,7 +139,7 @@ ckpt_status issue_groups_direct(ckpt_ctx* c, SnapRec& r, hipStream_t after, uint
         }
         // The group's small pieces, before the release that its copies wait for.
         e = launch_copy_pieces(c->d_small + c->small_first[g], c->small_first[g + 1] - c->small_first[g], himg,
-                               c->s_pack);
+                               c->grid_cap, c->s_pack);
         if (e != hipSuccess) return fail(c, CKPT_EHIP, "piece copy launch failed: %s", hipGetErrorString(e));
         if (r.timed && g == 0 && c->small_first[1]) HIPCHK(c, hipEventRecord(res->t_pieces, c->s_pack));
         // A copied group needs no event: its copies wait for the release that
@@ -390,7 +390,7 @@ ckpt_status issue_in_kernel(ckpt_ctx* c, SnapRec& r, hipStream_t after)
         HIPCHK(c, hipStreamWaitValue64(s, c->d_area_done, c->area_seq[0], hipStreamWaitValueGte, ~0ull));
     unsigned long long* sums = (unsigned long long*)c->h_sums[r.buf];
     hipError_t e;
-    if (c->C <= kSmallSpan) {
+    if (c->C <= kSmallSpan && c->n_chunks <= c->grid_cap) { // one workgroup per chunk
         const bool fused = c->n_chunks <= kReleaseChunks;
         e = launch_pack_chunks(c->d_frags, c->d_tile_src, c->geo, c->h_img[r.buf], sums, s,
                                fused ? res->dep_sums_val : nullptr, fused ? c->d_ticket : nullptr);

@@ -2,6 +2,8 @@
 restore with fewer tiles than the launch has workgroups, as many and more, in
 every mode, and bytes that the host changes between two calls; small images
 and small pieces written by the kernel; and verify, which does neither."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -196,3 +198,22 @@ def test_timing_counts_the_pieces_a_kernel_copies(level):
             t = P.ckpt_last_timing(ck.ctx, P.CKPT_OP_SNAPSHOT)
             # 66.6 MB; 16 lanes of PCIe 5.0 carry 63 GB/s
             assert t["copy_bytes"] / 64e6 < t["copy_ms"] < t["total_ms"] < 100, t
+
+
+@pytest.mark.parametrize("chunk", [65536, 1 << 20])  # packed by chunks, by tiles
+def test_grid_blocks_bounds_what_writes_the_image(chunk):
+    """grid_blocks caps these kernels too: one workgroup has 8 KiB on the
+    link, which wants 200, and takes several times as long."""
+    tensors, host = random_byte_fragments([2 << 20], seed=chunk)
+
+    def seconds(grid):
+        best = []
+        ck, _ = snapshot_and_check(tensors, host, chunk, 256, grid=grid)
+        for _ in range(5):
+            t = time.perf_counter()
+            ck.wait_committed(ck.snapshot(step=1))
+            best.append(time.perf_counter() - t)
+        ck.close()
+        return min(best)
+
+    assert seconds(1) > 2 * seconds(0)
