@@ -142,16 +142,18 @@ _pack = None
 
 
 def _native_pack():
-    """(_ckpt_py.pack_noalloc, address of ckpt_pack_noalloc)."""
+    """(_ckpt_py.pack_noalloc, address of ckpt_pack_noalloc); where the module
+    was not built for this Python and torch, a pack_noalloc that leaves every
+    call to the Python code."""
     global _pack
     if _pack is None:
         fn = C.cast(lib().ckpt_pack_noalloc, C.c_void_p).value
         try:
             from . import _ckpt_py
-        except ImportError as e:
-            raise RuntimeError("_ckpt_py.so is not built for this Python; run "
-                               "`python -c 'import __graft_entry__ as g; g.build()'`") from e
-        _pack = (_ckpt_py.pack_noalloc, fn)
+            usable = torch.__version__.split("+")[0] == _ckpt_py.torch_version
+        except ImportError:
+            usable = False
+        _pack = (_ckpt_py.pack_noalloc if usable else lambda *args: None, fn)
     return _pack
 
 
@@ -502,7 +504,8 @@ def ckpt_pack_noalloc(tensors, image, sums, chunk_bytes=0, align_bytes=0, stream
         if got[0] != CKPT_OK:
             raise CkptError(got[0], (lib().ckpt_last_error(None) or b"").decode())
         return got[1], got[2]
-    # Arguments that are not plain tensors and numbers, and those refused here.
+    # Arguments that are not plain tensors and numbers, and those refused here;
+    # every call where there is no native module.
     n = len(tensors)
     arr = (ckpt_tensor * max(n, 1))()
     for i, t in enumerate(tensors):

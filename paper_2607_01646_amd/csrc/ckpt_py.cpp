@@ -4,6 +4,7 @@
 #include <Python.h>
 
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/version.h>
 
 #include <vector>
 
@@ -76,4 +77,11 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_ckpt_py", nullptr, -1, methods, n
 
 } // namespace
 
-PyMODINIT_FUNC PyInit__ckpt_py() { return PyModule_Create(&module); }
+// torch_version: what it was compiled against; another torch lays tensors out
+// differently.
+PyMODINIT_FUNC PyInit__ckpt_py()
+{
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", TORCH_VERSION) != 0) Py_CLEAR(m);
+    return m;
+}

@@ -2,9 +2,11 @@
 point, and its host-only planning matches the oracle's layout (CPU only)."""
 import os
 import re
+import sys
 
 import numpy as np
 import pytest
+import torch
 from hypothesis import HealthCheck, given, settings
 from hypothesis import strategies as st
 
@@ -302,3 +304,20 @@ def test_layout_and_tile_plan_properties(P, layout):
     for t in range(len(tf)):
         x0, x1 = t * tb, min((t + 1) * tb, I) - 1
         assert tf[t] == holder(x0) and tl[t] == holder(x1), t
+
+
+@pytest.mark.parametrize("other", ["missing", "another torch's"])
+def test_noalloc_pack_without_its_native_module(P, monkeypatch, other):
+    """The Python path takes the call: here it refuses a host tensor."""
+    from paper_2607_01646_amd import _ckpt_py, ckpt
+
+    monkeypatch.setattr(ckpt, "_pack", None)
+    if other == "missing":
+        monkeypatch.delattr(sys.modules["paper_2607_01646_amd"], "_ckpt_py", raising=False)
+        monkeypatch.setitem(sys.modules, "paper_2607_01646_amd._ckpt_py", None)
+    else:
+        monkeypatch.setattr(_ckpt_py, "torch_version", "1.0.0")
+    t = torch.zeros(64, dtype=torch.uint8)
+    with pytest.raises(ValueError, match="not a device tensor"):
+        P.ckpt_pack_noalloc([t], t, t, stream=0, device=0)
+    assert ckpt._native_pack()[0]() is None
