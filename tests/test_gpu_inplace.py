@@ -23,21 +23,23 @@ TILE = 8192
 @pytest.mark.parametrize("mode", [dict(), dict(staging=8 * TILE), dict(direct=True), dict(bounce=8 * TILE)])
 @pytest.mark.parametrize("tiles", [1, 23, 24, 25, 160, 161, 500])
 def test_host_changes_between_calls_are_seen(tiles, mode):
+    """A changed byte of a fragment is found and restored as it is now; one of
+    the padding behind the last fragment is found and reaches no fragment."""
     chunk = 4 * TILE
-    tensors, host = random_byte_fragments([tiles * TILE - 5 * TILE // 3] * (tiles > 1) + [5 * TILE // 3 - 7], seed=tiles)
+    last = 2 * TILE // 3 - 7  # and 178 bytes of padding
+    tensors, host = random_byte_fragments([tiles * TILE - (last + 178), last], seed=tiles)
     ck, snap = snapshot_and_check(tensors, host, chunk, 256, group=chunk, **mode)
     img, sums = ck.host_image(snap)
+    assert img.size == tiles * TILE and int(ck.offsets[-1]) + last == img.size - 178
     before = img.copy()
-    for _ in range(2):
-        at = img.size - 9
+    for at in (img.size - 9, img.size - 179, 0):
         img[at] ^= 0x10
         c = at // chunk
         assert ck.verify() == [c]
         garbage_fill(tensors)
         assert ck.restore() == [c]
         got = O.pack([host_bytes(t) for t in tensors], 256, chunk)[0]
-        pad = got != img  # every byte is written back, padding aside
-        assert not pad.any() or at >= int(ck.offsets[-1]) + tensors[-1].numel()
+        assert np.array_equal(got[:-178], img[:-178]) and not got[-178:].any()
         img[at] ^= 0x10
         assert ck.verify() == []
         garbage_fill(tensors)
