@@ -32,9 +32,9 @@
 // address of its bytes itself.  The whole pack of a 14.2 GB shard: 4478 us
 // with 256 lanes x 2 vectors and the two lookups, 4460 with the entry alone,
 // 4385 with 512 lanes x 1.
-// A tile inside one fragment takes an unrolled non-temporal stream, with
-// unaligned 16-byte accesses on the fragment's side when the fragment is not
-// 16-byte aligned; otherwise each vector finds its fragment (binary search
+// A tile inside one fragment takes an unrolled non-temporal stream; when the
+// fragment is not 16-byte aligned its side reads the 4-byte words that hold
+// each vector (ld_any) and stores unaligned vectors.  Otherwise each vector finds its fragment (binary search
 // over the tile's fragment offsets in LDS), loads aligned 16-byte blocks and
 // funnel-shifts them when the fragment is misaligned, masks the fragment
 // tail and writes zeros for padding.
@@ -221,16 +221,31 @@ __device__ __forceinline__ void st(u32x4 v, u32x4* p)
     else *p = v;
 }
 
-// 16 bytes at any address.  Unaligned vector accesses are one instruction on
-// gfx950; the memory pipe splits those that cross a cache line.
+// Vector accesses at any address are one instruction on gfx950; the memory
+// pipe splits those that cross a cache line, and takes loads that start inside
+// a 4-byte word more slowly.
 typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+typedef unsigned int u32x4_words __attribute__((ext_vector_type(4), aligned(4)));
 
-template <bool NT>
+// 16 bytes at any address, from the 4-byte words that hold them: no word
+// without one of these bytes is read.  Cached, since neighbouring lanes share
+// words and lines.  Pack of one fragment of 100 MiB / 1 GiB, in us, that
+// starts at an odd or odd half word: one unaligned non-temporal load 45.2 /
+// 368, aligned pairs of vectors 39.0 / 352, this 39.1 / 351; at a word: 41.7 /
+// 335, 38.3 / 350, 38.5 / 341 (a multiple of 16, which does not come here:
+// 43.5 / 332).  Sums of 1 GiB 203, 189, 182; 164, 250, 176 (163).
 __device__ __forceinline__ u32x4 ld_any(const uint8_t* p)
 {
-    const u32x4_any* q = reinterpret_cast<const u32x4_any*>(p);
-    if (NT) return __builtin_nontemporal_load(q);
-    return *q;
+    const uint32_t sh = (uint32_t)(uintptr_t)p & 3;
+    const u32x4 v = *reinterpret_cast<const u32x4_words*>(p - sh);
+    if (sh == 0) return v;
+    const uint32_t w = *reinterpret_cast<const uint32_t*>(p - sh + 16);
+    u32x4 r;
+    r.x = __builtin_amdgcn_alignbyte(v.y, v.x, sh);
+    r.y = __builtin_amdgcn_alignbyte(v.z, v.y, sh);
+    r.z = __builtin_amdgcn_alignbyte(v.w, v.z, sh);
+    r.w = __builtin_amdgcn_alignbyte(w, v.w, sh);
+    return r;
 }
 
 // One wave's slice of a tile: the n <= 64 * UNROLL vectors at s (copied to d
@@ -246,7 +261,7 @@ __device__ __forceinline__ unsigned long long slice_stream(const uint8_t* s, uin
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u)
         if (lane + u * 64 < n)
-            r[u] = SRC_ANY ? ld_any<NTL>(s + 16 * (lane + u * 64))
+            r[u] = SRC_ANY ? ld_any(s + 16 * (lane + u * 64))
                            : ld<NTL>(reinterpret_cast<const u32x4*>(s) + lane + u * 64);
     unsigned long long acc = 0;
 #pragma unroll
@@ -437,7 +452,7 @@ __device__ __forceinline__ unsigned long long move_vector(const Args& a, uint64_
             if ((e & 15) == 0) st_stream(r, reinterpret_cast<u32x4*>(fr));
             else *reinterpret_cast<u32x4_any*>(fr) = r;
         } else {
-            r = ld_any<true>(fr);
+            r = ld_any(fr);
             if (MODE == PACK) st_stream(r, win);
         }
     } else {

@@ -100,6 +100,24 @@ def test_more_tiles_than_a_dispatch_has_workgroups(direct):
     ck.close()
 
 
+@pytest.mark.parametrize("shift", [1, 2, 3])
+def test_fragments_inside_a_word_are_read_at_the_rate_of_words(shift):
+    """One unaligned load per vector took a quarter longer than a fragment that
+    starts at a 4-byte word."""
+    flat = torch.zeros((1 << 30) + 64, dtype=torch.uint8, device="cuda")
+
+    def sums_ms(at):
+        with P.Checkpointer([flat[at:at + (1 << 30)]], chunk_bytes=1 << 20, direct=True) as ck:
+            P.ckpt_set_timing(ck.ctx, 1)
+            ms = []
+            for k in range(5):
+                ck.wait_committed(ck.snapshot(step=k))
+                ms.append(P.ckpt_last_timing(ck.ctx, P.CKPT_OP_SNAPSHOT)["kernel_ms"])
+            return min(ms)
+
+    assert sums_ms(4 + shift) < 1.12 * sums_ms(4)
+
+
 @pytest.mark.parametrize("shift", [0, 3, 8, 14])
 def test_unaligned_fragments_without_allocation(shift):
     _, views = shifted_views(shift, 77 + shift)
