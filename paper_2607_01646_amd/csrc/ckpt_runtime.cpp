@@ -468,13 +468,14 @@ bool pump_failed(ckpt_ctx* c, std::string* why)
     return c->pump->failed;
 }
 
-// Poll a signal that only the GPU is told about until it is 0; false after
-// the deadline.  The first 100 us without sleeping: a sleep of 20 us takes
-// about 75, and the last of a snapshot's signals is usually a few away.
-bool poll_until(hsa_signal_t sig, std::chrono::steady_clock::time_point deadline)
+// Poll until done(); false after the deadline.  The first 100 us without
+// sleeping: a sleep of 20 us takes about 75, and the last steps of a snapshot
+// are usually a few away.
+template <class Done>
+bool poll_until(const Done& done, std::chrono::steady_clock::time_point deadline)
 {
     const auto spin = std::chrono::steady_clock::now() + std::chrono::microseconds(100);
-    while (hsa_signal_load_scacquire(sig) != 0) {
+    while (!done()) {
         const auto now = std::chrono::steady_clock::now();
         if (now > deadline) return false;
         if (now > spin) std::this_thread::sleep_for(std::chrono::microseconds(20));
@@ -489,7 +490,7 @@ ckpt_status wait_copies(ckpt_ctx* c, SnapRec& r)
     // one-second slices against our own deadline.
     const auto deadline = std::chrono::steady_clock::now() + std::chrono::seconds(120);
     if (r.res->in_kernel) { // a signal with no event behind it, stored by the GPU
-        if (!poll_until(r.res->dep_sums, deadline))
+        if (!poll_until([&] { return hsa_signal_load_scacquire(r.res->dep_sums) == 0; }, deadline))
             return fail(c, CKPT_EHIP, "snapshot %llu: not packed after 120 s", (unsigned long long)r.id);
         return CKPT_OK;
     }
@@ -500,22 +501,17 @@ ckpt_status wait_copies(ckpt_ctx* c, SnapRec& r)
     // polls their values (the engines run the groups in order, so this
     // rarely finds one still pending once the sums have landed).
     for (uint32_t g = 0; g < r.groups_copied; ++g)
-        if (!poll_until(r.res->flagged[g], deadline))
+        if (!poll_until([&] { return hsa_signal_load_scacquire(r.res->flagged[g]) == 0; }, deadline))
             return fail(c, CKPT_EHIP, "snapshot %llu: group %u not copied after 120 s", (unsigned long long)r.id, g);
     if (r.bounce) { // every group also has to reach the pageable image
-        while (r.res->landed.load(std::memory_order_acquire) < r.groups_copied) {
-            if (std::chrono::steady_clock::now() > deadline)
-                return fail(c, CKPT_EHIP, "snapshot %llu: image not written after 120 s", (unsigned long long)r.id);
-            std::this_thread::sleep_for(std::chrono::microseconds(50));
-        }
+        if (!poll_until([&] { return r.res->landed.load(std::memory_order_acquire) >= r.groups_copied; }, deadline))
+            return fail(c, CKPT_EHIP, "snapshot %llu: image not written after 120 s", (unsigned long long)r.id);
         std::string why;
         if (r.res->failed.load(std::memory_order_acquire) || pump_failed(c, &why))
             return fail(c, CKPT_EHIP, "snapshot %llu: bounce copy failed: %s", (unsigned long long)r.id, why.c_str());
-        while (r.file && !r.aborted && !r.res->recorded.load(std::memory_order_acquire)) {
-            if (std::chrono::steady_clock::now() > deadline)
-                return fail(c, CKPT_EHIP, "snapshot %llu: commit record not written after 120 s", (unsigned long long)r.id);
-            std::this_thread::sleep_for(std::chrono::microseconds(50));
-        }
+        if (r.file && !r.aborted &&
+            !poll_until([&] { return r.res->recorded.load(std::memory_order_acquire); }, deadline))
+            return fail(c, CKPT_EHIP, "snapshot %llu: commit record not written after 120 s", (unsigned long long)r.id);
     }
     return CKPT_OK;
 }
