@@ -350,10 +350,12 @@ ckpt_status ckpt_debug_kernel_pieces(const uint64_t* nbytes, uint32_t n, uint8_t
 /* Test access to how the copy of one staged chunk group is dealt to the DMA
  * engines (host-only): spans (room for 9 words) receives n requests, in the
  * order in which they are issued, of 3 words each: first byte in the group,
- * bytes, engine (0 or 1, of the `engines` in use).  led = the group's first
- * bytes may go ahead of the rest (a snapshot's first group, full staging).
+ * bytes, engine (0 or 1, of the `engines` in use).  groups = how many the
+ * image has (pinned images); led = the group's first bytes may go ahead of the
+ * rest (a snapshot's first group, full staging).
  * Errors: EINVAL. */
-ckpt_status ckpt_debug_copy_plan(uint64_t group_bytes, uint32_t engines, uint32_t led, uint64_t* spans, uint32_t* n);
+ckpt_status ckpt_debug_copy_plan(uint64_t group_bytes, uint32_t engines, uint32_t groups, uint32_t led,
+                                 uint64_t* spans, uint32_t* n);
 
 /* ---- Crash-surviving local snapshots (Sec. V-B: the host copy lets a
  * rank come back from its own host memory alone; Sec. V-C: a local reset

@@ -102,7 +102,7 @@ def lib():
             "ckpt_plan": ([P(u64), u32, u64, u32, P(u64), P(u64), P(u64)], i32),
             "ckpt_debug_tile_plan": ([P(u64), u32, u64, u32, P(u64), P(u64), P(u32), P(u32)], i32),
             "ckpt_debug_kernel_pieces": ([P(u64), u32, P(C.c_uint8)], i32),
-            "ckpt_debug_copy_plan": ([u64, u32, u32, P(u64), P(u32)], i32),
+            "ckpt_debug_copy_plan": ([u64, u32, u32, u32, P(u64), P(u32)], i32),
             "ckpt_debug_direct_plan": ([P(u64), u32, u64, u32, u64, P(u64), P(u64), P(u64), P(u64), P(u64)], i32),
             "ckpt_last_error": ([vp], C.c_char_p),
             "ckpt_image_file": ([vp, C.c_char_p, u32], i32),
@@ -367,11 +367,11 @@ def ckpt_debug_kernel_pieces(nbytes):
     return out.astype(bool)
 
 
-def ckpt_debug_copy_plan(group_bytes, engines=2, led=False):
+def ckpt_debug_copy_plan(group_bytes, engines=2, led=False, groups=1):
     """[(first byte, bytes, engine)] of the requests that copy one staged
     chunk group."""
     spans, n = (C.c_uint64 * 9)(), C.c_uint32()
-    _check(None, lib().ckpt_debug_copy_plan(group_bytes, engines, int(led), spans, C.byref(n)))
+    _check(None, lib().ckpt_debug_copy_plan(group_bytes, engines, groups, int(led), spans, C.byref(n)))
     return [tuple(spans[3 * k:3 * k + 3]) for k in range(n.value)]
 
 

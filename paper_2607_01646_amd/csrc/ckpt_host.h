@@ -48,6 +48,16 @@ constexpr int kMaxEngines = 2;
 // not the same for the two), both together fill the link on each; below, a
 // second request costs more than it gives.
 constexpr uint64_t kSplitCopy = 8ull << 20;
+// Of several pinned groups smaller than this, alternate ones already keep both
+// engines busy, and a second request for each costs more.  Whole / in halves, us:
+// 64 MiB in groups of 8 MiB 1295 / 1335, of 16 1280 / 1295, 120 in 24 2320 /
+// 2355-2560, 128 in 32 2460 / 2500-2680, 96 in 48 1885 / 1885.  (Pageable
+// images drain group by group: 64 MiB in groups of 16 MiB 1700 / 1580.)
+constexpr uint64_t kSplitGroup = 48ull << 20;
+inline bool split_copy(uint64_t n, int engines, uint64_t pinned_groups, uint64_t group_bytes)
+{
+    return engines > 1 && n >= kSplitCopy && (pinned_groups <= 1 || group_bytes >= kSplitGroup);
+}
 // The lead: 16 MiB keep the link busy for 290 us, in which the rest of a group
 // of 1 GiB is packed (330 us); groups of less than four leads gain nothing.
 // It is part of its engine's half, so that each engine still moves half of
@@ -64,9 +74,9 @@ struct CopySpan {
     uint64_t lo, n;
     int engine;
 };
-inline int copy_spans(uint64_t n, int engines, uint64_t lead, CopySpan out[3])
+inline int copy_spans(uint64_t n, bool halves, uint64_t lead, CopySpan out[3])
 {
-    const uint64_t half = engines > 1 && n >= kSplitCopy ? ((n / 2 + 4095) & ~4095ull) : n;
+    const uint64_t half = halves ? ((n / 2 + 4095) & ~4095ull) : n;
     int k = 0;
     if (lead) out[k++] = CopySpan{0, lead, 0};
     out[k++] = CopySpan{lead, half - lead, 0};
@@ -503,7 +513,7 @@ inline uint64_t group_hi(const ckpt_ctx* c, uint64_t g) { return std::min((g + 1
 // Whether group g's staged copy is dealt to two engines in halves.
 inline bool in_halves(const ckpt_ctx* c, uint64_t g)
 {
-    return c->n_d2h_engines > 1 && group_hi(c, g) - group_lo(c, g) >= kSplitCopy;
+    return split_copy(group_hi(c, g) - group_lo(c, g), c->n_d2h_engines, c->bounce ? 0 : c->n_groups, c->G * c->C);
 }
 // Bytes of the first group that a launch of their own packs ahead of the rest
 // (0: none), whole tiles; full-image staging only.

@@ -1516,11 +1516,14 @@ ckpt_status ckpt_debug_kernel_pieces(const uint64_t* nbytes, uint32_t n, uint8_t
     return CKPT_OK;
 }
 
-ckpt_status ckpt_debug_copy_plan(uint64_t group_bytes, uint32_t engines, uint32_t led, uint64_t* spans, uint32_t* n)
+ckpt_status ckpt_debug_copy_plan(uint64_t group_bytes, uint32_t engines, uint32_t groups, uint32_t led,
+                                 uint64_t* spans, uint32_t* n)
 {
-    if (!group_bytes || !engines || !spans || !n) return CKPT_EINVAL;
+    if (!group_bytes || !engines || !groups || !spans || !n) return CKPT_EINVAL;
     CopySpan sp[3];
-    *n = (uint32_t)copy_spans(group_bytes, (int)std::min<uint32_t>(engines, kMaxEngines),
+    *n = (uint32_t)copy_spans(group_bytes,
+                              split_copy(group_bytes, (int)std::min<uint32_t>(engines, kMaxEngines), groups,
+                                         group_bytes),
                               led && engines > 1 && group_bytes >= 4 * kLead ? kLead : 0, sp);
     for (uint32_t k = 0; k < *n; ++k) {
         spans[3 * k] = sp[k].lo;
