@@ -927,6 +927,7 @@ def overlap_leg(torch, P, W, wid, steps, link_d2h_gbps, ratios=(1.5,), base_step
             raise RuntimeError("checksum mismatch after the overlap run: %s" % bad)
         recovery = {"verify_GBps": round(tv["copy_bytes"] / tv["total_ms"] / 1e6, 2),
                     "restore_GBps": round(tr["copy_bytes"] / tr["total_ms"] / 1e6, 2),
+                    # 2 x payload over the kernel's time, which the host link bounds
                     "scatter_GBps": round(tr["kernel_bytes"] / tr["kernel_ms"] / 1e6, 1),
                     "note": "H2D + checks (+ scatter) of the newest committed snapshot, after the overlap run"}
     if shared is None:
@@ -1655,6 +1656,8 @@ def main():
                        "d2h_note": "DMA span of the timed snapshots (alone on the host link)",
                        "h2d_GBps": round(h2d_gbps, 2), "h2d_link_peak_GBps": round(link["h2d"], 2),
                        "restore_GBps": round(restore_gbps, 2), "scatter_verify_GBps": round(scatter_gbps, 1),
+                       "scatter_verify_note": "2 x payload over the scatter kernel's time; it reads the host image "
+                                              "over the link, which bounds it",
                        "verify_GBps": round(verify_gbps, 2), "verify_kernel_GBps": round(verify_kernel_gbps, 1)},
         "overlap": overlap,
         "gating": gating,

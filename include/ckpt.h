@@ -578,7 +578,7 @@ ckpt_status ckpt_peer_restore_info(ckpt_ctx* ctx, uint64_t* ids, uint64_t cap, u
  * The library keeps the fragment table, the tile table and the partial sums
  * in one fixed 6 MiB device array per GPU (held until the process ends).
  * Limits: at most 65536 fragments, chunks of at most 1 GiB (at 8 KiB tiles);
- * the image may be any size (it is packed in groups of at most 1 GiB that
+ * the image may be any size (it is packed in groups of at most 2 GiB that
  * reuse the array).  Every call on a GPU uses that GPU's array: calls whose
  * work overlaps on one GPU (different streams, not ordered by events) race
  * and give wrong sums; order them, e.g. one stream.

@@ -55,7 +55,9 @@ constexpr uint32_t kMaxTileShift = 13;
 // itself.
 //   pack:     fragment bytes -> image window; image byte x goes to dst + (x - dst_origin);
 //             a non-null release is an HSA signal value the launch sets to 0
-//             as it starts (after the stream's previous kernel finished)
+//             once workgroup 0 has done its work: a tile, a run of small ones, or
+//             with a capped grid its share of all (so the stream's previous
+//             kernel has finished)
 //   sums:     the sums the pack would compute, from the fragments alone (no image
 //             window is written); release as for the pack
 //   scatter:  image window -> fragment bytes (image byte x read at src + (x - src_origin))
@@ -182,6 +184,11 @@ struct FragArgs {
 // 13.0 -> 7.4, 16 MiB 12.0 -> 9.3, 64 MiB 30.5 -> 22.3 (128 KiB chunks by one
 // workgroup each: 13.0 -> 12.1 at 1 MiB, 11.5 -> 15.4 at 16 MiB); 1 MiB chunks
 // in tiles, image of 1 MiB 12.4 -> 9.6, 16 MiB 11.6 -> 10.7, 64 MiB 28.7 -> 28.3.
+// There is no lower line: every workgroup's scan weighs more the smaller the
+// chunks are, but so does the table path's reduce, one workgroup per chunk.
+// 64 MiB with 8 / 248 fragments: 4 KiB chunks 72.8 -> 44.0 / 75.4 -> 53.7, 1 KiB
+// 187 -> 156 / 190 -> 192, 256 bytes 650 -> 613 / 654 -> 735, 16 bytes 10164 ->
+// 9750 / 10182 -> 11756.
 constexpr uint64_t kSmallSpan = 64ull << 10;
 constexpr uint64_t kSmallChunksImage = 64ull << 20;
 constexpr uint64_t kSmallImage = 16ull << 20;
