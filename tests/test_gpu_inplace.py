@@ -49,17 +49,17 @@ def test_host_changes_between_calls_are_seen(tiles, mode):
     ck.close()
 
 
-@pytest.mark.parametrize("bounce", [0, 16 << 20])
+@pytest.mark.parametrize("bounce", [False, True])
 @pytest.mark.parametrize("size,chunk", [((700 << 20) - 77, 1 << 20), ((100 << 20) - 77, 3 * 4096 * 11),
                                         ((70 << 20) + 1, 40 << 20), (5000, 4096), (1, 1 << 20)])
 def test_verify_goes_through_its_ring(size, chunk, bounce):
     """Verify over fewer spans than its ring has slots and over more, with
     several wrong chunks; its kernels run for a small part of the transfer, so
-    that training beside it keeps the compute units."""
-    if bounce and chunk > 8 << 20:
-        bounce = 2 * chunk
+    that training beside it keeps the compute units.  (A launch lasts 6 to 20 us
+    by its events whatever it reads, 4 MiB are 70 us on the link.)"""
+    group = max(chunk, (4 << 20) // chunk * chunk) if bounce else 0
     tensors, host = random_byte_fragments([size // 3, size - size // 3], seed=size)
-    ck, snap = snapshot_and_check(tensors, host, chunk, 16, group=chunk if bounce else 0, bounce=bounce)
+    ck, snap = snapshot_and_check(tensors, host, chunk, 16, group=group, bounce=4 * group)
     P.ckpt_set_timing(ck.ctx, 1)
     img, sums = ck.host_image(snap)
     at = sorted({x // chunk: x for x in (0, img.size // 2, img.size - 1)}.values())  # one byte in a chunk
@@ -72,7 +72,7 @@ def test_verify_goes_through_its_ring(size, chunk, bounce):
     assert np.array_equal(P.ckpt_last_sums(ck.ctx), sums)
     t = P.ckpt_last_timing(ck.ctx, P.CKPT_OP_VERIFY)
     assert t["copies"] == t["kernels"] > 0 and t["copy_bytes"] == img.size
-    assert size < 1 << 20 or t["kernel_ms"] < 0.25 * t["copy_ms"]
+    assert size < 1 << 20 or t["kernel_ms"] < 0.3 * t["copy_ms"]
     ck.close()
 
 
