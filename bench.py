@@ -250,12 +250,26 @@ def timed_pack_average(d, bench):
     return sum(durs) / len(durs), len(durs)
 
 
+def copy_requests(image, groups, unit, pinned):
+    """DMA requests of one staged snapshot of `groups` chunk groups of `unit`
+    bytes (a group may go in halves); None when that is not how it is cut."""
+    import paper_2607_01646_amd as P
+
+    if not unit or groups != -(-image // unit):
+        return None
+    last = image - (groups - 1) * unit
+    whole = len(P.ckpt_debug_copy_plan(unit, groups=groups if pinned else 1))
+    return (groups - 1) * whole + (min(whole, len(P.ckpt_debug_copy_plan(last))) if pinned and groups > 1
+                                   else len(P.ckpt_debug_copy_plan(last)))
+
+
 def timed_d2h_from_trace(d, bench):
     """Per timed snapshot of the bench's workload-2 steps: image bytes / (last
     group copy's end - first group copy's start), from the memory-copy trace.
     The group copies are the device-to-host copies longer than 1 ms, in time
-    order: (warmup + steps) snapshots of one copy per chunk group each come
-    first (the calibration copies before them are blit kernels, not copies)."""
+    order: (warmup + steps) snapshots of copy_requests_per_snapshot (one per
+    chunk group where that is not given) each come first (the calibration
+    copies before them are blit kernels, not copies)."""
     import csv
     import glob
     import statistics
@@ -268,7 +282,7 @@ def timed_d2h_from_trace(d, bench):
             if "DEVICE_TO_HOST" in kind and b - a > 1_000_000:
                 copies.append((a, b))
     copies.sort()
-    per = bench["config"].get("groups_per_snapshot") or bench["roofline"]["launches"] // bench["steps"]
+    per = bench["config"].get("copy_requests_per_snapshot") or bench["config"].get("groups_per_snapshot") or bench["roofline"]["launches"] // bench["steps"]
     image = bench["config"]["image_bytes"]
     rates = []
     for k in range(bench["warmup"], bench["warmup"] + bench["steps"]):
@@ -1636,6 +1650,9 @@ def main():
                    "device_staging": ("none (direct D2H)" if args.direct
                                       else staging_text(args.staging_bytes, wl["chunk"])),
                    "groups_per_snapshot": int(sn["copies"]), "pack_launches_per_snapshot": int(sn["kernels"]),
+                   "copy_requests_per_snapshot": None if args.direct or args.staging_bytes else
+                   copy_requests(int(sn["copy_bytes"]), int(sn["copies"]),
+                                 (group_bytes or 1 << 30) // wl["chunk"] * wl["chunk"], not bounce),
                    "group_bytes": group_bytes or None, "pack_launch_bytes": launch_bytes or None,
                    "parallelism": "one rank, one GPU"},
         "roofline": roofline,

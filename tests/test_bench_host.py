@@ -79,6 +79,24 @@ def test_d2h_per_snapshot_from_a_copy_trace(bench, tmp_path):
     assert rates == [pytest.approx(1.0)] * 3 and med == pytest.approx(1.0)  # 20e6 bytes in 20 ms = 1 GB/s
 
 
+def test_d2h_per_snapshot_of_groups_copied_in_halves(bench, tmp_path):
+    """Two requests per group, on two engines at once: a snapshot's copies are
+    all of its requests."""
+    assert bench.copy_requests((9 << 28) + (16 << 20), 10, 1 << 28, False) == 20
+    assert bench.copy_requests(9 << 28, 9, 1 << 28, True) == 18
+    assert bench.copy_requests((3 << 25) + 5, 4, 1 << 25, True) == 4  # small pinned groups go whole
+    assert bench.copy_requests((3 << 25) + 5, 4, 1 << 25, False) == 7
+    assert bench.copy_requests(100, 3, 1 << 25, True) is None
+    ms = 1_000_000  # ns
+    rows = [(k * 100 * ms + g * 5 * ms + e, k * 100 * ms + (g + 1) * 5 * ms, "MEMORY_COPY_DEVICE_TO_HOST")
+            for k in range(5) for g in range(4) for e in (0, 1)]
+    _write(tmp_path / "x_memory_copy_trace.csv", ["Start_Timestamp", "End_Timestamp", "Direction"], rows)
+    b = {"steps": 3, "warmup": 2, "roofline": {"launches": 3},
+         "config": {"image_bytes": 20 * ms, "groups_per_snapshot": 4, "copy_requests_per_snapshot": 8}}
+    rates, med = bench.timed_d2h_from_trace(str(tmp_path), b)
+    assert rates == [pytest.approx(1.0)] * 3
+
+
 def test_more_than_one_gpu_is_refused():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True,
                        text=True, timeout=60)
