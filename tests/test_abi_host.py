@@ -324,3 +324,13 @@ def test_noalloc_pack_without_its_native_module(P, monkeypatch, other):
     with pytest.raises(ValueError, match="not a device tensor"):
         P.ckpt_pack_noalloc([t], t, t, stream=0, device=0)
     assert ckpt._native_pack()[0]() is None
+
+
+def test_native_module_has_no_thread_local_data(P):
+    """Loading it would slow down every other library's (see build.py)."""
+    from paper_2607_01646_amd import _ckpt_py
+
+    elf = open(_ckpt_py.__file__, "rb").read()
+    at, size, n = (int.from_bytes(elf[a:a + w], "little") for a, w in ((32, 8), (54, 2), (56, 2)))
+    types = [int.from_bytes(elf[at + k * size:at + k * size + 4], "little") for k in range(n)]
+    assert 1 in types and 7 not in types  # PT_LOAD, PT_TLS
