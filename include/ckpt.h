@@ -188,7 +188,8 @@ ckpt_status ckpt_register_tensors(ckpt_ctx* ctx, const ckpt_tensor* t, uint32_t 
  * sums chunk group by chunk group into the host image that does not hold
  * the newest committed snapshot (with direct_d2h: sums the fragments in place
  * and copies them straight into that image).  Pinned images of one chunk
- * group and at most 2 MiB (direct_d2h: 16 MiB) are written by the pack kernel
+ * group and at most 2 MiB (direct_d2h: 16 MiB when their fragments have at most
+ * 80 KiB on average) are written by the pack kernel
  * itself, over the link, unless timing is on, poison is set or the snapshot
  * is to be interrupted; their gate opens when they are written.  One image
  * always holds the newest
@@ -346,6 +347,11 @@ ckpt_status ckpt_debug_direct_plan(const uint64_t* nbytes, uint32_t n, uint64_t 
  * order) direct D2H into pinned images copies in a kernel (host-only):
  * by_kernel[k] is 1 for those.  Errors: EINVAL. */
 ckpt_status ckpt_debug_kernel_pieces(const uint64_t* nbytes, uint32_t n, uint8_t* by_kernel);
+
+/* Test access to whether the pack kernel writes a pinned image of one chunk
+ * group itself (host-only): pieces = its fragment pieces in direct D2H, 0 = full
+ * staging.  Errors: EINVAL. */
+ckpt_status ckpt_debug_in_kernel(uint64_t image_bytes, uint64_t pieces, uint32_t* in_kernel);
 
 /* Test access to how the copy of one staged chunk group is dealt to the DMA
  * engines (host-only): spans (room for 9 words) receives n requests, in the

@@ -102,6 +102,7 @@ def lib():
             "ckpt_plan": ([P(u64), u32, u64, u32, P(u64), P(u64), P(u64)], i32),
             "ckpt_debug_tile_plan": ([P(u64), u32, u64, u32, P(u64), P(u64), P(u32), P(u32)], i32),
             "ckpt_debug_kernel_pieces": ([P(u64), u32, P(C.c_uint8)], i32),
+            "ckpt_debug_in_kernel": ([u64, u64, P(u32)], i32),
             "ckpt_debug_copy_plan": ([u64, u32, u32, u32, P(u64), P(u32)], i32),
             "ckpt_debug_direct_plan": ([P(u64), u32, u64, u32, u64, P(u64), P(u64), P(u64), P(u64), P(u64)], i32),
             "ckpt_last_error": ([vp], C.c_char_p),
@@ -365,6 +366,13 @@ def ckpt_debug_kernel_pieces(nbytes):
     out = np.zeros(nb.size, dtype=np.uint8)
     _check(None, lib().ckpt_debug_kernel_pieces(_u64p(nb), nb.size, out.ctypes.data_as(C.POINTER(C.c_uint8))))
     return out.astype(bool)
+
+
+def ckpt_debug_in_kernel(image_bytes, pieces=0):
+    """Whether the pack kernel writes a pinned image of one chunk group itself."""
+    out = C.c_uint32()
+    _check(None, lib().ckpt_debug_in_kernel(image_bytes, pieces, C.byref(out)))
+    return bool(out.value)
 
 
 def ckpt_debug_copy_plan(group_bytes, engines=2, led=False, groups=1):

@@ -107,11 +107,24 @@ constexpr uint64_t kMaxDirectPieces = 65536;
 // DMA -> kernel, 64 KiB and 1 MiB chunks: staged, 64 KiB 53 -> 46, 1 MiB
 // 72 -> 50/57, 2 MiB 90 -> 71/76, 4 MiB 130 -> 113/123, 8 MiB 204 -> 236; the
 // gate waits for the kernel, so the line lies where that is still less than a
-// DMA snapshot of nothing.  Direct, where each fragment is a request of ~9 us
-// and the gate waits for the copies either way: 8 fragments, 1 MiB 132 -> 54,
-// 16 MiB 431 -> 369; 240 fragments, 1 MiB 2247 -> 55, 16 MiB 2635 -> 370.
-constexpr uint64_t kInKernelStaged = 2ull << 20;
+// DMA snapshot of nothing.  In direct mode, where each fragment is a request of
+// ~9 us and the gate waits for the copies either way, larger images too when
+// their pieces are at most kInKernelPiece on average: the kernel holds compute
+// units, and GEMMs beside it lose half as long as it runs.  Snapshot / what
+// 4096^3 bf16 products lost by it, in us, DMA -> kernel: 2 MiB in 8 fragments
+// 116/2 -> 82/23, 4 MiB in 8 156/4 -> 117/53, in 64 420/3 -> 117/53, 8 MiB in 8
+// 235/5 -> 218/110, 16 MiB in 8 400/4 -> 363/178, in 64 650/33 -> 362/177, in 240
+// 1460/10 -> 358/182.  (Staged, 1 MiB 74/2 -> 63/9, 2 MiB 97/0 -> 80/21.)
+constexpr uint64_t kInKernelImage = 2ull << 20;
 constexpr uint64_t kInKernelDirect = 16ull << 20;
+constexpr uint64_t kInKernelPiece = 80ull << 10;
+// Whether a pinned image of one group is written by the pack kernel; pieces:
+// fragment pieces of direct D2H, 0 = full staging.
+inline bool in_kernel_size(uint64_t image_bytes, uint64_t pieces)
+{
+    return image_bytes <= kInKernelImage ||
+           (image_bytes <= kInKernelDirect && image_bytes <= pieces * kInKernelPiece);
+}
 
 // GPU-side resources of one snapshot record, recycled between snapshots.
 struct RecRes {

@@ -1516,6 +1516,13 @@ ckpt_status ckpt_debug_kernel_pieces(const uint64_t* nbytes, uint32_t n, uint8_t
     return CKPT_OK;
 }
 
+ckpt_status ckpt_debug_in_kernel(uint64_t image_bytes, uint64_t pieces, uint32_t* in_kernel)
+{
+    if (!image_bytes || !in_kernel) return CKPT_EINVAL;
+    *in_kernel = in_kernel_size(image_bytes, pieces);
+    return CKPT_OK;
+}
+
 ckpt_status ckpt_debug_copy_plan(uint64_t group_bytes, uint32_t engines, uint32_t groups, uint32_t led,
                                  uint64_t* spans, uint32_t* n)
 {

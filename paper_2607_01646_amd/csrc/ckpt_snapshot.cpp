@@ -418,8 +418,8 @@ ckpt_status issue_in_kernel(ckpt_ctx* c, SnapRec& r, hipStream_t after)
 // or the canary asked for, it takes the way that those look into.
 bool small_image(const ckpt_ctx* c, const SnapRec& r, int32_t stop)
 {
-    return c->n_groups == 1 && c->I <= (c->direct ? kInKernelDirect : kInKernelStaged) && !c->bounce &&
-           !c->poison && !r.timed && stop < 0;
+    return c->n_groups == 1 && in_kernel_size(c->I, c->direct ? c->pieces.size() + c->small_first[1] : 0) &&
+           !c->bounce && !c->poison && !r.timed && stop < 0;
 }
 
 ckpt_status issue_snapshot(ckpt_ctx* c, SnapRec& r, hipStream_t after, uint64_t n_copy, int32_t stop)

@@ -193,6 +193,17 @@ def test_kernel_copies_leave_training_the_compute_units(P, seed):
         assert n[k].sum() + left.min() > n.sum() // 64
 
 
+@pytest.mark.parametrize("kib,pieces,want", [
+    (2048, 0, True), (2049, 0, False), (2048, 1, True), (2049, 8, False),
+    (4096, 64, True), (8192, 8, False), (16384, 8, False), (16384, 64, False), (16384, 204, False), (16384, 205, True),
+    (16385, 10000, False)])
+def test_large_fragments_are_left_to_the_engines(P, kib, pieces, want):
+    """Direct D2H: the kernel that writes a small image holds compute units for
+    as long as the link takes, which pays only where the engines take longer by
+    a request per small fragment."""
+    assert P.ckpt_debug_in_kernel(kib << 10, pieces) == want
+
+
 def test_plan_rejects_bad_geometry(P):
     with pytest.raises(P.CkptError):
         P.ckpt_plan([10, 20], 1000, 256)  # chunk not a multiple of the alignment
