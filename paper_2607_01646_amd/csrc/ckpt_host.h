@@ -100,6 +100,11 @@ struct Frag {
 };
 
 constexpr uint64_t kMaxDirectPieces = 65536;
+// Direct D2H into pinned images: most copies of one group.  They wait in the
+// engines' queues for a release that a launch behind them stores, so a call
+// that blocked on a full queue would never end: 16384 on one engine have run,
+// 65536 had not come back after 90 s.  4096 leave each at least 256 bytes of a 1 MiB queue.
+constexpr size_t kMaxRequests = 4096;
 
 // Images up to these sizes (one chunk group, pinned) are packed straight into
 // host memory: the kernels write over the link at its full rate (57 GB/s), and

@@ -156,7 +156,8 @@ bool direct_plan(const uint64_t* off, const uint64_t* nb, uint32_t n, uint64_t I
 // Which of a group's pieces (their bytes, in image order) a kernel copies and
 // not the engines: every one of up to kKernelPiece bytes, and larger ones of up
 // to kKernelPieceMax, smallest first, while all of them are at most
-// 1 / kKernelShare of the group.  Never the last, whose copy signals the
+// 1 / kKernelShare of the group, and any size, smallest first, that would make
+// more than kMaxRequests copies.  Never the last, whose copy signals the
 // group's.
 std::vector<uint8_t> kernel_pieces(const std::vector<uint64_t>& n)
 {
@@ -165,13 +166,17 @@ std::vector<uint8_t> kernel_pieces(const std::vector<uint64_t>& n)
     uint64_t total = 0, taken = 0;
     for (size_t k = 0; k < n.size(); ++k) {
         total += n[k];
-        if (k + 1 < n.size() && n[k] <= kKernelPieceMax) order.push_back(k);
+        if (k + 1 < n.size()) order.push_back(k);
     }
     std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return n[a] < n[b]; });
+    size_t requests = n.size();
     for (size_t k : order) {
-        if (n[k] > kKernelPiece && taken + n[k] > total / kKernelShare) break;
+        if (requests <= kMaxRequests && n[k] > kKernelPiece &&
+            (n[k] > kKernelPieceMax || taken + n[k] > total / kKernelShare))
+            break;
         taken += n[k];
         by_kernel[k] = 1;
+        --requests;
     }
     return by_kernel;
 }

@@ -193,6 +193,19 @@ def test_kernel_copies_leave_training_the_compute_units(P, seed):
         assert n[k].sum() + left.min() > n.sum() // 64
 
 
+@pytest.mark.parametrize("n", [4096, 4097, 31000, 65536])
+@pytest.mark.parametrize("size", [33 << 10, 600 << 10])
+def test_no_group_fills_an_engines_queue(P, n, size):
+    """Direct D2H: a group's copies wait for a launch behind them, so there are
+    at most 4096, the smallest pieces being left to the kernel."""
+    sizes = size + np.arange(n)[::-1]
+    k = P.ckpt_debug_kernel_pieces(sizes)
+    by_share = int(np.searchsorted(np.cumsum(np.sort(sizes[:-1])), sizes.sum() // 64, "right")) if size < 1 << 19 else 0
+    assert not k[-1] and k.sum() == max(n - 4096, by_share)
+    if k.any():
+        assert sizes[k].max() < sizes[:-1][~k[:-1]].min()
+
+
 @pytest.mark.parametrize("kib,pieces,want", [
     (2048, 0, True), (2049, 0, False), (2048, 1, True), (2049, 8, False),
     (4096, 64, True), (8192, 8, False), (16384, 8, False), (16384, 64, False), (16384, 204, False), (16384, 205, True),

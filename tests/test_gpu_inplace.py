@@ -219,3 +219,13 @@ def test_grid_blocks_bounds_what_writes_the_image(chunk):
         return min(best)
 
     assert seconds(1) > 2 * seconds(0)
+
+
+def test_more_pieces_than_a_group_has_requests():
+    """Direct D2H of 6000 pieces of 40 KiB in one group: 4096 copies by the
+    engines, the rest by the kernel."""
+    sizes = [(40 << 10) + 16 * (k % 7) - k % 3 for k in range(6000)]
+    assert P.ckpt_debug_kernel_pieces(sizes).sum() == 6000 - 4096
+    tensors, host = random_byte_fragments(sizes, seed=6)
+    ck, _ = snapshot_and_check(tensors, host, 1 << 20, direct=True)
+    ck.close()
