@@ -23,6 +23,7 @@ struct Geometry {
     uint64_t n_chunks;
     uint32_t tile_shift;
     uint32_t tiles_per_chunk; // chunk_bytes >> tile_shift
+    bool dense = false;       // at least one non-empty fragment for two tiles: most are shared by several
 };
 
 // Where tile t's bytes are, one 64-bit word per tile: the device address of

@@ -61,8 +61,16 @@ namespace {
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBlock = 512;      // lanes per workgroup (8 wave64)
-constexpr int kLdsFrags = 256;  // fragment offsets cached per tile (an 8 KiB tile holds at most 33 non-empty ones)
+constexpr int kLdsFrags = 256;  // fragment records cached per tile (an 8 KiB tile holds at most 33 non-empty ones)
 constexpr int kUnroll = 1;      // 16-byte vectors per lane per batch: one batch covers an 8 KiB tile
+// The pack of layouts in which most tiles are shared by fragments
+// (Geometry::dense).  Such a tile has a chain of dependent loads ahead of its
+// data, and twice the tiles are under way with half the lanes each.  Pack in
+// us, 256 lanes x 2 with two table lookups / 512 x 1 / 512 x 1 with the
+// fragments' records in LDS / this, records too: 65536 fragments of 9000 bytes
+// 210 / 278 / 250 / 206, of 4097 102 / 110 / 102 / 93, 262144 of 1 KiB 99 / 122
+// / 108 / 92 (large aligned fragments: 4 GiB 1367 / 1317 / 1320 / 1380).
+constexpr int kDenseBlock = 256, kDenseUnroll = 2;
 
 enum Mode { PACK = 0, SCATTER = 1, VERIFY = 2, SUMS = 3 };
 
@@ -331,10 +339,16 @@ __device__ __forceinline__ uint32_t find_frag_global(const FragDev* frags, uint3
     return lo;
 }
 
+// The fragments of a tile that several share: records in LDS, so that no vector
+// waits for its fragment's record behind the search.
+struct TileFrags {
+    uint64_t off[kLdsFrags], ptr[kLdsFrags], nbytes[kLdsFrags];
+};
+
 // One tile: wave w owns vectors [w * slice, (w + 1) * slice) of it.  Returns
 // the sum of the vectors this lane moved.
 template <int MODE, int BLOCK, int UNROLL, bool NTL, bool NTS>
-__device__ __forceinline__ unsigned long long move_tile(const Args& a, uint64_t t, uint64_t* s_off)
+__device__ __forceinline__ unsigned long long move_tile(const Args& a, uint64_t t, TileFrags& s)
 {
     static_assert(BLOCK * UNROLL * 16 == (1u << kMaxTileShift), "one batch per lane covers the largest tile");
     constexpr uint32_t kSlice = 64 * UNROLL; // vectors per wave slice
@@ -369,19 +383,32 @@ __device__ __forceinline__ unsigned long long move_tile(const Args& a, uint64_t 
         } else {
             const uint32_t f0 = tile_first(e), f1 = tile_last(e), nf = f1 - f0 + 1;
             const bool in_lds = f0 != f1 && nf <= (uint32_t)kLdsFrags;
+            FragDev F;
             if (in_lds) {
-                // Several fragments: their offsets go to LDS for the search.
+                // Several fragments: their records go to LDS for the search.
                 // Both barriers are workgroup-uniform (e depends on t only);
                 // the first keeps the previous tile's readers ahead of the refill.
                 __syncthreads();
-                for (uint32_t k = tid; k < nf; k += BLOCK) s_off[k] = a.frags[f0 + k].off;
+                for (uint32_t k = tid; k < nf; k += BLOCK) {
+                    const FragDev r = a.frags[f0 + k];
+                    s.off[k] = r.off;
+                    s.ptr[k] = r.ptr;
+                    s.nbytes[k] = r.nbytes;
+                }
                 __syncthreads();
+            } else {
+                F = a.frags[f0];
             }
-            FragDev F = a.frags[f0];
             for (uint32_t v = v0 + lane; v < v1; v += 64) {
                 const uint64_t x = base + 16ull * v;
-                if (f0 != f1)
-                    F = a.frags[in_lds ? f0 + find_frag_lds(s_off, nf, x) : find_frag_global(a.frags, f0, f1, x)];
+                if (in_lds) {
+                    const uint32_t k = find_frag_lds(s.off, nf, x);
+                    F.off = s.off[k];
+                    F.ptr = s.ptr[k];
+                    F.nbytes = s.nbytes[k];
+                } else if (f0 != f1) {
+                    F = a.frags[find_frag_global(a.frags, f0, f1, x)];
+                }
                 const uint64_t p = x - F.off;
                 if (MODE == SUMS) {
                     acc += vsum(fetch_general(F.ptr, F.nbytes, p));
@@ -403,9 +430,9 @@ __device__ __forceinline__ unsigned long long move_tile(const Args& a, uint64_t 
 
 // One tile and its sum, stored by lane 0 of the workgroup to partials[t].
 template <int MODE, int BLOCK, int UNROLL, bool NTL, bool NTS>
-__device__ __forceinline__ void do_tile(const Args& a, uint64_t t, uint64_t* s_off, unsigned long long* s_red)
+__device__ __forceinline__ void do_tile(const Args& a, uint64_t t, TileFrags& s_frags, unsigned long long* s_red)
 {
-    const unsigned long long acc = wave_sum(move_tile<MODE, BLOCK, UNROLL, NTL, NTS>(a, t, s_off));
+    const unsigned long long acc = wave_sum(move_tile<MODE, BLOCK, UNROLL, NTL, NTS>(a, t, s_frags));
     if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = acc;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -422,16 +449,16 @@ __device__ __forceinline__ void do_tile(const Args& a, uint64_t t, uint64_t* s_o
 template <int MODE, bool LOOP, int BLOCK = kBlock, int UNROLL = kUnroll, bool NTL = true, bool NTS = true>
 __global__ __launch_bounds__(BLOCK) void tile_kernel(Args a)
 {
-    __shared__ uint64_t s_off[kLdsFrags];
+    __shared__ TileFrags s_frags;
     __shared__ unsigned long long s_red[BLOCK / 64];
     const uint64_t first = blockIdx.x;
     if (LOOP) {
         for (uint64_t t = a.t_lo + first; t < a.t_hi; t += gridDim.x) {
-            do_tile<MODE, BLOCK, UNROLL, NTL, NTS>(a, t, s_off, s_red);
+            do_tile<MODE, BLOCK, UNROLL, NTL, NTS>(a, t, s_frags, s_red);
             __syncthreads(); // s_red is read before the next tile writes it
         }
     } else {
-        do_tile<MODE, BLOCK, UNROLL, NTL, NTS>(a, a.t_lo + first, s_off, s_red);
+        do_tile<MODE, BLOCK, UNROLL, NTL, NTS>(a, a.t_lo + first, s_frags, s_red);
     }
     if (MODE == PACK || MODE == SUMS) release_signal(a.release);
 }
@@ -523,7 +550,7 @@ constexpr int kSumsBlock = 256;
 
 __global__ __launch_bounds__(kSumsBlock) void sums_run_kernel(Args a)
 {
-    __shared__ uint64_t s_off[kLdsFrags];
+    __shared__ TileFrags s_frags;
     __shared__ unsigned long long s_red[kSumsBlock / 64];
     constexpr uint32_t kTileVecs = 1u << (kMaxTileShift - 4);
     const uint64_t t = a.t_lo + (uint64_t)kSumsTiles * blockIdx.x; // < t_hi (grid: ceil(tiles / kSumsTiles))
@@ -547,7 +574,7 @@ __global__ __launch_bounds__(kSumsBlock) void sums_run_kernel(Args a)
         if (threadIdx.x < kSumsTiles) a.partials[t + threadIdx.x] = s_red[2 * threadIdx.x] + s_red[2 * threadIdx.x + 1];
     } else {
         for (uint32_t k = 0; k < kSumsTiles && t + k < a.t_hi; ++k) {
-            do_tile<SUMS, kSumsBlock, 2, true, true>(a, t + k, s_off, s_red);
+            do_tile<SUMS, kSumsBlock, 2, true, true>(a, t + k, s_frags, s_red);
             __syncthreads(); // s_red is read before the next tile writes it
         }
     }
@@ -596,7 +623,7 @@ __global__ __launch_bounds__(kReduceBlock) void chunk_reduce_kernel(ReduceArgs r
 // of its XCD's L2, so this is for few workgroups (kReleaseChunks).
 __global__ __launch_bounds__(kBlock) void pack_chunks_kernel(Args a, unsigned long long* sums_out, uint32_t* ticket)
 {
-    __shared__ uint64_t s_off[kLdsFrags];
+    __shared__ TileFrags s_frags;
     __shared__ unsigned long long s_red[kBlock / 64];
     const uint64_t t0 = (uint64_t)blockIdx.x * a.g.tiles_per_chunk;
     const uint64_t t1 = t0 + a.g.tiles_per_chunk < a.g.n_tiles ? t0 + a.g.tiles_per_chunk : a.g.n_tiles;
@@ -606,7 +633,7 @@ __global__ __launch_bounds__(kBlock) void pack_chunks_kernel(Args a, unsigned lo
         const uint64_t end = (t1 << a.g.tile_shift) < a.g.image_bytes ? t1 << a.g.tile_shift : a.g.image_bytes;
         for (uint64_t x = lo + 16 * threadIdx.x; x < end; x += 16 * kBlock) acc += move_vector<PACK>(a, x);
     } else {
-        for (uint64_t t = t0; t < t1; ++t) acc += move_tile<PACK, kBlock, kUnroll, true, true>(a, t, s_off);
+        for (uint64_t t = t0; t < t1; ++t) acc += move_tile<PACK, kBlock, kUnroll, true, true>(a, t, s_frags);
     }
     acc = block_sum<kBlock>(acc, s_red);
     if (threadIdx.x == 0) sums_out[blockIdx.x] = acc;
@@ -637,12 +664,18 @@ hipError_t launch_tiles(const Args& a, uint32_t grid_cap, hipStream_t s, hipEven
     if (a.t_hi <= a.t_lo) return hipSuccess;
     const uint32_t per_run = kMaxTileShift - a.g.tile_shift; // log2 of the tiles in 8 KiB
     const uint64_t n = (a.t_hi - a.t_lo + (1ull << per_run) - 1) >> per_run;
-    const uint32_t grid = (uint32_t)std::min<uint64_t>(n, std::min(grid_cap, max_grid(kBlock)));
+    uint32_t block = kBlock, grid = (uint32_t)std::min<uint64_t>(n, std::min(grid_cap, max_grid(kBlock)));
     void (*kern)(Args) = per_run ? run_kernel<MODE> : grid == n ? tile_kernel<MODE, false> : tile_kernel<MODE, true>;
+    if (MODE == PACK && !per_run && a.g.dense) {
+        block = kDenseBlock;
+        grid = (uint32_t)std::min<uint64_t>(n, std::min(grid_cap, max_grid(kDenseBlock)));
+        kern = grid == n ? tile_kernel<PACK, false, kDenseBlock, kDenseUnroll>
+                         : tile_kernel<PACK, true, kDenseBlock, kDenseUnroll>;
+    }
     if (t0 && t1)
-        hipExtLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), 0, s, t0, t1, 0, a);
+        hipExtLaunchKernelGGL(kern, dim3(grid), dim3(block), 0, s, t0, t1, 0, a);
     else
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), 0, s, a);
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(block), 0, s, a);
     return hipGetLastError();
 }
 

@@ -150,8 +150,9 @@ extern "C" ckpt_status ckpt_pack_noalloc(const ckpt_tensor* t, uint32_t n, uint6
     batch.count = 0;
     batch.off = 0;
     const bool one_batch = n <= kArgFrags;
-    uint64_t off = 0;
+    uint64_t off = 0, bearing = 0; // non-empty fragments
     for (uint32_t i = 0; i < n; ++i) {
+        bearing += t[i].nbytes != 0;
         batch.f[batch.count].ptr = (uint64_t)(uintptr_t)t[i].dev_ptr;
         batch.f[batch.count++].nbytes = t[i].nbytes;
         off = align_up(off + t[i].nbytes, A);
@@ -162,6 +163,7 @@ extern "C" ckpt_status ckpt_pack_noalloc(const ckpt_tensor* t, uint32_t n, uint6
             batch.off = off;
         }
     }
+    g.dense = 2 * bearing >= g.n_tiles;
     const bool by_chunk = one_batch && C <= kSmallSpan && I <= kSmallChunksImage;
     const bool by_tile = one_batch && ts == kMaxTileShift && I <= kSmallImage;
     if (by_chunk || by_tile) {

@@ -889,6 +889,9 @@ ckpt_status ckpt_register_tensors(ckpt_ctx* c, const ckpt_tensor* t, uint32_t n)
     c->geo.image_bytes = c->I;
     c->geo.tile_shift = pl.tile_shift;
     c->geo.tiles_per_chunk = (uint32_t)(c->C >> pl.tile_shift);
+    uint64_t bearing = 0; // non-empty fragments
+    for (uint32_t i = 0; i < n; ++i) bearing += t[i].nbytes != 0;
+    c->geo.dense = 2 * bearing >= c->geo.n_tiles;
     c->geo.n_tiles = pl.n_tiles;
     c->geo.n_chunks = c->n_chunks;
 

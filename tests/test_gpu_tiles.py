@@ -118,6 +118,43 @@ def test_fragments_inside_a_word_are_read_at_the_rate_of_words(shift):
     assert sums_ms(4 + shift) < 1.12 * sums_ms(4)
 
 
+@pytest.mark.parametrize("grid", [0, 5])
+@pytest.mark.parametrize("n,size,align,empty", [(700, 16384 - 256, 256, 0), (700, 16384 + 16, 16, 0), (900, 9001, 16, 9),
+                                                (6000, 333, 256, 0), (20000, 17, 16, 3)])
+def test_layouts_around_a_fragment_for_two_tiles(n, size, align, empty, grid):
+    """Both shapes of the pack, on either side of their line and among empty
+    fragments, at any alignment."""
+    rng = np.random.default_rng(n)
+    flat = torch.from_numpy(rng.integers(0, 256, n * (size + 1) + 1, dtype=np.uint8)).cuda()
+    views = [flat[1 + k * (size + 1):1 + k * (size + 1) + size] for k in range(n)]
+    for k in range(empty):
+        views.insert(k * 7, flat[:0])
+    host = [host_bytes(v) for v in views]
+    ck, _ = snapshot_and_check(views, host, 1 << 16, align, grid=grid)
+    ck.close()
+    want, _, nc = O.pack(host, align, 1 << 16)
+    image, sums = torch.empty(want.size, dtype=torch.uint8, device="cuda"), torch.empty(nc, dtype=torch.int64, device="cuda")
+    P.ckpt_pack_noalloc(views, image, sums, chunk_bytes=1 << 16, align_bytes=align)
+    assert np.array_equal(host_bytes(image), want)
+    assert np.array_equal(host_bytes(sums).view(np.uint64), O.chunk_sums(want, 0, want.size, 1 << 16))
+
+
+def test_shared_tiles_are_packed_at_the_rate_of_whole_ones():
+    """Most tiles hold the ends of fragments: the pack took a third longer than
+    of one fragment of as many bytes with 512 lanes for each such tile."""
+    def pack_ms(n, size):
+        flat = torch.zeros(n * size, dtype=torch.uint8, device="cuda")
+        with P.Checkpointer([flat[k * size:(k + 1) * size] for k in range(n)], chunk_bytes=1 << 20) as ck:
+            P.ckpt_set_timing(ck.ctx, 1)
+            ms = []
+            for k in range(5):
+                ck.wait_committed(ck.snapshot(step=k))
+                ms.append(P.ckpt_last_timing(ck.ctx, P.CKPT_OP_SNAPSHOT)["kernel_ms"])
+            return min(ms)
+
+    assert pack_ms(65536, 9216) < 1.25 * pack_ms(1, 65536 * 9216)
+
+
 @pytest.mark.parametrize("shift", [0, 3, 8, 14])
 def test_unaligned_fragments_without_allocation(shift):
     _, views = shifted_views(shift, 77 + shift)
