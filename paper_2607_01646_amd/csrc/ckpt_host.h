@@ -43,7 +43,7 @@ constexpr uint64_t kDefaultLaunch = 0; // full-image staging: bytes per pack lau
 constexpr uint32_t kMaxMeta = 1u << 20;
 constexpr uint32_t kDefaultGrid = 0x7fffffff; // one workgroup per tile unless capped
 constexpr int kMaxEngines = 2;
-// Group copies of at least this many bytes are dealt to both engines in halves.
+// Group copies of at least this many bytes are dealt to both engines.
 // What an engine alone moves depends on the machine (29 to 57 GB/s seen, and
 // not the same for the two), both together fill the link on each; below, a
 // second request costs more than it gives.
@@ -60,27 +60,37 @@ inline bool split_copy(uint64_t n, int engines, uint64_t pinned_groups, uint64_t
 }
 // The lead: 16 MiB keep the link busy for 290 us, in which the rest of a group
 // of 1 GiB is packed (330 us); groups of less than four leads gain nothing.
-// It is part of its engine's half, so that each engine still moves half of
-// the group.  Snapshot to commit without / with it, where each engine alone
+// It is part of its engine's share, so that the other still has its own.
+// Snapshot to commit without / with it, where each engine alone
 // fills the link: 65 MiB 1336 / 1322 us, 120 MiB 2362 / 2329, 239 MB 4389 /
 // 4284, 1.5 GB 26744 / 26410, 2.8 GB 49514 / 49133.  (With all of the group
 // behind the lead on the other engine 239 MB took 4288 us there, and 7710
 // where that engine alone moves 29 GB/s.)
 constexpr uint64_t kLead = 16ull << 20;
+// Bytes of an n-byte group that its first engine moves when both do: half of
+// one of several groups, whose first engines alternate, and three quarters of an
+// only one.  There engine 0 alone nearly fills the link on every machine but
+// the first (41 GB/s), and engine 1 on some does not: 239 MB took 4400 us whole
+// on engine 0, 5323 in halves and 7707 mostly on engine 1 where that moves 29
+// GB/s.  A quarter is done in time from 14 GB/s on.  Where both fill the link,
+// whole / halves / this: 4380 / 4280 / 4315.
+inline uint64_t first_share(uint64_t n, uint64_t groups)
+{
+    return ((groups > 1 ? n / 2 : n / 4 * 3) + 4095) & ~4095ull;
+}
 // The requests of a staged group's copy of n bytes, in the order in which
-// they are issued: the lead if any, the (rest of the) first half on the
-// group's first engine (0), the second half on its other one.  Returns how many.
+// they are issued: the lead if any, the (rest of the) first `cut` bytes on the
+// group's first engine (0), what is left of n on its other one.  Returns how many.
 struct CopySpan {
     uint64_t lo, n;
     int engine;
 };
-inline int copy_spans(uint64_t n, bool halves, uint64_t lead, CopySpan out[3])
+inline int copy_spans(uint64_t n, uint64_t cut, uint64_t lead, CopySpan out[3])
 {
-    const uint64_t half = halves ? ((n / 2 + 4095) & ~4095ull) : n;
     int k = 0;
     if (lead) out[k++] = CopySpan{0, lead, 0};
-    out[k++] = CopySpan{lead, half - lead, 0};
-    if (half < n) out[k++] = CopySpan{half, n - half, 1};
+    out[k++] = CopySpan{lead, cut - lead, 0};
+    if (cut < n) out[k++] = CopySpan{cut, n - cut, 1};
     return k;
 }
 // Verify's device ring: slots of up to 64 MiB of whole chunks (at least one),

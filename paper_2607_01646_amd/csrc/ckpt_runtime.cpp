@@ -1536,9 +1536,8 @@ ckpt_status ckpt_debug_copy_plan(uint64_t group_bytes, uint32_t engines, uint32_
 {
     if (!group_bytes || !engines || !groups || !spans || !n) return CKPT_EINVAL;
     CopySpan sp[3];
-    *n = (uint32_t)copy_spans(group_bytes,
-                              split_copy(group_bytes, (int)std::min<uint32_t>(engines, kMaxEngines), groups,
-                                         group_bytes),
+    const bool split = split_copy(group_bytes, (int)std::min<uint32_t>(engines, kMaxEngines), groups, group_bytes);
+    *n = (uint32_t)copy_spans(group_bytes, split ? first_share(group_bytes, groups) : group_bytes,
                               led && engines > 1 && group_bytes >= 4 * kLead ? kLead : 0, sp);
     for (uint32_t k = 0; k < *n; ++k) {
         spans[3 * k] = sp[k].lo;

@@ -90,7 +90,7 @@ int issue_halves(ckpt_ctx* c, RecRes* res, uint64_t g, uint8_t* dst, hsa_agent_t
                  uint64_t n, const hsa_signal_t* dep, uint64_t lead)
 {
     CopySpan sp[3];
-    const int n_sp = copy_spans(n, in_halves(c, g), lead, sp);
+    const int n_sp = copy_spans(n, in_halves(c, g) ? first_share(n, c->n_groups) : n, lead, sp);
     int got = 0;
     for (int k = 0; k < n_sp; ++k) {
         const bool is_lead = lead && k == 0;

@@ -156,10 +156,11 @@ def test_direct_plan_brute_force(P):
 @pytest.mark.parametrize("n", [1, 4096, (8 << 20) - 1, 8 << 20, (8 << 20) + 1, (48 << 20) - 1, 48 << 20,
                                (64 << 20) - 16, 64 << 20, (64 << 20) + 8191, 239_000_016, 1 << 30])
 @pytest.mark.parametrize("groups", [1, 3])
-def test_copy_plan_gives_each_engine_half(P, n, led, groups):
-    """A staged group's copy: its requests cover it once, and each of two
-    engines moves half of it, with or without bytes that go ahead; of several
-    groups, which alternate between the engines, from 48 MiB on."""
+def test_copy_plan_gives_each_engine_its_share(P, n, led, groups):
+    """A staged group's copy: its requests cover it once, with or without bytes
+    that go ahead.  Each of two engines moves half of one of several groups,
+    which alternate between them, from 48 MiB on; of an only group the second
+    engine, which on some machines has half the link's rate, moves a quarter."""
     spans = P.ckpt_debug_copy_plan(n, 2, led, groups)
     least = (8 if groups == 1 else 48) << 20
     assert sorted(spans)[0][0] == 0 and all(b > 0 for _, b, _ in spans)
@@ -168,7 +169,7 @@ def test_copy_plan_gives_each_engine_half(P, n, led, groups):
     if n < least:
         assert by == [n, 0]
     else:
-        assert abs(by[0] - by[1]) <= 8192
+        assert abs(by[1] - (n / 2 if groups > 1 else n / 4)) <= 4100
     assert len(spans) == 1 + (n >= least) + (led and n >= 64 << 20)
     assert [b for _, b, _ in P.ckpt_debug_copy_plan(n, 1, led, groups)] == [n]
 
