@@ -150,7 +150,7 @@ struct RecRes {
     std::vector<hsa_signal_t> flagged;  // per group: the area-done copy after it finished
     std::vector<hsa_signal_t> piece_done; // direct D2H, per piece but each group's last (whose copy
                                           // signals `copied`): the piece's copy finished;
-                                          // else per group: the copy of its second half (issue_halves)
+                                          // else per group: the copy of its second share (issue_halves)
     hsa_signal_t dep_lead{0};           // the first group's lead (lead_bytes) packed
     hsa_signal_t lead_done{0};          // ... and copied
     int64_t* dep_lead_val = nullptr;
@@ -538,7 +538,7 @@ bool geometry_ok(uint64_t C, uint32_t A);
 // device image) and where that area starts.
 inline uint64_t group_lo(const ckpt_ctx* c, uint64_t g) { return g * c->G * c->C; }
 inline uint64_t group_hi(const ckpt_ctx* c, uint64_t g) { return std::min((g + 1) * c->G * c->C, c->I); }
-// Whether group g's staged copy is dealt to two engines in halves.
+// Whether group g's staged copy is dealt to two engines.
 inline bool in_halves(const ckpt_ctx* c, uint64_t g)
 {
     return split_copy(group_hi(c, g) - group_lo(c, g), c->n_d2h_engines, c->bounce ? 0 : c->n_groups, c->G * c->C);
@@ -607,9 +607,9 @@ ckpt_status issue_snapshot(ckpt_ctx* c, SnapRec& r, hipStream_t after, uint64_t 
 uint64_t issue_pieces(ckpt_ctx* c, RecRes* res, uint64_t g, uint8_t* dst, hsa_agent_t dst_agent,
                       const hsa_signal_t* first_dep, const hsa_amd_sdma_engine_id_t engine[2]);
 // Copy group g, n bytes at src (device staging) to dst (pinned), after *dep:
-// its halves on the two engines, or in one request when it is small or there is
-// one engine; with lead > 0 (two engines, less than a half) the first `lead`
-// bytes of the first half go ahead, after res->dep_lead.  Returns the signals
+// its shares on the two engines, or in one request when it is small or there is
+// one engine; with lead > 0 (two engines, less than a share) the first `lead`
+// bytes of the first share go ahead, after res->dep_lead.  Returns the signals
 // of group_signals() that will be lowered: fewer means that a request could not
 // be issued (the signals of what was not issued are 0).
 int issue_halves(ckpt_ctx* c, RecRes* res, uint64_t g, uint8_t* dst, hsa_agent_t dst_agent, const uint8_t* src,

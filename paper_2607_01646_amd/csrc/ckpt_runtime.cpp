@@ -7,7 +7,7 @@
 //                  pack kernel (fragments -> staging, tile sums)
 //                  event captured[g]            <- the gate waits on this
 //                  release kernel: dep[g] = 0
-//   SDMA engines : (poll dep[g]) copy the halves of staging(g) -> pinned image -> copied[g], piece_done[g]
+//   SDMA engines : (poll dep[g]) copy the shares of staging(g) -> pinned image -> copied[g], piece_done[g]
 //   counter engine: (after both) 8-byte copy: area_done[area(g)] = use count
 //   after the last group: one reduce kernel (tile sums -> chunk sums), release
 //   dep_sums; SDMA copies the chunk sums.
